@@ -220,37 +220,6 @@ __global__ void k_search_header(SearchHeader* h, int64_t capacity, int64_t n_wor
 constexpr int kCompactThreads = 256;
 constexpr int kCompactBlocks = 1024;
 
-// Hits with pass[i] set, among the first min(*n_dev, cap), appended to out in
-// wavefront-sized groups (one atomic per wavefront).
-__global__ __launch_bounds__(kCompactThreads) void k_compact_matches(
-    const plast_hit_t* __restrict__ hits, const int32_t* __restrict__ gscore, const uint8_t* __restrict__ pass,
-    const unsigned long long* __restrict__ n_dev, int64_t cap, plast_match_t* __restrict__ out,
-    unsigned long long* __restrict__ n_out) {
-  const int64_t n = min((int64_t)*n_dev, cap);
-  const int lane = __lane_id();
-  for (int64_t base = (int64_t)blockIdx.x * kCompactThreads; base < n; base += (int64_t)gridDim.x * kCompactThreads) {
-    const int64_t i = base + threadIdx.x;
-    const bool take = i < n && pass[i];
-    const unsigned long long m = __ballot(take);
-    if (!m) continue;
-    const int leader = __ffsll((long long)m) - 1;
-    unsigned long long b = 0;
-    if (lane == leader) b = atomicAdd(n_out, (unsigned long long)__popcll(m));
-    b = __shfl(b, leader);
-    if (take) {
-      const plast_hit_t h = hits[i];
-      plast_match_t o;
-      o.seq1 = h.seq1;
-      o.pos1 = h.pos1;
-      o.seq2 = h.seq2;
-      o.pos2 = h.pos2;
-      o.score = h.score;
-      o.gscore = gscore[i];
-      out[b + __popcll(m & ((1ull << lane) - 1ull))] = o;
-    }
-  }
-}
-
 // Segment of query sequence q: the s with seg_first[s] <= q < seg_first[s + 1].
 __device__ __forceinline__ int segment_of(const int32_t* __restrict__ seg_first, int n_seg, int q) {
   int lo = 0, hi = n_seg - 1;
@@ -359,6 +328,81 @@ __global__ __launch_bounds__(kCompactThreads) void k_segment_scatter(
   }
 }
 
+// The same two passes for up to kTileSegs segments, and the plain compaction (one
+// segment, seg_first null): counters per workgroup in LDS, one global atomic
+// per (tile of kMatchTile hits, segment) instead of one per (wavefront,
+// segment).  Atomics on one address take about 12 ns each whatever the number of
+// workgroups, so with a few segments they were the whole cost: 12.7M hits in 3
+// segments took 2.38 ms in each pass, and take 0.08 and 0.12 ms here.  Above
+// kTileSegs the counters would not leave room for several workgroups on a compute
+// unit, and so many addresses do not contend: the kernels above run.
+constexpr int kMatchPer = 8;
+constexpr int kMatchTile = kCompactThreads * kMatchPer;
+constexpr int kTileSegs = 2048;
+static_assert(kMatchTile <= 1 << 16 && kTileSegs < 1 << 15, "a place packs a segment and a rank in 31 bits");
+
+__global__ __launch_bounds__(kCompactThreads) void k_tile_count(
+    const plast_hit_t* __restrict__ hits, const uint8_t* __restrict__ pass, const unsigned long long* __restrict__ n_dev,
+    int64_t cap, const int32_t* __restrict__ seg_first, int n_seg, unsigned long long* __restrict__ cnt) {
+  __shared__ uint32_t c[kTileSegs];
+  const int64_t n = min((int64_t)*n_dev, cap);
+  for (int s = threadIdx.x; s < n_seg; s += kCompactThreads) c[s] = 0;
+  __syncthreads();
+  // one workgroup counts fewer than 2^32 hits: cap < 2^63 / 20 records of one allocation, over its share of the grid
+  for (int64_t base = (int64_t)blockIdx.x * kMatchTile; base < n; base += (int64_t)gridDim.x * kMatchTile) {
+#pragma unroll
+    for (int j = 0; j < kMatchPer; ++j) {
+      const int64_t i = base + j * kCompactThreads + threadIdx.x;
+      if (i < n && pass[i]) atomicAdd(&c[segment_of(seg_first, n_seg, hits[i].seq1)], 1u);
+    }
+  }
+  __syncthreads();
+  for (int s = threadIdx.x; s < n_seg; s += kCompactThreads)
+    if (c[s]) atomicAdd(&cnt[s], (unsigned long long)c[s]);
+}
+
+__global__ __launch_bounds__(kCompactThreads) void k_tile_scatter(
+    const plast_hit_t* __restrict__ hits, const int32_t* __restrict__ gscore, const uint8_t* __restrict__ pass,
+    const unsigned long long* __restrict__ n_dev, int64_t cap, const int32_t* __restrict__ seg_first, int n_seg,
+    unsigned long long* __restrict__ cur, plast_match_t* __restrict__ out) {
+  __shared__ uint32_t c[kTileSegs];
+  __shared__ unsigned long long first[kTileSegs];
+  const int64_t n = min((int64_t)*n_dev, cap);
+  for (int64_t base = (int64_t)blockIdx.x * kMatchTile; base < n; base += (int64_t)gridDim.x * kMatchTile) {
+    for (int s = threadIdx.x; s < n_seg; s += kCompactThreads) c[s] = 0;
+    __syncthreads();
+    uint32_t place[kMatchPer];  // segment << 16 | rank in the tile, or ~0
+#pragma unroll
+    for (int j = 0; j < kMatchPer; ++j) {
+      const int64_t i = base + j * kCompactThreads + threadIdx.x;
+      place[j] = ~0u;
+      if (i < n && pass[i]) {
+        const int seg = seg_first ? segment_of(seg_first, n_seg, hits[i].seq1) : 0;
+        place[j] = ((uint32_t)seg << 16) | atomicAdd(&c[seg], 1u);
+      }
+    }
+    __syncthreads();
+    for (int s = threadIdx.x; s < n_seg; s += kCompactThreads)
+      if (c[s]) first[s] = atomicAdd(&cur[s], (unsigned long long)c[s]);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kMatchPer; ++j) {
+      if (place[j] == ~0u) continue;
+      const int64_t i = base + j * kCompactThreads + threadIdx.x;
+      const plast_hit_t h = hits[i];
+      plast_match_t o;
+      o.seq1 = h.seq1;
+      o.pos1 = h.pos1;
+      o.seq2 = h.seq2;
+      o.pos2 = h.pos2;
+      o.score = h.score;
+      o.gscore = gscore[i];
+      out[first[place[j] >> 16] + (place[j] & 0xffffu)] = o;
+    }
+    __syncthreads();
+  }
+}
+
 __global__ void k_zero_u64(unsigned long long* __restrict__ p, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0ull;
 }
@@ -392,22 +436,33 @@ int search_enqueue_impl(const plast_bank_t* a, const plast_index_t* b, const pla
     rc = gapped_filter_impl(&va, b, d_hits, capacity, ungapped_n_hits_dev(uws), g, d_gscore, d_pass, s);
     if (rc != PLAST_OK) return rc;
     const int64_t blocks = min((int64_t)kCompactBlocks, (capacity + kCompactThreads - 1) / kCompactThreads);
+    const int64_t tiles = min((int64_t)kCompactBlocks, (capacity + kMatchTile - 1) / kMatchTile);
     const unsigned long long* nh = ungapped_n_hits_dev(uws);
     if (d_matches && d_seg_first) {
       unsigned long long* off = (unsigned long long*)d_seg_off;
       unsigned long long* cur = off + (n_seg + 1);
+      const bool tiled = n_seg <= kTileSegs;
       hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, off, n_seg + 1);
-      hipLaunchKernelGGL(k_segment_count, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s,
-                         (const plast_hit_t*)d_hits, (const uint8_t*)d_pass, nh, capacity, d_seg_first, (int)n_seg,
-                         off);
+      if (tiled)
+        hipLaunchKernelGGL(k_tile_count, dim3((unsigned)tiles), dim3(kCompactThreads), 0, s, (const plast_hit_t*)d_hits,
+                           (const uint8_t*)d_pass, nh, capacity, d_seg_first, (int)n_seg, off);
+      else
+        hipLaunchKernelGGL(k_segment_count, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s,
+                           (const plast_hit_t*)d_hits, (const uint8_t*)d_pass, nh, capacity, d_seg_first, (int)n_seg,
+                           off);
       hipLaunchKernelGGL(k_segment_scan, dim3(1), dim3(256), 0, s, off, (int)n_seg, cur, &hdr->n_match);
-      hipLaunchKernelGGL(k_segment_scatter, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s,
-                         (const plast_hit_t*)d_hits, (const int32_t*)d_gscore, (const uint8_t*)d_pass, nh, capacity,
-                         d_seg_first, (int)n_seg, cur, d_matches);
+      if (tiled)
+        hipLaunchKernelGGL(k_tile_scatter, dim3((unsigned)tiles), dim3(kCompactThreads), 0, s,
+                           (const plast_hit_t*)d_hits, (const int32_t*)d_gscore, (const uint8_t*)d_pass, nh, capacity,
+                           d_seg_first, (int)n_seg, cur, d_matches);
+      else
+        hipLaunchKernelGGL(k_segment_scatter, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s,
+                           (const plast_hit_t*)d_hits, (const int32_t*)d_gscore, (const uint8_t*)d_pass, nh, capacity,
+                           d_seg_first, (int)n_seg, cur, d_matches);
     } else if (d_matches) {
-      hipLaunchKernelGGL(k_compact_matches, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s,
-                         (const plast_hit_t*)d_hits, (const int32_t*)d_gscore, (const uint8_t*)d_pass, nh, capacity,
-                         d_matches, &hdr->n_match);
+      hipLaunchKernelGGL(k_tile_scatter, dim3((unsigned)tiles), dim3(kCompactThreads), 0, s, (const plast_hit_t*)d_hits,
+                         (const int32_t*)d_gscore, (const uint8_t*)d_pass, nh, capacity, (const int32_t*)nullptr, 1,
+                         &hdr->n_match, d_matches);
     }
   }
   PLAST_HIP(hipGetLastError());

@@ -113,3 +113,33 @@ def test_search_grouped_and_ungrouped_matches(setup):
     for j in range(len(first)):
         part = grouped[off[j]:off[j + 1]]
         assert ((part[:, 0] >= seg[j]) & (part[:, 0] < seg[j + 1])).all()
+
+
+@pytest.mark.parametrize("n_seg", [1, 3, 255, 2048, 2049])
+def test_search_segments_at_the_edges_of_the_grouping(setup, n_seg):
+    """Segment counts around the limit of the counters in LDS, empty segments
+    among them: the matches are those of the ungrouped search, each in its
+    segment's slice."""
+    B, S, w, res = setup
+    rng = np.random.default_rng(n_seg)
+    query = synth.random_bank(rng, 2060, 5, 40)
+    n = query.n_seqs
+    sr = B.Searcher(res.index, query.codes.shape[0], n, res.items_bound(query.codes.shape[0], None), 4_000_000,
+                    params.S1, params.S2)
+    sr.codes.copy_(torch.from_numpy(query.codes))
+    sr.starts.copy_(torch.from_numpy(query.seq_start))
+    sr.enqueue(query.codes.shape[0], n)
+    flat = S.canonical(sr.matches[:sr.result()["n_matches"]].cpu().numpy())
+    cuts = np.sort(rng.integers(0, n + 1, n_seg - 1))  # repeated cuts: empty segments
+    seg = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    sr.seg_first[:n_seg + 1].copy_(torch.from_numpy(seg))
+    sr.enqueue(query.codes.shape[0], n, n_seg=n_seg)
+    r = sr.result()
+    grouped = sr.matches[:r["n_matches"]].cpu().numpy()
+    off = sr.seg_off[:n_seg + 1].cpu().numpy()
+    assert r["status"] == B.OK and len(flat) == r["n_matches"] > 1000
+    assert np.array_equal(S.canonical(grouped), flat)
+    assert np.array_equal(np.diff(off), np.diff(np.searchsorted(flat[:, 0], seg)))
+    for j in range(n_seg):
+        part = grouped[off[j]:off[j + 1], 0]
+        assert ((part >= seg[j]) & (part < seg[j + 1])).all()
