@@ -30,6 +30,9 @@
 // item with one global atomic (a wavefront whose reservation does not fit the
 // staging area writes directly).  Order of hits is unspecified.
 //
+// The BATCHED schedule runs matrices of small entries and banks of enough rows a
+// key on the matrix cores instead (ungapped_mfma.h), on items of 64 rows.
+//
 // Schedules.  PLAIN: one grid per key with candidate pairs, in key order, one
 // item of 4096 columns per workgroup (the paper's one-launch-per-seed GPU
 // offload, Sec. 5.2.1, without its per-seed copies).  BATCHED: a device work
@@ -83,13 +86,15 @@ struct UngappedArgs {
   int64_t capacity;
   unsigned long long* n_hits;
   int16_t mat[kNLet * kNLet];  // [a letter][b letter], separator row/column = kSepScore
+  float thrf;                  // threshold of the matrix-core tile
 };
 
 // Hits found in an item are staged in LDS as (row | score << 5, seq2, pos2).
 constexpr int kHitSlots = 1024;
 
-struct __align__(16) Smem {
-  uint8_t prof[kProfBytes];            // 8-byte entries (offset 0)
+template <int GROUPS>  // 4-row groups that a tile may have
+struct __align__(16) SmemT {
+  uint8_t prof[GROUPS * kProfRG];      // 8-byte entries (offset 0)
   uint8_t rowlet[kSpan * kTileRows];   // read as 4-byte groups
   int32_t rowq[kTileRows];
   int32_t rowseq[kTileRows];
@@ -105,6 +110,7 @@ struct __align__(16) Smem {
   unsigned long long hit_base;
   uint16_t mat[kNLet * kNLet];         // profile values (int16 or binary16 bits)
 };
+typedef SmemT<kRowGroups> Smem;
 static_assert(offsetof(Smem, rowlet) % 16 == 0 && offsetof(Smem, rowq) % 4 == 0, "LDS alignment");
 
 template <bool F16>
@@ -138,9 +144,9 @@ __device__ __forceinline__ int to_int(vec2<F16> v, int half) {
   return half ? (int)v.y : (int)v.x;
 }
 
-template <bool F16>
-__device__ __forceinline__ void smem_init(const UngappedArgs& A, Smem& S) {
-  for (int i = threadIdx.x; i < kNLet * kNLet; i += kThreads) {
+template <bool F16, int NT, int GROUPS>
+__device__ __forceinline__ void smem_init(const UngappedArgs& A, SmemT<GROUPS>& S) {
+  for (int i = threadIdx.x; i < kNLet * kNLet; i += NT) {
     if constexpr (F16)
       S.mat[i] = __builtin_bit_cast(uint16_t, (_Float16)A.mat[i]);
     else
@@ -155,8 +161,9 @@ __device__ __forceinline__ void smem_init(const UngappedArgs& A, Smem& S) {
 // Rows of the tile (bank-a occurrences row0 .. row0+rows-1 of the key) and
 // the 44-step profile of its first `groups` 4-row groups (rows past `rows`
 // hold separators).  Called by all threads (contains barriers).
+template <int NT, int GROUPS>
 __device__ __forceinline__ void build_profile(const UngappedArgs& A, const WorkItem& it, int64_t a0, int rows,
-                                              int groups, Smem& S) {
+                                              int groups, SmemT<GROUPS>& S) {
   const int tid = threadIdx.x;
   if (tid < kTileRows) {
     int q = -1, sq = 0, ps = 0;
@@ -172,7 +179,7 @@ __device__ __forceinline__ void build_profile(const UngappedArgs& A, const WorkI
   }
   __syncthreads();
   const int nr = 4 * groups;
-  for (int idx = tid; idx < kSpan * nr; idx += kThreads) {
+  for (int idx = tid; idx < kSpan * nr; idx += NT) {
     int t = idx / nr, r = idx - t * nr;
     int q = S.rowq[r];
     int letter = kPadCode;
@@ -184,7 +191,7 @@ __device__ __forceinline__ void build_profile(const UngappedArgs& A, const WorkI
   }
   __syncthreads();
   // prof[rg][t][c] = scores of rows 4rg..4rg+3 at step t against bank-b letter c
-  for (int e = tid; e < groups * kSpan * kNLet; e += kThreads) {
+  for (int e = tid; e < groups * kSpan * kNLet; e += NT) {
     int rg = e / (kSpan * kNLet);
     int rem = e - rg * (kSpan * kNLet);
     int t = rem / kNLet;
@@ -206,7 +213,7 @@ __device__ __forceinline__ void build_profile(const UngappedArgs& A, const WorkI
 // win: the window as (letter * 8) bytes, byte b = position q - 20 + b.
 // m receives best-right + best-left of every row (register i: rows 2i, 2i+1).
 template <bool F16, int RG>
-__device__ __forceinline__ void scan_window(const Smem& S, const uint32_t (&win)[11], vec2<F16> (&m)[2 * RG]) {
+__device__ __forceinline__ void scan_window(const uint8_t* prof, const uint32_t (&win)[11], vec2<F16> (&m)[2 * RG]) {
   typedef vec2<F16> V;
   constexpr int NP = 2 * RG;
   V s[NP];
@@ -214,7 +221,7 @@ __device__ __forceinline__ void scan_window(const Smem& S, const uint32_t (&win)
   auto load = [&](int t, uint2(&dst)[RG]) {
     const int bidx = t < kRight ? kNbr + t : (kSpan - 1) - t;
     const uint32_t c8 = (win[bidx >> 2] >> (8 * (bidx & 3))) & 0xffu;
-    const uint8_t* p = S.prof + c8 + t * kProfT;
+    const uint8_t* p = prof + c8 + t * kProfT;
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) dst[rg] = *(const uint2*)(p + rg * kProfRG);
   };
@@ -328,8 +335,8 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 // so the ones that fit form a prefix of the staging area; the one that
 // straddles its end (at most one) records where the prefix stops, and it and
 // every later one write their hits directly.
-template <bool F16, int RG>
-__device__ __forceinline__ void emit_hits(const UngappedArgs& A, Smem& S, const vec2<F16> (&m)[2 * RG],
+template <bool F16, int RG, int GROUPS>
+__device__ __forceinline__ void emit_hits(const UngappedArgs& A, SmemT<GROUPS>& S, const vec2<F16> (&m)[2 * RG],
                                           uint32_t mask, int s2, int p2) {
   const uint32_t any = wave_or(mask);  // every lane of the wavefront takes part
   if (!any || !mask) return;
@@ -362,7 +369,8 @@ __device__ __forceinline__ void emit_hits(const UngappedArgs& A, Smem& S, const 
 
 // Called by all threads (contains barriers); ends with a barrier so the next
 // item may overwrite the staging area and the row data.
-__device__ __forceinline__ void flush_hits(const UngappedArgs& A, Smem& S) {
+template <int NT, int GROUPS>
+__device__ __forceinline__ void flush_hits(const UngappedArgs& A, SmemT<GROUPS>& S) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const int n = min(S.n_hit, S.n_fit);
@@ -374,7 +382,7 @@ __device__ __forceinline__ void flush_hits(const UngappedArgs& A, Smem& S) {
   __syncthreads();
   const int n = __builtin_amdgcn_readfirstlane(S.n_flush);
   const unsigned long long base = S.hit_base;
-  for (int e = threadIdx.x; e < n; e += kThreads) {
+  for (int e = threadIdx.x; e < n; e += NT) {
     if (base + e < (unsigned long long)A.capacity) {
       const uint32_t rs = S.hit_rs[e];
       plast_hit_t h;
@@ -397,22 +405,23 @@ __device__ __forceinline__ void load_window_raw(const UngappedArgs& A, int q2, u
 
 // The item's columns against its first 4 RG rows (rows <= 4 RG), then the
 // flush of its hits.  Called by all threads (contains barriers).
-template <bool F16, int RG>
-__device__ void run_tile(const UngappedArgs& A, const WorkItem& it, int64_t a0, int64_t b0, int rows, Smem& S) {
+template <bool F16, int RG, int NT, int GROUPS>
+__device__ __forceinline__ void run_tile(const UngappedArgs& A, const WorkItem& it, int64_t a0, int64_t b0, int rows,
+                                         SmemT<GROUPS>& S) {
   const int tid = threadIdx.x;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t valid = valid_rows_mask(rows);
-  build_profile(A, it, a0, rows, RG, S);
+  build_profile<NT>(A, it, a0, rows, RG, S);
 
-  // Lane columns: col0 + tid + kThreads * k.  Column data is software-pipelined:
+  // Lane columns: col0 + tid + NT * k.  Column data is software-pipelined:
   // the occurrence two columns ahead and the window one column ahead are in
   // flight while the current column is scanned.
   const int col_end = it.col0 + it.ncols;
   int nk = 0;  // column steps of this wavefront
-  while (nk < kMaxColsPerLane && it.col0 + wid * 64 + kThreads * nk < col_end) ++nk;
+  while (it.col0 + wid * 64 + NT * nk < col_end) ++nk;
   nk = __builtin_amdgcn_readfirstlane(nk);
   auto occ_index = [&](int k) {
-    const int j = it.col0 + tid + kThreads * k;
+    const int j = it.col0 + tid + NT * k;
     return b0 + (j < col_end ? j : it.col0);
   };
   int q_cur = 0, s_cur = 0, q_nxt = 0, s_nxt = 0;
@@ -429,7 +438,7 @@ __device__ void run_tile(const UngappedArgs& A, const WorkItem& it, int64_t a0, 
     s_nxt = A.b.occ_seq[o];
   }
   for (int k = 0; k < nk; ++k) {
-    const bool active = it.col0 + tid + kThreads * k < col_end;
+    const bool active = it.col0 + tid + NT * k < col_end;
     const int q2 = q_cur, s2 = s_cur;
     uint32_t win[11];
     const int sh = (q2 - kNbr) & 3;
@@ -447,11 +456,11 @@ __device__ void run_tile(const UngappedArgs& A, const WorkItem& it, int64_t a0, 
     }
     const int st2 = (int)A.b.seq_start[s2];
     vec2<F16> m[2 * RG];
-    scan_window<F16, RG>(S, win, m);
+    scan_window<F16, RG>(S.prof, win, m);
     const uint32_t mask = active ? (hit_mask<F16, RG>(A.thr, m) & valid) : 0u;
     emit_hits<F16, RG>(A, S, m, mask, s2, q2 - st2);
   }
-  flush_hits(A, S);
+  flush_hits<NT>(A, S);
 }
 
 // All threads of the workgroup call run_item with the same item (it contains
@@ -465,16 +474,18 @@ __device__ void run_item(const UngappedArgs& A, const WorkItem it, Smem& S) {
   const int rows = __builtin_amdgcn_readfirstlane(min(kTileRows, n1 - it.row0));
   const int64_t b0 = A.b.key_off[it.key];
   if (rows <= 4)
-    run_tile<F16, 1>(A, it, a0, b0, rows, S);
+    run_tile<F16, 1, kThreads>(A, it, a0, b0, rows, S);
   else if (rows <= 8)
-    run_tile<F16, 2>(A, it, a0, b0, rows, S);
+    run_tile<F16, 2, kThreads>(A, it, a0, b0, rows, S);
   else if (rows <= 12)
-    run_tile<F16, 3>(A, it, a0, b0, rows, S);
+    run_tile<F16, 3, kThreads>(A, it, a0, b0, rows, S);
   else if (rows <= 16)
-    run_tile<F16, 4>(A, it, a0, b0, rows, S);
+    run_tile<F16, 4, kThreads>(A, it, a0, b0, rows, S);
   else
-    run_tile<F16, kRowGroups>(A, it, a0, b0, rows, S);
+    run_tile<F16, kRowGroups, kThreads>(A, it, a0, b0, rows, S);
 }
+
+#include "ungapped_mfma.h"
 
 constexpr int kPlainCols = 4096;  // item width of the PLAIN schedule
 
@@ -482,7 +493,7 @@ template <bool F16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_ungapped_plain(UngappedArgs A, int32_t key, int32_t n_row_tiles, int32_t n2) {
   __shared__ Smem S;
-  smem_init<F16>(A, S);
+  smem_init<F16, kThreads>(A, S);
   __syncthreads();
   WorkItem it;
   it.key = key;
@@ -493,19 +504,18 @@ void k_ungapped_plain(UngappedArgs A, int32_t key, int32_t n_row_tiles, int32_t 
 }
 
 // Workspace header of the BATCHED schedule: UngappedCounters at 0, queue
-// counters at 32 (kMaxQueues int32), both cleared by the first kernel.
+// counters at 32 (kMaxQueues int32), the length of the list at 64, all cleared
+// by the first kernel.
 constexpr int kCtrOffset = 32;
-constexpr int kHeaderDwords = 16;
+constexpr int kListOffset = 64;
+constexpr int kHeaderDwords = 17;
 static_assert(sizeof(UngappedCounters) <= kCtrOffset, "counter header");
-static_assert(kCtrOffset + 4 * kMaxQueues <= 4 * kHeaderDwords, "queue counters");
+static_assert(kCtrOffset + 4 * kMaxQueues <= kListOffset && kListOffset + 4 <= 4 * kHeaderDwords, "queue counters");
 
-template <bool F16>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void k_ungapped_persistent(UngappedArgs A, const WorkItem* __restrict__ items,
-                           const UngappedCounters* __restrict__ cnt, int32_t* __restrict__ ctr, int32_t n_queues) {
-  __shared__ Smem S;
-  smem_init<F16>(A, S);
-  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : cnt->n_items);
+// Pops the items of the work list until every queue is empty.
+template <typename Run>
+__device__ __forceinline__ void work_loop(int n_items, int32_t* __restrict__ ctr, int32_t n_queues, int32_t* slot,
+                                          Run run) {
   const int q0 = (int)(blockIdx.x % (unsigned)n_queues);  // workgroups are dealt to XCDs round robin
   for (int j = 0; j < n_queues; ++j) {
     const int q = (q0 + j) % n_queues;
@@ -513,17 +523,37 @@ void k_ungapped_persistent(UngappedArgs A, const WorkItem* __restrict__ items,
     // The item index is read back as a scalar so that the loop exit is
     // uniform: with a per-lane exit the compiler may let lanes other than
     // thread 0 reach a barrier before thread 0 has fetched the next item.  The
-    // second barrier keeps thread 0 from overwriting S.item (next item or next
+    // second barrier keeps thread 0 from overwriting the slot (next item or next
     // queue) before every wavefront has read it.
     for (;;) {
-      if (threadIdx.x == 0) S.item = atomicAdd(&ctr[q], 1);
+      if (threadIdx.x == 0) *slot = atomicAdd(&ctr[q], 1);
       __syncthreads();
-      const int i = __builtin_amdgcn_readfirstlane(S.item) + beg;
+      const int i = __builtin_amdgcn_readfirstlane(*slot) + beg;
       __syncthreads();
       if (i >= end) break;
-      run_item<F16>(A, items[i], S);
+      run(i);
     }
   }
+}
+
+template <bool F16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_ungapped_persistent(UngappedArgs A, const WorkItem* __restrict__ items,
+                           const UngappedCounters* __restrict__ cnt, const int32_t* __restrict__ list_len,
+                           int32_t* __restrict__ ctr, int32_t n_queues) {
+  __shared__ Smem S;
+  smem_init<F16, kThreads>(A, S);
+  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
+  work_loop(n_items, ctr, n_queues, &S.item, [&](int i) { run_item<F16>(A, items[i], S); });
+}
+
+__global__ __launch_bounds__(kMThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_ungapped_mfma(UngappedArgs A, const WorkItem* __restrict__ items, const UngappedCounters* __restrict__ cnt,
+                     const int32_t* __restrict__ list_len, int32_t* __restrict__ ctr, int32_t n_queues) {
+  __shared__ MSmem S;
+  m_tables(A, S);
+  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
+  work_loop(n_items, ctr, n_queues, &S.item, [&](int i) { run_item_m(A, items[i], S); });
 }
 
 // ---------------------------------------------------------------- planning
@@ -532,8 +562,11 @@ struct PlanShape {
   int32_t min_n2[kClasses];
   int32_t cols[kClasses];
   uint32_t mask;  // classes that get items
+  int32_t rows;   // rows of an item of the list that is run (kTileRows or kMRows)
 };
 
+// Items of kTileRows rows: the length that is reported and held against the
+// workspace's limit, whatever the rows of the items that are run (no fewer).
 __host__ __device__ __forceinline__ int64_t items_of(const PlanShape& P, int64_t n1, int64_t n2, int32_t* width) {
   if (n1 <= 0 || n2 <= 0) return 0;
   int c = 0;
@@ -552,7 +585,8 @@ __global__ void k_plan_count(const int64_t* __restrict__ a_off, const int64_t* _
   int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
   int32_t w = 0;
   const int64_t c = items_of(P, n1, n2, &w);
-  keycnt[k] = (int32_t)min(c, (int64_t)INT32_MAX);
+  const int64_t run = c > 0 ? ((n1 + P.rows - 1) / P.rows) * ((n2 + w - 1) / w) : 0;
+  keycnt[k] = (int32_t)min(run, (int64_t)INT32_MAX);
   if (c > 0) {
     atomicAdd(&cnt->n_ext, (unsigned long long)(n1 * n2));
     atomicAdd(&cnt->n_items64, (unsigned long long)c);
@@ -565,6 +599,7 @@ __global__ void k_plan_emit(const int64_t* __restrict__ a_off, const int64_t* __
                             WorkItem* __restrict__ items) {
   const int k = blockIdx.x;
   const unsigned long long n = cnt->n_items64;
+  if (k == 0 && threadIdx.x == 0) cnt->n_items = (int32_t)n;
   const int flag = (n > (unsigned long long)max_items || n > (unsigned long long)INT32_MAX)
                        ? 1
                        : (((err_a && *err_a) || (err_b && *err_b)) ? 2 : 0);
@@ -574,14 +609,14 @@ __global__ void k_plan_emit(const int64_t* __restrict__ a_off, const int64_t* __
   }
   int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
   int32_t width = 0;
-  const int ni = (int)items_of(P, n1, n2, &width);
-  if (ni == 0) return;
-  const int nrt = (int)((n1 + kTileRows - 1) / kTileRows);
+  if (items_of(P, n1, n2, &width) == 0) return;
+  const int nrt = (int)((n1 + P.rows - 1) / P.rows);
+  const int ni = nrt * (int)((n2 + width - 1) / width);
   for (int idx = threadIdx.x; idx < ni; idx += blockDim.x) {
     const int rt = idx % nrt, ct = idx / nrt;  // row tiles of one column range are adjacent
     WorkItem w;
     w.key = k;
-    w.row0 = rt * kTileRows;
+    w.row0 = rt * P.rows;
     w.col0 = ct * width;
     w.ncols = (int)min((int64_t)width, n2 - (int64_t)w.col0);
     items[item_off[k] + idx] = w;
@@ -599,6 +634,7 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
 struct UngappedWs {
   UngappedCounters* cnt;
   int32_t* ctr;
+  int32_t* list_len;
   int32_t* keycnt;
   void* scan_tmp;
   WorkItem* items;
@@ -610,6 +646,7 @@ UngappedWs carve(void* d_ws, size_t ws_bytes) {
   uint8_t* p = (uint8_t*)d_ws;
   W.cnt = (UngappedCounters*)p;
   W.ctr = (int32_t*)(p + kCtrOffset);
+  W.list_len = (int32_t*)(p + kListOffset);
   W.keycnt = (int32_t*)(p + 256);
   W.scan_tmp = p + 256 + align_up(sizeof(int32_t) * kNKeys, 256);
   W.items = (WorkItem*)(p + ungapped_ws_fixed_bytes());
@@ -617,18 +654,21 @@ UngappedWs carve(void* d_ws, size_t ws_bytes) {
   return W;
 }
 
-PlanShape shape_of(const plast_tuning_t& t, uint32_t mask) {
+PlanShape shape_of(const plast_tuning_t& t, uint32_t mask, int rows) {
   PlanShape P;
   for (int c = 0; c < kClasses; ++c) {
     P.min_n2[c] = t.class_min_n2[c];
     P.cols[c] = t.item_cols[c];
   }
   P.mask = mask;
+  P.rows = rows;
   return P;
 }
 
-// Returns true when the f16 variant is exact for this matrix.
-bool fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, const plast_ungapped_params_t* p,
+// Which tile routine is exact for a matrix: the matrix cores, packed binary16 or int16.
+enum class Tile { kMfma, kF16, kI16 };
+
+Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, const plast_ungapped_params_t* p,
                plast_hit_t* d_hits, int64_t capacity, unsigned long long* n_hits) {
   A.a = BankView{a->key_off, a->occ, a->occ_seq, a->scan_codes, a->seq_start};
   A.b = BankView{b->key_off, b->occ, b->occ_seq, b->scan_codes, b->seq_start};
@@ -647,6 +687,7 @@ bool fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
       A.mat[x * kNLet + y] = (x < 20 && y < 20) ? m[x * 20 + y] : kSepScore;
       maxabs = max(maxabs, abs((int)A.mat[x * kNLet + y]));
     }
+  A.thrf = (float)min(p->s1, 1 << 20);  // scores lie in [0, 44 * maxabs]
   const bool f16 = maxabs <= kF16MaxEntry;
   // Threshold register: hit iff thr - best < 0.  Scores lie in [0, 44 * maxabs].
   if (f16) {
@@ -659,21 +700,33 @@ bool fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
     const uint16_t h = (uint16_t)(int16_t)t;
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   }
-  return f16;
+  // The matrix-core tile counts on pairs of score 0 not being hits, and pays
+  // from about 12 rows a key on: against 100,000 proteins, a query of 450 (143,000
+  // codes) takes 1.25 ms on it and 1.39 on the VALU tiles, one of 200 (64,000) 0.91
+  // and 0.82.
+  return maxabs <= kMaxEntry && p->s1 >= 1 && a->n_padded >= (int64_t)kMMinRows * kNKeys ? Tile::kMfma : (f16 ? Tile::kF16 : Tile::kI16);
 }
 
-template <bool F16>
-int persistent_grid() {
-  static int cached = 0;
-  if (!cached) {
+// Workgroups of a persistent kernel resident on the device at once (0 on error).
+template <typename K>
+int resident_grid(K kernel, int threads, int* cached) {
+  if (!*cached) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_ungapped_persistent<F16>, kThreads, 0) != hipSuccess)
-      return 0;
-    cached = cus * (per > 0 ? per : 1);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess) return 0;
+    *cached = cus * (per > 0 ? per : 1);
   }
-  return cached;
+  return *cached;
+}
+
+int persistent_grid(Tile t) {
+  static int cached[3] = {0, 0, 0};
+  switch (t) {
+    case Tile::kMfma: return resident_grid(k_ungapped_mfma, kMThreads, &cached[0]);
+    case Tile::kF16: return resident_grid(k_ungapped_persistent<true>, kThreads, &cached[1]);
+    default: return resident_grid(k_ungapped_persistent<false>, kThreads, &cached[2]);
+  }
 }
 
 }  // namespace
@@ -706,7 +759,7 @@ int check_tuning(const plast_tuning_t* t) {
 }
 
 int ungapped_prepare() {
-  return (persistent_grid<true>() > 0 && persistent_grid<false>() > 0)
+  return (persistent_grid(Tile::kMfma) > 0 && persistent_grid(Tile::kF16) > 0 && persistent_grid(Tile::kI16) > 0)
              ? PLAST_OK
              : set_error(PLAST_E_HIP, "cannot query device occupancy");
 }
@@ -729,7 +782,7 @@ int read_key_offsets(const plast_index_t* x, int64_t* h, hipStream_t s) {
 
 int64_t plan_items_host(const int64_t* ha, const int64_t* hb, const plast_tuning_t& t, uint32_t class_mask,
                         int64_t* n_ext) {
-  const PlanShape P = shape_of(t, class_mask);
+  const PlanShape P = shape_of(t, class_mask, kTileRows);
   int64_t items = 0, ext = 0;
   for (int k = 0; k < kNKeys; ++k) {
     const int64_t n1 = ha[k + 1] - ha[k], n2 = hb[k + 1] - hb[k];
@@ -762,26 +815,30 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
     return set_error(PLAST_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, ungapped_ws_fixed_bytes());
   UngappedWs W = carve(d_ws, ws_bytes);
   UngappedArgs A;
-  const bool f16 = fill_args(A, a, b, p, d_hits, capacity, &W.cnt->n_hits);
-  const int grid = f16 ? persistent_grid<true>() : persistent_grid<false>();
+  const Tile tile = fill_args(A, a, b, p, d_hits, capacity, &W.cnt->n_hits);
+  const int grid = persistent_grid(tile);
   if (grid <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
-  const PlanShape P = shape_of(t, class_mask);
+  const PlanShape P = shape_of(t, class_mask, tile == Tile::kMfma ? kMRows : kTileRows);
   hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)d_ws, (int64_t)kHeaderDwords, 0u);
   timing_mark(kStagePlan, false, stream);
   hipLaunchKernelGGL(k_plan_count, dim3((kNKeys + 255) / 256), dim3(256), 0, stream, a->key_off, b->key_off, P,
                      W.keycnt, W.cnt);
-  exclusive_scan_i32(W.keycnt, kNKeys, &W.cnt->n_items, W.scan_tmp, stream);
+  exclusive_scan_i32(W.keycnt, kNKeys, W.list_len, W.scan_tmp, stream);
   hipLaunchKernelGGL(k_plan_emit, dim3(kNKeys), dim3(256), 0, stream, a->key_off, b->key_off, P,
                      (const int32_t*)W.keycnt, W.cnt, W.max_items, err_a, err_b, W.items);
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
-  if (f16)
-    hipLaunchKernelGGL(k_ungapped_persistent<true>, dim3(grid), dim3(kThreads), 0, stream, A,
-                       (const WorkItem*)W.items, (const UngappedCounters*)W.cnt, W.ctr, (int32_t)t.xcd_queues);
+  if (tile == Tile::kMfma)
+    hipLaunchKernelGGL(k_ungapped_mfma, dim3(grid), dim3(kMThreads), 0, stream, A, (const WorkItem*)W.items,
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues);
+  else if (tile == Tile::kF16)
+    hipLaunchKernelGGL(k_ungapped_persistent<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues);
   else
     hipLaunchKernelGGL(k_ungapped_persistent<false>, dim3(grid), dim3(kThreads), 0, stream, A,
-                       (const WorkItem*)W.items, (const UngappedCounters*)W.cnt, W.ctr, (int32_t)t.xcd_queues);
+                       (const WorkItem*)W.items, (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr,
+                       (int32_t)t.xcd_queues);
   if (ev1) PLAST_HIP(hipEventRecord(ev1, stream));
   timing_mark(kStageUngapped, true, stream);
   timing_launches(1);
@@ -802,7 +859,7 @@ int ungapped_extend_impl(const plast_index_t* a, const plast_index_t* b, const p
 
   if (mode == PLAST_PLAIN) {
     UngappedArgs A;
-    const bool f16 = fill_args(A, a, b, p, d_hits, capacity, &((UngappedCounters*)d_ws)->n_hits);
+    const bool f16 = fill_args(A, a, b, p, d_hits, capacity, &((UngappedCounters*)d_ws)->n_hits) != Tile::kI16;
     std::vector<int64_t> ha(kNKeys + 1), hb(kNKeys + 1);
     int rc;
     if ((rc = read_key_offsets(a, ha.data(), stream)) || (rc = read_key_offsets(b, hb.data(), stream))) return rc;
