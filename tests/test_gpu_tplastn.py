@@ -135,3 +135,35 @@ def test_plastx_search_matches_oracle_and_finds_plants(B):
                 found += 1
                 break
     assert found >= 0.85 * len(w.plants), (found, len(w.plants))
+
+
+def _dense_stops(n_nt, phase):
+    """ATG TAA ATG TAA ...: as many fragments as a frame can hold, one codon each."""
+    return np.resize(np.array([0, 3, 2, 3, 0, 0], dtype=np.uint8), n_nt + phase)[phase:]
+
+
+@pytest.mark.parametrize("codons", [1024, 4096])
+@pytest.mark.parametrize("extra", [-4, -1, 0, 1, 2, 3, 50])
+def test_translation_at_the_edges_of_the_chunks(B, codons, extra):
+    """Streams that end around one and two chunks of either workgroup size, with no stop, with stops as dense as they
+    can be, and random; sequences at every alignment."""
+    rng = np.random.default_rng(codons + extra)
+    long = codons == 4096
+    seqs = []
+    for n in (3 * codons + extra, 6 * codons + extra):
+        seqs += [np.zeros(n, np.uint8), _dense_stops(n, 0), _dense_stops(n, 2), rng.integers(0, 4, n + 1).astype(np.uint8)]
+    if not long:  # a mean length that takes the small workgroups
+        seqs += [rng.integers(0, 4, 5).astype(np.uint8)] * 12
+    else:  # one that takes the large ones
+        seqs += [rng.integers(0, 4, 200_000).astype(np.uint8)]
+    dna = synth.DnaBank.from_seqs(seqs)
+    assert (dna.codes.shape[0] > 16384 * dna.n_seqs) == long
+    _check_translation(B, dna)
+
+
+@pytest.mark.parametrize("n_seqs", [682, 683, 2500])
+def test_translation_of_many_sequences(B, n_seqs):
+    """Around the number of streams (4096) from which several workgroups scan them."""
+    rng = np.random.default_rng(n_seqs)
+    dna = synth.DnaBank.from_seqs([rng.integers(0, 4, int(n)).astype(np.uint8) for n in rng.integers(0, 60, n_seqs)])
+    _check_translation(B, dna)
