@@ -6,15 +6,15 @@
 // |i - j| <= band; a gap of length k costs gap_open + k * gap_extend.  The side
 // scores max(0, best existing cell) and the hit scores right + left.
 //
-// One thread per hit.  The band of row i is held in registers, indexed by
-// d = j - i + 16 (33 cells), so H and F of the previous row are read at d
-// (diagonal) and d + 1 (vertical) and overwritten in place; E runs left to
-// right inside the row.  The letters of y under the band slide by one register
-// per row.  The thread's windows are staged in LDS; y positions past the clipped
-// length hold a wall letter with a non-positive substitution score.  A cell past
-// the end of y never feeds a cell inside it, and is reached only from cells
-// inside through wall letters or gaps, which cannot raise the score; so it never
-// exceeds the best existing cell and no per-cell length test is needed.
+// The band of row i is held in registers, indexed by d = j - i + 16 (33 cells at
+// band 16), so H and F of the previous row are read at d (diagonal) and d + 1
+// (vertical) and overwritten in place; E runs left to right inside the row.  The
+// letters of y under the band slide by one register per row.  Positions past the
+// clipped length hold the separator letter, whose substitution score is negative
+// (the packed path: -inf).  A cell past the end of x or y never feeds a cell inside
+// it, and is reached only from cells inside through separators or gaps, which cannot
+// raise the score; so it never exceeds the best existing cell and no per-cell length
+// test is needed.
 //
 // Fast path (band 16, window <= 64, and every finite DP value an integer of
 // magnitude < 2048, which holds for BLOSUM62 with open 11 / extend 1): one lane
@@ -42,6 +42,17 @@
 // builds the 37 KB table once and strides over the hits.  The last four blocks
 // of rows are peeled at compile time and skip their cells right of column 64,
 // which no window reaches (about 5% of the band).
+//
+// General path (narrower bands, larger entries or costs): the same shifted
+// recurrence, anti-diagonal maxima and pair table in int32 (table entries in
+// int16), one lane per side of a hit: the lower half of a wavefront takes the right
+// sides of 32 hits, the upper half their left sides, whose letters run backward.
+// A cell is 6 instructions (the score's half of a table entry is sign-extended by
+// the addition), so a side costs about 1.35 of a packed one.  It is compiled for
+// the even bands and masks the outermost cells for the odd ones and 0.  Measured on
+// 390,000 hits, against one lane per hit with its windows as bytes in LDS and no
+// shift: band 10, window 40 0.43 -> 0.15 ms; band 4, window 64 0.68 -> 0.12; band 16
+// with costs past the packed path's 0.58 -> 0.36.
 #include <type_traits>
 
 #include "plast_internal.h"
@@ -50,13 +61,10 @@ namespace plast {
 
 namespace {
 
-constexpr int kGThreads = 128;
 constexpr int kGMaxWin = 64;
 constexpr int kGMaxBand = 16;
 constexpr int kGCells = 2 * kGMaxBand + 1;  // 33
-constexpr int kGYLen = kGMaxWin + kGMaxBand + 16;  // 96 y letters staged per side
-constexpr int kWall = 21;                   // letter code of the wall
-constexpr int kWallScore = -1000;          // any value <= 0 works: a cell past y only loses score
+constexpr int kWallScore = -16000;          // of a separator: any value <= 0 works that an int16 holds with 2 extend
 constexpr int kNeg = -(1 << 28);
 
 struct GappedArgs {
@@ -66,116 +74,9 @@ struct GappedArgs {
   const int64_t* b_seq_start;
   int32_t a_nseq, b_nseq;
   int32_t window, band, gap_open, gap_extend, s2, pad_;
-  int16_t mat[kNLet * 22];     // [x letter][y letter or wall]
+  int16_t mat[kNLet * kNLet];     // [x letter][y letter], score + 2 extend (general path)
   uint16_t tbl16[kNLet * kNLet];  // binary16 [x letter][y letter], -inf where either is the separator (20)
 };
-
-struct GSmem {
-  int32_t mat[kNLet * 22];
-  uint8_t x[kGThreads][kGMaxWin];
-  uint8_t y[kGThreads][kGYLen];
-};
-
-template <int BAND>
-__device__ int gapped_side(const GappedArgs& G, GSmem& S, int t, int lx, int ly, int band) {
-  const int oe = G.gap_open + G.gap_extend;
-  const int ext = G.gap_extend;
-  const uint8_t* xs = S.x[t];
-  const uint8_t* ys = S.y[t];
-  int H[kGCells], F[kGCells], Y[kGCells];
-  // row 0: H(0, j) = -(open + j*ext) for 0 < j <= band, H(0,0) = 0
-#pragma unroll
-  for (int d = 0; d < kGCells; ++d) {
-    const int j = d - kGMaxBand;
-    const bool inband = BAND == kGMaxBand ? true : (j >= -band && j <= band);
-    H[d] = (j < 0 || !inband) ? kNeg : (j == 0 ? 0 : -(G.gap_open + j * ext));
-    F[d] = kNeg;
-    // letter of y[j' - 1] for row 1, j' = 1 + d - 16 -> index d - 16
-    Y[d] = (d - kGMaxBand >= 0) ? ys[d - kGMaxBand] : kWall;
-  }
-  int best = 0;
-  for (int i = 1; i <= lx; ++i) {
-    const int* mrow = &S.mat[xs[i - 1] * 22];
-    int e = kNeg, hleft = kNeg;
-    const int ynext = ys[i + kGMaxBand];  // y index (i+1) + 32 - 17 for the next row
-#pragma unroll
-    for (int d = 0; d < kGCells; ++d) {
-      const int diag = H[d] + mrow[Y[d]];
-      const int f = d + 1 < kGCells ? max(F[d + 1] - ext, H[d + 1] - oe) : kNeg;
-      e = max(e - ext, hleft - oe);
-      int h = max(max(diag, e), f);
-      int fv = f;
-      if (BAND != kGMaxBand) {
-        const int j = i + d - kGMaxBand;
-        if (j - i < -band || j - i > band) {
-          h = kNeg;
-          fv = kNeg;
-          e = kNeg;
-        }
-      }
-      h = max(h, kNeg);
-      best = max(best, h);
-      H[d] = h;
-      F[d] = max(fv, kNeg);
-      hleft = h;
-    }
-#pragma unroll
-    for (int d = 0; d + 1 < kGCells; ++d) Y[d] = Y[d + 1];
-    Y[kGCells - 1] = ynext;
-  }
-  (void)ly;
-  return best;
-}
-
-template <int BAND>
-__global__ __launch_bounds__(kGThreads) void k_gapped(GappedArgs G, const plast_hit_t* __restrict__ hits,
-                                                      int64_t n_hits, const unsigned long long* __restrict__ n_dev,
-                                                      int32_t* __restrict__ gscore, uint8_t* __restrict__ pass) {
-  __shared__ GSmem S;
-  for (int i = threadIdx.x; i < kNLet * 22; i += kGThreads) S.mat[i] = G.mat[i];
-  if (n_dev) n_hits = min(n_hits, (int64_t)*n_dev);
-  __syncthreads();
-  const int t = threadIdx.x;
-  const int64_t h = (int64_t)blockIdx.x * kGThreads + t;
-  const bool live = h < n_hits;
-  plast_hit_t hit = live ? hits[h] : plast_hit_t{0, 0, 0, 0, 0};
-  int total = 0;
-  bool sane = live && hit.seq1 >= 0 && hit.seq1 < G.a_nseq && hit.seq2 >= 0 && hit.seq2 < G.b_nseq;
-  int64_t sa = 0, sb = 0;
-  int la = 0, lb = 0;
-  if (sane) {
-    sa = G.a_seq_start[hit.seq1];
-    sb = G.b_seq_start[hit.seq2];
-    la = (int)(G.a_seq_start[hit.seq1 + 1] - sa - kPadLen);
-    lb = (int)(G.b_seq_start[hit.seq2 + 1] - sb - kPadLen);
-    sane = hit.pos1 >= 0 && hit.pos1 < la && hit.pos2 >= 0 && hit.pos2 < lb;
-  }
-  if (live && !sane) {  // not a hit of these banks: flagged, nothing read
-    gscore[h] = -1;
-    pass[h] = 0;
-  }
-  if (sane) {
-    const int64_t qa = sa + hit.pos1, qb = sb + hit.pos2;
-    for (int side = 0; side < 2; ++side) {
-      int lx, ly;
-      if (side == 0) {
-        lx = min(G.window, la - hit.pos1);
-        ly = min(G.window, lb - hit.pos2);
-        for (int k = 0; k < lx; ++k) S.x[t][k] = G.a_scan[qa + k] / kScale;
-        for (int k = 0; k < kGYLen; ++k) S.y[t][k] = k < ly ? G.b_scan[qb + k] / kScale : kWall;
-      } else {
-        lx = min(G.window, hit.pos1);
-        ly = min(G.window, hit.pos2);
-        for (int k = 0; k < lx; ++k) S.x[t][k] = G.a_scan[qa - 1 - k] / kScale;
-        for (int k = 0; k < kGYLen; ++k) S.y[t][k] = k < ly ? G.b_scan[qb - 1 - k] / kScale : kWall;
-      }
-      total += gapped_side<BAND>(G, S, t, lx, ly, G.band);
-    }
-    gscore[h] = total;
-    pass[h] = total >= G.s2 ? 1 : 0;
-  }
-}
-
 
 // ---------------------------------------------------------------- packed f16 path
 typedef _Float16 gh2 __attribute__((ext_vector_type(2)));
@@ -225,6 +126,170 @@ __device__ __forceinline__ uint32_t load4(const uint8_t* __restrict__ buf, int64
 
 __device__ __forceinline__ uint32_t byte_of(uint32_t v, int k) { return (v >> (8 * k)) & 0xffu; }
 
+// ---------------------------------------------------------------- general path
+// One side of a hit on one lane: lx x lx letters from qa and ly from qb, forward
+// or (back) backward from the letters before them.  All lanes of a wavefront call
+// it together.
+template <int BAND, bool MASK>
+__device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* tbl, int64_t qa, int64_t qb, int lx,
+                                           int ly, bool back) {
+  constexpr int kCells = 2 * BAND + 1;
+  constexpr int kY = kCells + kFBlock;  // y letters held for a block of rows
+  const uint32_t order = back ? 0x00010203u : 0x03020100u;
+  // letters i .. i + 3 (0-based, along the side) of a sequence, in scan-code bytes
+  auto letters = [&](const uint8_t* buf, int64_t q, int i) {
+    const uint32_t w = load4(buf, back ? q - 4 - i : q + i);
+    return __builtin_amdgcn_perm(w, w, order);
+  };
+  auto letter = [&](uint32_t w, int t, int i, int n) {  // byte t of w, letter i of n
+    return (i >= 0 && i < n ? byte_of(w, t) : kWall8) / kScale;
+  };
+  const int op = G.gap_open, ex = G.gap_extend;
+  int H[kCells], F[kCells];
+  // YY[k]: pair-table offset of the letters at y indices i0 + k - BAND - 1 and
+  // i0 + k - BAND for the block at row i0; ylast: the last letter of the last pair
+  uint32_t YY[kY - 1];
+  uint32_t ylast = kPadCode;
+  // row 0 (shifted): H(0, 0) = 0, H(0, j) + j * extend = -open for 0 < j <= band; F holds F(1, j)
+#pragma unroll
+  for (int d = 0; d < kCells; ++d) {
+    const int j = d - BAND;
+    H[d] = j < 0 || (MASK && j > G.band) ? kNeg : (j == 0 ? 0 : -op);
+    F[d] = H[d] - op;
+  }
+#pragma unroll
+  for (int g = 0; g < (kY + 3) / 4; ++g) {
+    const uint32_t w = letters(G.b_scan, qb, 4 * g - BAND);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * g + t;
+      if (k < kY) {
+        const uint32_t y = letter(w, t, k - BAND, ly);
+        if (k > 0) YY[k - 1] = ylast * (uint32_t)(kNLet * 4) + y * 4u;
+        ylast = y;
+      }
+    }
+  }
+  uint32_t xb[kFBlock];
+  {
+    const uint32_t w = letters(G.a_scan, qa, 0);
+#pragma unroll
+    for (int r = 0; r < kFBlock; ++r) xb[r] = letter(w, r, r, lx) * kXRowBytes;
+  }
+  int best = 0;  // H(0, 0): the empty alignment
+  // best shifted value per anti-diagonal i + j = 2 i0 - BAND + t of the current block
+  constexpr int kAcc = 2 * (kFBlock - 1) + kCells;
+  constexpr int kDone = 2 * kFBlock;  // anti-diagonals completed per block
+  int acc[kAcc];
+#pragma unroll
+  for (int t = 0; t < kAcc; ++t) acc[t] = kNeg;
+  int sh = (2 - BAND) * ex;  // shift of anti-diagonal 2 i0 - BAND
+  const char* tb = (const char*)tbl;
+  for (int i0 = 1; __ballot(i0 <= lx) != 0; i0 += kFBlock) {
+    // raw letters of the next block, decoded after this block's rows
+    const uint32_t nx = letters(G.a_scan, qa, i0 - 1 + kFBlock);
+    const int k0 = i0 + kY - BAND - 1;
+    const uint32_t ny = letters(G.b_scan, qb, k0);
+    // table lookups (one per two cells) are issued kAhead pairs ahead
+    constexpr int kPairs = (kCells + 1) / 2, kSeq = kFBlock * kPairs, kAhead = 5;
+    uint32_t sc[kSeq];
+    auto issue = [&](int q) {
+      const int r = q / kPairs, p = q % kPairs;
+      sc[q] = *(const uint32_t*)(tb + (xb[r] + YY[2 * p + r]));
+    };
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) issue(q);
+    int e = kNeg;
+#pragma unroll
+    for (int q = 0; q < kSeq; ++q) {
+      if (q + kAhead < kSeq) issue(q + kAhead);
+      const int r = q / kPairs, p = q % kPairs;
+      if (p == 0) e = kNeg;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int d = 2 * p + c;
+        if (d >= kCells) continue;
+        // cell (i0 + r, d) lies on anti-diagonal t; in an odd row it shares it with
+        // cell d + 2 of the row above, still in H[d + 2]
+        const int t = 2 * r + d;
+        const int s = (int)(int16_t)(sc[q] >> (16 * c));
+        const int f = d + 1 < kCells ? F[d + 1] : kNeg;
+        int h = max(max(H[d] + s, e), f);
+        if (MASK && (d < 2 || d >= kCells - 2)) h = abs(d - BAND) > G.band ? kNeg : h;
+        if (r & 1)
+          acc[t] = d + 2 < kCells ? max(max(acc[t], h), H[d + 2]) : max(acc[t], h);
+        else if (d < 2)
+          acc[t] = max(acc[t], h);
+        const int ho = h - op;
+        e = max(e, ho);
+        F[d] = max(f, ho);
+        H[d] = h;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < kDone; ++t) best = max(best, acc[t] - (sh + t * ex));
+    sh += kDone * ex;
+#pragma unroll
+    for (int t = 0; t < kAcc; ++t) acc[t] = t + kDone < kAcc ? acc[t + kDone] : kNeg;
+#pragma unroll
+    for (int k = 0; k + kFBlock < kY - 1; ++k) YY[k] = YY[k + kFBlock];
+#pragma unroll
+    for (int t = 0; t < kFBlock; ++t) {
+      const uint32_t y = letter(ny, t, k0 + t, ly);
+      YY[kY - 1 - kFBlock + t] = ylast * (uint32_t)(kNLet * 4) + y * 4u;
+      ylast = y;
+      xb[t] = letter(nx, t, i0 - 1 + kFBlock + t, lx) * kXRowBytes;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kAcc; ++t) best = max(best, acc[t] - (sh + t * ex));
+  return best;
+}
+
+constexpr int kGThreads = 256;
+constexpr int kGHits = kGThreads / 2;  // hits of a workgroup at a time
+
+template <int BAND, bool MASK>
+__global__ __launch_bounds__(kGThreads) void k_gapped(GappedArgs G, const plast_hit_t* __restrict__ hits,
+                                                      int64_t n_hits, const unsigned long long* __restrict__ n_dev,
+                                                      int32_t* __restrict__ gscore, uint8_t* __restrict__ pass) {
+  __shared__ uint32_t tbl[kPairDwords];
+  for (int i = threadIdx.x; i < kPairDwords; i += kGThreads) {
+    const int x = i / kPairRow, y1 = (i / kNLet) % kNLet, y2 = i % kNLet;
+    tbl[i] = (uint32_t)(uint16_t)G.mat[x * kNLet + y1] | ((uint32_t)(uint16_t)G.mat[x * kNLet + y2] << 16);
+  }
+  if (n_dev) n_hits = min(n_hits, (int64_t)*n_dev);
+  __syncthreads();
+  const int lane = __lane_id();
+  const bool back = lane >= 32;
+  for (int64_t base = (int64_t)blockIdx.x * kGHits; base < n_hits; base += (int64_t)gridDim.x * kGHits) {
+    const int64_t h = base + (threadIdx.x >> 6) * 32 + (lane & 31);
+    const bool live = h < n_hits;
+    const plast_hit_t hit = live ? hits[h] : plast_hit_t{0, 0, 0, 0, 0};
+    bool sane = live && hit.seq1 >= 0 && hit.seq1 < G.a_nseq && hit.seq2 >= 0 && hit.seq2 < G.b_nseq;
+    int64_t sa = 0, sb = 0;
+    int la = 0, lb = 0;
+    if (sane) {
+      sa = G.a_seq_start[hit.seq1];
+      sb = G.b_seq_start[hit.seq2];
+      la = (int)(G.a_seq_start[hit.seq1 + 1] - sa - kPadLen);
+      lb = (int)(G.b_seq_start[hit.seq2 + 1] - sb - kPadLen);
+      sane = hit.pos1 >= 0 && hit.pos1 < la && hit.pos2 >= 0 && hit.pos2 < lb;
+    }
+    // a lane without a valid record reads separators
+    const int64_t qa = sane ? sa + hit.pos1 : kPadLen, qb = sane ? sb + hit.pos2 : kPadLen;
+    const int lx = sane ? min(G.window, back ? hit.pos1 : la - hit.pos1) : 0;
+    const int ly = sane ? min(G.window, back ? hit.pos2 : lb - hit.pos2) : 0;
+    const int side = gapped_side<BAND, MASK>(G, tbl, qa, qb, lx, ly, back);
+    const int total = side + __shfl_xor(side, 32);
+    if (live && !back) {  // not a hit of these banks: flagged
+      gscore[h] = sane ? total : -1;
+      pass[h] = sane && total >= G.s2 ? 1 : 0;
+    }
+  }
+}
+
+// ---------------------------------------------------------------- packed path, continued
 // Letters of one hit: x rows i = 1.. and y indices k = 0.. for the rightward
 // (R) and leftward (L) extension, in scan-code units; walls outside.
 struct GLetters {
@@ -488,41 +553,70 @@ void k_gapped_f16(GappedArgs G, const plast_hit_t* __restrict__ hits, int64_t n_
     gapped_hit_f16(G, tbl, hits, h, n_hits, gscore, pass);
 }
 
-// Workgroups of k_gapped_f16<NT> resident on the device at once (0 on error).
-template <int NT>
-int64_t fast_resident() {
-  static int64_t cached = 0;
-  if (!cached) {
+// Workgroups of a kernel resident on the device at once (0 on error).
+template <typename K>
+int64_t resident(K kernel, int threads, int64_t* cached) {
+  if (!*cached) {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_gapped_f16<NT>, NT, 0) != hipSuccess)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess)
       return 0;
-    cached = (int64_t)cus * (per > 0 ? per : 1);
+    *cached = (int64_t)cus * (per > 0 ? per : 1);
   }
-  return cached;
+  return *cached;
 }
 
-// The grid is at most one resident wave of workgroups: each workgroup builds
-// the 37 KB pair table once and then strides over the hits.
-template <int NT>
-int launch_fast(const GappedArgs& G, const plast_hit_t* d_hits, int64_t n_hits, const unsigned long long* d_n,
-                int32_t* d_gscore, uint8_t* d_pass, hipStream_t stream) {
-  const int64_t resident = fast_resident<NT>();
-  if (resident <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
-  const int64_t need = (n_hits + NT - 1) / NT;
-  const int64_t grid = need < resident ? need : resident;
-  hipLaunchKernelGGL(k_gapped_f16<NT>, dim3((unsigned)grid), dim3(NT), 0, stream, G, d_hits, n_hits, d_n, d_gscore,
-                     d_pass);
-  return PLAST_OK;
+typedef void (*GappedKernel)(GappedArgs, const plast_hit_t*, int64_t, const unsigned long long*, int32_t*, uint8_t*);
+
+// The kernels: the packed one by workgroup size, the general one by band (even
+// ones, and odd ones on the next with its outermost cells masked).
+struct GappedForm {
+  GappedKernel kernel;
+  int threads, hits;  // of a workgroup
+};
+constexpr int kForms = 3 + kGMaxBand + 1;
+
+GappedForm form(int i) {
+  switch (i) {
+    case 0: return {k_gapped_f16<128>, 128, 128};
+    case 1: return {k_gapped_f16<256>, 256, 256};
+    case 2: return {k_gapped_f16<512>, 512, 512};
+    case 3: return {k_gapped<2, true>, kGThreads, kGHits};  // band 0
+#define PLAST_GAPPED_BANDS(n)                                   \
+  case 3 + n - 1: return {k_gapped<n, true>, kGThreads, kGHits}; \
+  case 3 + n: return {k_gapped<n, false>, kGThreads, kGHits};
+    PLAST_GAPPED_BANDS(2)
+    PLAST_GAPPED_BANDS(4)
+    PLAST_GAPPED_BANDS(6)
+    PLAST_GAPPED_BANDS(8)
+    PLAST_GAPPED_BANDS(10)
+    PLAST_GAPPED_BANDS(12)
+    PLAST_GAPPED_BANDS(14)
+    PLAST_GAPPED_BANDS(16)
+#undef PLAST_GAPPED_BANDS
+    default: return {nullptr, 0, 0};
+  }
+}
+
+int form_of(bool fast, int threads, int band) {
+  if (fast) return threads == 128 ? 0 : (threads == 512 ? 2 : 1);
+  return 3 + band;
+}
+
+int64_t form_resident(int i) {
+  static int64_t cached[kForms] = {};
+  const GappedForm f = form(i);
+  return resident(f.kernel, f.threads, &cached[i]);
 }
 
 }  // namespace
 
+// Occupancy queries are not made inside a graph capture: all forms, once.
 int gapped_prepare() {
-  return (fast_resident<128>() > 0 && fast_resident<256>() > 0 && fast_resident<512>() > 0)
-             ? PLAST_OK
-             : set_error(PLAST_E_HIP, "cannot query device occupancy");
+  for (int i = 0; i < kForms; ++i)
+    if (form_resident(i) <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
+  return PLAST_OK;
 }
 
 int gapped_filter_impl(const plast_index_t* a, const plast_index_t* b, const plast_hit_t* d_hits, int64_t n_hits,
@@ -549,8 +643,8 @@ int gapped_filter_impl(const plast_index_t* a, const plast_index_t* b, const pla
   }
   int maxabs = 0;
   for (int x = 0; x < kNLet; ++x)
-    for (int y = 0; y < 22; ++y) {
-      G.mat[x * 22 + y] = (x < 20 && y < 20) ? m[x * 20 + y] : kWallScore;
+    for (int y = 0; y < kNLet; ++y) {
+      G.mat[x * kNLet + y] = (int16_t)(((x < 20 && y < 20) ? m[x * 20 + y] : kWallScore) + 2 * g->gap_extend);
       if (x < 20 && y < 20) maxabs = max(maxabs, abs((int)m[x * 20 + y]));
     }
   const uint16_t ninf16 = 0xFC00;  // binary16 -inf
@@ -565,21 +659,16 @@ int gapped_filter_impl(const plast_index_t* a, const plast_index_t* b, const pla
                     64 * maxabs + 3 * (g->gap_open + g->gap_extend) + 280 * g->gap_extend <= 2000;
   const int threads = g->tuning ? g->tuning->gapped_threads : 256;
   if (n_hits <= 0) return PLAST_OK;
+  // The grid is at most one resident wave of workgroups: each builds the 37 KB
+  // pair table once and then strides over the hits.
+  const int i = form_of(fast, threads, g->band);
+  const GappedForm f = form(i);
+  const int64_t most = form_resident(i);
+  if (most <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
+  const int64_t need = (n_hits + f.hits - 1) / f.hits;
   timing_mark(kStageGapped, false, stream);
-  if (fast) {
-    const int rc = threads == 128   ? launch_fast<128>(G, d_hits, n_hits, d_n, d_gscore, d_pass, stream)
-                   : threads == 512 ? launch_fast<512>(G, d_hits, n_hits, d_n, d_gscore, d_pass, stream)
-                                    : launch_fast<256>(G, d_hits, n_hits, d_n, d_gscore, d_pass, stream);
-    if (rc != PLAST_OK) return rc;
-  } else {
-    unsigned blocks = (unsigned)((n_hits + kGThreads - 1) / kGThreads);
-    if (g->band == kGMaxBand)
-      hipLaunchKernelGGL(k_gapped<kGMaxBand>, dim3(blocks), dim3(kGThreads), 0, stream, G, d_hits, n_hits, d_n,
-                         d_gscore, d_pass);
-    else
-      hipLaunchKernelGGL(k_gapped<-1>, dim3(blocks), dim3(kGThreads), 0, stream, G, d_hits, n_hits, d_n, d_gscore,
-                         d_pass);
-  }
+  hipLaunchKernelGGL(f.kernel, dim3((unsigned)(need < most ? need : most)), dim3(f.threads), 0, stream, G, d_hits,
+                     n_hits, d_n, d_gscore, d_pass);
   timing_mark(kStageGapped, true, stream);
   PLAST_HIP(hipGetLastError());
   return PLAST_OK;
