@@ -50,10 +50,8 @@ __device__ __forceinline__ void wave_sync() {
 // position t * kIxTile (sequence 0 for the leading separators).  A sequence
 // writes its tiles only when its own starts are consistent; the table is read
 // only when no thread flagged the layout, and then every tile is written.
-__global__ void k_layout_check(const int64_t* __restrict__ seq_start, int32_t n_seqs, int64_t n_padded,
-                               int32_t* __restrict__ tile_seq, int64_t tiles, int32_t* __restrict__ err) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > n_seqs) return;
+__device__ __forceinline__ bool layout_bad(const int64_t* __restrict__ seq_start, int64_t i, int32_t n_seqs,
+                                           int64_t n_padded, int32_t* __restrict__ tile_seq, int64_t tiles) {
   int64_t s = seq_start[i];
   bool bad = s < kPadLen || s > n_padded;
   if (i == 0 && s != kPadLen) bad = true;
@@ -66,7 +64,34 @@ __global__ void k_layout_check(const int64_t* __restrict__ seq_start, int32_t n_
       for (int64_t t = (lo + kIxTile - 1) / kIxTile; t < tiles && t * kIxTile < nx; ++t) tile_seq[t] = (int32_t)i;
     }
   }
-  if (bad) atomicOr(err, 1);
+  return bad;
+}
+
+// err is cleared before.
+__global__ void k_layout_check(const int64_t* __restrict__ seq_start, int32_t n_seqs, int64_t n_padded,
+                               int32_t* __restrict__ tile_seq, int64_t tiles, int32_t* __restrict__ err) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i > n_seqs) return;
+  if (layout_bad(seq_start, i, n_seqs, n_padded, tile_seq, tiles)) atomicOr(err, 1);
+}
+
+// Up to kLayoutOne sequences, by one workgroup that also clears err: one launch
+// instead of two for a query bank.
+constexpr int kLayoutThreads = 1024;
+constexpr int kLayoutOne = 4 * kLayoutThreads;
+
+__global__ __launch_bounds__(kLayoutThreads) void k_layout_check_one(const int64_t* __restrict__ seq_start,
+                                                                     int32_t n_seqs, int64_t n_padded,
+                                                                     int32_t* __restrict__ tile_seq, int64_t tiles,
+                                                                     int32_t* __restrict__ err) {
+  bool bad = false;
+  for (int64_t i = threadIdx.x; i <= n_seqs; i += kLayoutThreads)
+    bad |= layout_bad(seq_start, i, n_seqs, n_padded, tile_seq, tiles);
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) {
+    err[0] = any ? 1 : 0;
+    err[1] = 0;
+  }
 }
 
 // Loads starts s0 + 1 .. s0 + 64 * K of the sequences (INT64_MAX past the
@@ -580,12 +605,24 @@ __global__ __launch_bounds__(256) void k_ix_key_off(const uint64_t* __restrict__
 }
 
 // ---------------------------------------------------------------- scan
+// Exclusive scans in place, in as few launches as the length allows (a launch costs
+// about 5 us where little else runs): one workgroup up to kScanOne elements; up to
+// kScanTops blocks, a local scan of each block and then one pass in which every
+// block sums the totals before its own (8 KB of L2 reads a block on average at
+// most); beyond, where those reads would exceed the data, a scan of the totals in
+// between.
 constexpr int kScanThreads = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanBlock = kScanThreads * kScanPer;
+constexpr int kScanTops = 4096;
+constexpr int kScanOneThreads = 1024;
+constexpr int kScanOnePer = 16;
+constexpr int kScanOne = kScanOneThreads * kScanOnePer;
 
+// Workgroup-wide exclusive scan of one value per thread (contains barriers).
+template <int NT>
 __device__ __forceinline__ int block_excl_scan(int v, int* total) {
-  __shared__ int wsum[kScanThreads / 64];
+  __shared__ int wsum[NT / 64];
   int lane = lane_id(), wid = threadIdx.x / 64;
   int incl = v;
 #pragma unroll
@@ -597,7 +634,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total) {
   __syncthreads();
   int before = 0, all = 0;
 #pragma unroll
-  for (int w = 0; w < kScanThreads / 64; ++w) {
+  for (int w = 0; w < NT / 64; ++w) {
     before += (w < wid) ? wsum[w] : 0;
     all += wsum[w];
   }
@@ -606,23 +643,66 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total) {
   return before + incl - v;
 }
 
+// PER consecutive elements from `base` (0 past n), 16 bytes at a time where they
+// all exist; data is 16-byte aligned and base a multiple of 4.
+template <int PER>
+__device__ __forceinline__ void load_run(const int32_t* __restrict__ data, int64_t base, int64_t n, int (&v)[PER]) {
+  if (base + PER <= n) {
+#pragma unroll
+    for (int i = 0; i < PER; i += 4) {
+      const int4 x = *(const int4*)(data + base + i);
+      v[i] = x.x;
+      v[i + 1] = x.y;
+      v[i + 2] = x.z;
+      v[i + 3] = x.w;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = base + i < n ? data[base + i] : 0;
+  }
+}
+
+template <int PER>
+__device__ __forceinline__ void store_run(int32_t* __restrict__ data, int64_t base, int64_t n, const int (&v)[PER]) {
+  if (base + PER <= n) {
+#pragma unroll
+    for (int i = 0; i < PER; i += 4) *(int4*)(data + base + i) = make_int4(v[i], v[i + 1], v[i + 2], v[i + 3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (base + i < n) data[base + i] = v[i];
+  }
+}
+
+// One block: the exclusive scan of its elements in place; returns their sum.
+template <int NT, int PER>
+__device__ __forceinline__ int scan_block(int32_t* __restrict__ data, int64_t base, int64_t n) {
+  int v[PER], sum = 0;
+  load_run<PER>(data, base, n, v);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) sum += v[i];
+  int total;
+  int run = block_excl_scan<NT>(sum, &total);
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int x = v[i];
+    v[i] = run;
+    run += x;
+  }
+  store_run<PER>(data, base, n, v);
+  return total;
+}
+
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(int32_t* __restrict__ data, int64_t n,
+                                                              int32_t* __restrict__ grand) {
+  const int total = scan_block<kScanOneThreads, kScanOnePer>(data, (int64_t)threadIdx.x * kScanOnePer, n);
+  if (threadIdx.x == 0 && grand) *grand = total;
+}
+
 __global__ __launch_bounds__(kScanThreads) void k_scan_local(int32_t* __restrict__ data, int64_t n,
                                                              int32_t* __restrict__ tops) {
-  int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
-  int v[kScanPer];
-  int sum = 0;
-#pragma unroll
-  for (int i = 0; i < kScanPer; ++i) {
-    v[i] = (base + i < n) ? data[base + i] : 0;
-    sum += v[i];
-  }
-  int total;
-  int run = block_excl_scan(sum, &total);
-#pragma unroll
-  for (int i = 0; i < kScanPer; ++i) {
-    if (base + i < n) data[base + i] = run;
-    run += v[i];
-  }
+  const int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
+  const int total = scan_block<kScanThreads, kScanPer>(data, base, n);
   if (threadIdx.x == 0) tops[blockIdx.x] = total;
 }
 
@@ -639,7 +719,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tops(int32_t* __restrict_
       sum += v[i];
     }
     int total;
-    int run = carry + block_excl_scan(sum, &total);
+    int run = carry + block_excl_scan<kScanThreads>(sum, &total);
 #pragma unroll
     for (int i = 0; i < kScanPer; ++i) {
       if (base + i < nb) tops[base + i] = run;
@@ -650,13 +730,33 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tops(int32_t* __restrict_
   if (threadIdx.x == 0 && grand) *grand = carry;
 }
 
+// SCANNED: tops hold the exclusive scan of the blocks' totals; otherwise the
+// totals themselves, which the block sums up to its own.
+template <bool SCANNED>
 __global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* __restrict__ data, int64_t n,
-                                                           const int32_t* __restrict__ tops) {
-  int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
-  int add = tops[blockIdx.x];
+                                                           const int32_t* __restrict__ tops,
+                                                           int32_t* __restrict__ grand) {
+  int add = 0;
+  if (SCANNED) {
+    add = tops[blockIdx.x];
+  } else {
+    __shared__ int wsum[kScanThreads / 64];
+    int v = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kScanThreads) v += tops[i];
 #pragma unroll
-  for (int i = 0; i < kScanPer; ++i)
-    if (base + i < n) data[base + i] += add;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane_id() == 0) wsum[threadIdx.x / 64] = v;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) add += wsum[w];
+    if (threadIdx.x == 0 && grand && blockIdx.x == gridDim.x - 1) *grand = add + tops[blockIdx.x];
+  }
+  const int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
+  int v[kScanPer];
+  load_run<kScanPer>(data, base, n, v);
+#pragma unroll
+  for (int i = 0; i < kScanPer; ++i) v[i] += add;
+  store_run<kScanPer>(data, base, n, v);
 }
 
 }  // namespace
@@ -664,12 +764,21 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* __restrict__
 size_t scan_tmp_bytes(int64_t n) { return align_up(sizeof(int32_t) * (size_t)((n + kScanBlock - 1) / kScanBlock + 1), 256); }
 
 void exclusive_scan_i32(int32_t* d_data, int64_t n, int32_t* d_total, void* d_tmp, hipStream_t s) {
-  int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  if (nb == 0) nb = 1;
+  if (n <= kScanOne) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, d_data, n, d_total);
+    return;
+  }
+  const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
   int32_t* tops = (int32_t*)d_tmp;
   hipLaunchKernelGGL(k_scan_local, dim3((unsigned)nb), dim3(kScanThreads), 0, s, d_data, n, tops);
+  if (nb <= kScanTops) {
+    hipLaunchKernelGGL(k_scan_add<false>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, d_data, n,
+                       (const int32_t*)tops, d_total);
+    return;
+  }
   hipLaunchKernelGGL(k_scan_tops, dim3(1), dim3(kScanThreads), 0, s, tops, nb, d_total);
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)nb), dim3(kScanThreads), 0, s, d_data, n, (const int32_t*)tops);
+  hipLaunchKernelGGL(k_scan_add<true>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, d_data, n, (const int32_t*)tops,
+                     (int32_t*)nullptr);
 }
 
 IndexLayout index_layout(int64_t n_padded) {
@@ -746,10 +855,15 @@ int index_enqueue(const uint8_t* d_codes, const int64_t* d_seq_start, int32_t n_
 
   SeedClasses sc = seed_classes();
   timing_mark(kStageIndex, false, stream);
-  // a fill kernel rather than a memset node, so that the sequence can be captured in a graph
-  hipLaunchKernelGGL(k_clear2, dim3(1), dim3(64), 0, stream, d_err);
-  hipLaunchKernelGGL(k_layout_check, dim3((unsigned)((n_seqs + 1 + 255) / 256)), dim3(256), 0, stream, d_seq_start,
-                     n_seqs, n_padded, tile_seq, W.tiles1, d_err);
+  if (n_seqs < kLayoutOne) {
+    hipLaunchKernelGGL(k_layout_check_one, dim3(1), dim3(kLayoutThreads), 0, stream, d_seq_start, n_seqs, n_padded,
+                       tile_seq, W.tiles1, d_err);
+  } else {
+    // a fill kernel rather than a memset node, so that the sequence can be captured in a graph
+    hipLaunchKernelGGL(k_clear2, dim3(1), dim3(64), 0, stream, d_err);
+    hipLaunchKernelGGL(k_layout_check, dim3((unsigned)((n_seqs + 1 + 255) / 256)), dim3(256), 0, stream, d_seq_start,
+                       n_seqs, n_padded, tile_seq, W.tiles1, d_err);
+  }
   // After a layout error the passes that read the tile table or the word
   // arrays return at once and key_off says the index holds no word.
   const unsigned g1 = (unsigned)((W.tiles1 + kIxWaves - 1) / kIxWaves);

@@ -15,6 +15,7 @@
 // are replaced by device-side flags (a bank with an error gets an empty work
 // list, the gapped filter reads the hit count from device memory), so a replay
 // needs no host round trip.  Counters are cleared by kernels, not memset nodes.
+#include <stddef.h>
 #include <string.h>
 
 #include <new>
@@ -38,12 +39,26 @@ namespace plast {
 namespace {
 
 struct PipelineLayout {
-  size_t idx_a, idx_b, build, uws, total;
+  size_t uws, idx_a, idx_b, build, total;
+};
+constexpr size_t kPipeUws = 256;
+
+// What a result needs, as it lies at the start of a pipeline's or a search's
+// workspace.
+template <typename Head>
+struct __align__(8) ResultHead {
+  Head head;
+  uint8_t pad[256 - sizeof(Head)];
+  UngappedCounters c;
 };
 
 PipelineLayout pipeline_layout(const plast_bank_t* a, const plast_bank_t* b, int64_t max_items) {
   PipelineLayout L;
-  size_t off = 256;  // error words of both banks
+  // error words of both banks, then the extension's workspace, whose counters are
+  // read back with them in one copy
+  size_t off = kPipeUws;
+  L.uws = off;
+  off = align_up(off + ungapped_ws_fixed_bytes() + sizeof(WorkItem) * (size_t)max_items, 256);
   L.idx_a = off;
   off = align_up(off + index_layout(a->n_padded).total, 256);
   L.idx_b = off;
@@ -51,8 +66,6 @@ PipelineLayout pipeline_layout(const plast_bank_t* a, const plast_bank_t* b, int
   L.build = off;
   const size_t wa = index_ws_bytes(a->n_padded), wb = index_ws_bytes(b->n_padded);
   off = align_up(off + (wa > wb ? wa : wb), 256);
-  L.uws = off;
-  off = align_up(off + ungapped_ws_fixed_bytes() + sizeof(WorkItem) * (size_t)max_items, 256);
   L.total = off;
   return L;
 }
@@ -106,7 +119,7 @@ int pipeline_create_impl(const plast_bank_t* a, const plast_bank_t* b, const pla
     rc = index_enqueue(b->codes, b->seq_start, b->n_seqs, b->n_padded, base + L.idx_b, base + L.build, P->err_b,
                        &P->vb, P->cap);
   if (rc == PLAST_OK)
-    rc = ungapped_enqueue_batched(&P->va, &P->vb, p, T, ~0u, P->uws, L.total - L.uws, d_hits, capacity, P->err_a,
+    rc = ungapped_enqueue_batched(&P->va, &P->vb, p, T, ~0u, P->uws, L.idx_a - L.uws, d_hits, capacity, P->err_a,
                                   P->err_b, nullptr, nullptr, P->cap);
   if (rc == PLAST_OK && capacity > 0)
     rc = gapped_filter_impl(&P->va, &P->vb, d_hits, capacity, ungapped_n_hits_dev(P->uws), g, d_gscore, d_pass,
@@ -137,11 +150,15 @@ int pipeline_launch_impl(plast_pipeline_t* pl, hipStream_t s) {
 }
 
 int pipeline_result_impl(plast_pipeline_t* pl, plast_pipeline_result_t* out, hipStream_t s) {
-  int32_t err[4] = {0, 0, 0, 0};
-  UngappedCounters c{0, 0, 0, 0, 0};
-  PLAST_HIP(hipMemcpyAsync(err, pl->err_a, sizeof(err), hipMemcpyDeviceToHost, s));
-  PLAST_HIP(hipMemcpyAsync(&c, ungapped_counters_dev(pl->uws), sizeof(c), hipMemcpyDeviceToHost, s));
+  struct Err {
+    int32_t e[4];
+  };
+  ResultHead<Err> h;
+  static_assert(offsetof(ResultHead<Err>, c) == kPipeUws, "workspace start");
+  PLAST_HIP(hipMemcpyAsync(&h, pl->err_a, sizeof(h), hipMemcpyDeviceToHost, s));
   PLAST_HIP(hipStreamSynchronize(s));
+  const int32_t* err = h.head.e;
+  const UngappedCounters& c = h.c;
   out->n_items = c.n_items;
   out->n_hits = (int64_t)c.n_hits;
   out->n_ext = (int64_t)c.n_ext;
@@ -209,12 +226,15 @@ SearchLayout search_layout(const plast_bank_t* a, int64_t max_items) {
   return L;
 }
 
-__global__ void k_search_header(SearchHeader* h, int64_t capacity, int64_t n_words_b) {
+// The search's header, and its segment counters (n_zero of them) cleared.
+__global__ void k_search_header(SearchHeader* h, int64_t capacity, int64_t n_words_b,
+                                unsigned long long* __restrict__ zero, int n_zero) {
   if (threadIdx.x == 0) {
     h->n_match = 0ull;
     h->capacity = capacity;
     h->n_words_b = n_words_b;
   }
+  for (int i = threadIdx.x; i < n_zero; i += blockDim.x) zero[i] = 0ull;
 }
 
 constexpr int kCompactThreads = 256;
@@ -403,10 +423,6 @@ __global__ __launch_bounds__(kCompactThreads) void k_tile_scatter(
   }
 }
 
-__global__ void k_zero_u64(unsigned long long* __restrict__ p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0ull;
-}
-
 }  // namespace
 
 size_t search_ws_bytes(const plast_bank_t* a, int64_t max_items) { return search_layout(a, max_items).total; }
@@ -424,7 +440,9 @@ int search_enqueue_impl(const plast_bank_t* a, const plast_index_t* b, const pla
   uint8_t* base = (uint8_t*)d_ws;
   SearchHeader* hdr = (SearchHeader*)base;
   plast_index_t va;
-  hipLaunchKernelGGL(k_search_header, dim3(1), dim3(64), 0, s, hdr, capacity, b->n_words);
+  const bool grouped = d_matches && d_seg_first && capacity > 0;
+  hipLaunchKernelGGL(k_search_header, dim3(1), dim3(256), 0, s, hdr, capacity, b->n_words,
+                     (unsigned long long*)d_seg_off, grouped ? n_seg + 1 : 0);
   int rc = index_enqueue(a->codes, a->seq_start, a->n_seqs, a->n_padded, base + L.idx_a, base + L.build, hdr->err,
                          &va, s);
   if (rc != PLAST_OK) return rc;
@@ -438,11 +456,10 @@ int search_enqueue_impl(const plast_bank_t* a, const plast_index_t* b, const pla
     const int64_t blocks = min((int64_t)kCompactBlocks, (capacity + kCompactThreads - 1) / kCompactThreads);
     const int64_t tiles = min((int64_t)kCompactBlocks, (capacity + kMatchTile - 1) / kMatchTile);
     const unsigned long long* nh = ungapped_n_hits_dev(uws);
-    if (d_matches && d_seg_first) {
+    if (grouped) {
       unsigned long long* off = (unsigned long long*)d_seg_off;
       unsigned long long* cur = off + (n_seg + 1);
       const bool tiled = n_seg <= kTileSegs;
-      hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, off, n_seg + 1);
       if (tiled)
         hipLaunchKernelGGL(k_tile_count, dim3((unsigned)tiles), dim3(kCompactThreads), 0, s, (const plast_hit_t*)d_hits,
                            (const uint8_t*)d_pass, nh, capacity, d_seg_first, (int)n_seg, off);
@@ -470,12 +487,12 @@ int search_enqueue_impl(const plast_bank_t* a, const plast_index_t* b, const pla
 }
 
 int search_result_impl(const void* d_ws, plast_pipeline_result_t* out, int64_t* n_matches, hipStream_t s) {
-  SearchHeader h;
-  UngappedCounters c{0, 0, 0, 0, 0};
-  PLAST_HIP(hipMemcpyAsync(&h, d_ws, sizeof(h), hipMemcpyDeviceToHost, s));
-  PLAST_HIP(hipMemcpyAsync(&c, ungapped_counters_dev((const uint8_t*)d_ws + kSearchUws), sizeof(c),
-                           hipMemcpyDeviceToHost, s));
+  ResultHead<SearchHeader> r;
+  static_assert(offsetof(ResultHead<SearchHeader>, c) == kSearchUws, "workspace start");
+  PLAST_HIP(hipMemcpyAsync(&r, d_ws, sizeof(r), hipMemcpyDeviceToHost, s));
   PLAST_HIP(hipStreamSynchronize(s));
+  const SearchHeader& h = r.head;
+  const UngappedCounters& c = r.c;
   const int64_t capacity = h.capacity;
   out->n_items = c.n_items;
   out->n_hits = (int64_t)c.n_hits;

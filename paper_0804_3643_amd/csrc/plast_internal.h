@@ -87,7 +87,8 @@ int build_index_impl(const uint8_t* d_codes, const int64_t* d_seq_start, int32_t
                      void* d_index, void* d_ws, plast_index_t* out, hipStream_t stream);
 
 // ---------------------------------------------------------------- scans
-// Exclusive int32 scan of n elements in place; d_tmp needs scan_tmp_bytes(n).
+// Exclusive int32 scan of n elements in place (16-byte aligned); d_tmp needs
+// scan_tmp_bytes(n).  d_total may be null.
 size_t scan_tmp_bytes(int64_t n);
 void exclusive_scan_i32(int32_t* d_data, int64_t n, int32_t* d_total, void* d_tmp, hipStream_t s);
 

@@ -504,13 +504,12 @@ void k_ungapped_plain(UngappedArgs A, int32_t key, int32_t n_row_tiles, int32_t 
 }
 
 // Workspace header of the BATCHED schedule: UngappedCounters at 0, queue
-// counters at 32 (kMaxQueues int32), the length of the list at 64, all cleared
-// by the first kernel.
+// counters at 32 (kMaxQueues int32), the length of the list at 64, all set by the
+// first kernel.
 constexpr int kCtrOffset = 32;
 constexpr int kListOffset = 64;
-constexpr int kHeaderDwords = 17;
 static_assert(sizeof(UngappedCounters) <= kCtrOffset, "counter header");
-static_assert(kCtrOffset + 4 * kMaxQueues <= kListOffset && kListOffset + 4 <= 4 * kHeaderDwords, "queue counters");
+static_assert(kCtrOffset + 4 * kMaxQueues <= kListOffset && kListOffset + 4 <= 256, "queue counters");
 
 // Pops the items of the work list until every queue is empty.
 template <typename Run>
@@ -565,6 +564,11 @@ struct PlanShape {
   int32_t rows;   // rows of an item of the list that is run (kTileRows or kMRows)
 };
 
+// Column ranges of a key (occurrence counts are below 2^31: 32-bit divisions).
+__host__ __device__ __forceinline__ uint32_t col_items(int64_t n2, int32_t width) {
+  return ((uint32_t)n2 + (uint32_t)width - 1) / (uint32_t)width;
+}
+
 // Items of kTileRows rows: the length that is reported and held against the
 // workspace's limit, whatever the rows of the items that are run (no fewer).
 __host__ __device__ __forceinline__ int64_t items_of(const PlanShape& P, int64_t n1, int64_t n2, int32_t* width) {
@@ -575,51 +579,119 @@ __host__ __device__ __forceinline__ int64_t items_of(const PlanShape& P, int64_t
     if (n2 >= P.min_n2[i]) c = i;
   if (!((P.mask >> c) & 1u)) return 0;
   *width = P.cols[c];
-  return ((n1 + kTileRows - 1) / kTileRows) * ((n2 + P.cols[c] - 1) / P.cols[c]);
+  return (int64_t)(((uint32_t)n1 + kTileRows - 1) / kTileRows) * col_items(n2, P.cols[c]);
 }
 
-__global__ void k_plan_count(const int64_t* __restrict__ a_off, const int64_t* __restrict__ b_off, PlanShape P,
-                             int32_t* __restrict__ keycnt, UngappedCounters* __restrict__ cnt) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= kNKeys) return;
-  int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
-  int32_t w = 0;
-  const int64_t c = items_of(P, n1, n2, &w);
-  const int64_t run = c > 0 ? ((n1 + P.rows - 1) / P.rows) * ((n2 + w - 1) / w) : 0;
-  keycnt[k] = (int32_t)min(run, (int64_t)INT32_MAX);
-  if (c > 0) {
-    atomicAdd(&cnt->n_ext, (unsigned long long)(n1 * n2));
-    atomicAdd(&cnt->n_items64, (unsigned long long)c);
-  }
+// Row ranges of an item of the list that is run.
+__host__ __device__ __forceinline__ uint32_t row_items(const PlanShape& P, int64_t n1) {
+  return ((uint32_t)n1 + (uint32_t)P.rows - 1) / (uint32_t)P.rows;
 }
 
-__global__ void k_plan_emit(const int64_t* __restrict__ a_off, const int64_t* __restrict__ b_off, PlanShape P,
-                            const int32_t* __restrict__ item_off, UngappedCounters* __restrict__ cnt,
-                            int64_t max_items, const int32_t* __restrict__ err_a, const int32_t* __restrict__ err_b,
-                            WorkItem* __restrict__ items) {
-  const int k = blockIdx.x;
-  const unsigned long long n = cnt->n_items64;
-  if (k == 0 && threadIdx.x == 0) cnt->n_items = (int32_t)n;
-  const int flag = (n > (unsigned long long)max_items || n > (unsigned long long)INT32_MAX)
-                       ? 1
-                       : (((err_a && *err_a) || (err_b && *err_b)) ? 2 : 0);
-  if (flag) {
-    if (k == 0 && threadIdx.x == 0) cnt->overflow = flag;
-    return;
+// The header and the per-key offsets of the list, by one workgroup: the counts,
+// their scan and the checks in one launch.  The list stays empty (overflow set) when it is longer than the
+// workspace holds (1) or a bank had an error (2).
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanPer = (kNKeys + kPlanThreads - 1) / kPlanThreads;
+
+__global__ __launch_bounds__(kPlanThreads) void k_plan_count(
+    const int64_t* __restrict__ a_off, const int64_t* __restrict__ b_off, PlanShape P, int32_t* __restrict__ keyoff,
+    int64_t max_items, const int32_t* __restrict__ err_a, const int32_t* __restrict__ err_b,
+    UngappedCounters* __restrict__ cnt, int32_t* __restrict__ ctr, int32_t* __restrict__ list_len) {
+  __shared__ int wrun[kPlanThreads / 64];
+  __shared__ unsigned long long wext[kPlanThreads / 64], witems[kPlanThreads / 64];
+  __shared__ int32_t count[kPlanPer * kPlanThreads];
+  const int lane = __lane_id(), wid = threadIdx.x >> 6;
+  unsigned long long ext = 0, items = 0;
+#pragma unroll
+  for (int i = 0; i < kPlanPer; ++i) {
+    const int k = i * kPlanThreads + threadIdx.x;
+    int32_t c = 0;
+    if (k < kNKeys) {
+      const int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
+      int32_t w = 0;
+      const int64_t all = items_of(P, n1, n2, &w);
+      if (all > 0) {
+        ext += (unsigned long long)(n1 * n2);
+        items += (unsigned long long)all;
+        c = (int32_t)min((int64_t)row_items(P, n1) * col_items(n2, w), (int64_t)INT32_MAX);
+      }
+    }
+    count[k] = c;
   }
-  int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
+  __syncthreads();
+  const int k0 = threadIdx.x * kPlanPer;
+  int run[kPlanPer], sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPlanPer; ++i) {
+    run[i] = count[k0 + i];
+    sum += run[i];
+  }
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+    ext += __shfl_xor(ext, o);
+    items += __shfl_xor(items, o);
+  }
+  if (lane == 63) wrun[wid] = incl;
+  if (lane == 0) {
+    wext[wid] = ext;
+    witems[wid] = items;
+  }
+  __syncthreads();
+  int at = incl - sum, total = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    at += w < wid ? wrun[w] : 0;
+    total += wrun[w];
+  }
+#pragma unroll
+  for (int i = 0; i < kPlanPer; ++i) {
+    count[k0 + i] = at;
+    at += run[i];
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kNKeys; k += kPlanThreads) keyoff[k] = count[k];
+  if (threadIdx.x == 0) {
+    UngappedCounters c{0, 0, 0, 0, 0};
+    for (int w = 0; w < kPlanThreads / 64; ++w) {
+      c.n_ext += wext[w];
+      c.n_items64 += witems[w];
+    }
+    c.n_items = (int32_t)c.n_items64;
+    c.overflow = (c.n_items64 > (unsigned long long)max_items || c.n_items64 > (unsigned long long)INT32_MAX)
+                     ? 1
+                     : (((err_a && *err_a) || (err_b && *err_b)) ? 2 : 0);
+    *cnt = c;
+    *list_len = total;
+  }
+  if (threadIdx.x < kMaxQueues) ctr[threadIdx.x] = 0;
+}
+
+// The items of a key, one wavefront each.
+constexpr int kEmitThreads = 256;
+
+__global__ __launch_bounds__(kEmitThreads) void k_plan_emit(const int64_t* __restrict__ a_off,
+                                                            const int64_t* __restrict__ b_off, PlanShape P,
+                                                            const int32_t* __restrict__ keyoff,
+                                                            const UngappedCounters* __restrict__ cnt,
+                                                            WorkItem* __restrict__ items) {
+  const int k = (int)blockIdx.x * (kEmitThreads / 64) + (int)(threadIdx.x >> 6);
+  if (k >= kNKeys || cnt->overflow) return;
+  const int64_t n1 = a_off[k + 1] - a_off[k], n2 = b_off[k + 1] - b_off[k];
   int32_t width = 0;
   if (items_of(P, n1, n2, &width) == 0) return;
-  const int nrt = (int)((n1 + P.rows - 1) / P.rows);
-  const int ni = nrt * (int)((n2 + width - 1) / width);
-  for (int idx = threadIdx.x; idx < ni; idx += blockDim.x) {
+  const int nrt = (int)row_items(P, n1);
+  const int ni = nrt * (int)col_items(n2, width);
+  for (int idx = __lane_id(); idx < ni; idx += 64) {
     const int rt = idx % nrt, ct = idx / nrt;  // row tiles of one column range are adjacent
     WorkItem w;
     w.key = k;
     w.row0 = rt * P.rows;
     w.col0 = ct * width;
     w.ncols = (int)min((int64_t)width, n2 - (int64_t)w.col0);
-    items[item_off[k] + idx] = w;
+    items[keyoff[k] + idx] = w;
   }
 }
 
@@ -630,13 +702,13 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
 
 // ---------------------------------------------------------------- workspace
 // [0, 256): UngappedCounters, queue counters
-// [256, ...): per-key item counts/offsets (int32[kNKeys]), scan scratch, items
+// [256, ...): per-key item offsets (int32[kNKeys]), 256 bytes unused (they keep the
+// list length that a given workspace holds), items
 struct UngappedWs {
   UngappedCounters* cnt;
   int32_t* ctr;
   int32_t* list_len;
   int32_t* keycnt;
-  void* scan_tmp;
   WorkItem* items;
   int64_t max_items;
 };
@@ -648,7 +720,6 @@ UngappedWs carve(void* d_ws, size_t ws_bytes) {
   W.ctr = (int32_t*)(p + kCtrOffset);
   W.list_len = (int32_t*)(p + kListOffset);
   W.keycnt = (int32_t*)(p + 256);
-  W.scan_tmp = p + 256 + align_up(sizeof(int32_t) * kNKeys, 256);
   W.items = (WorkItem*)(p + ungapped_ws_fixed_bytes());
   W.max_items = ungapped_ws_max_items(ws_bytes);
   return W;
@@ -764,7 +835,7 @@ int ungapped_prepare() {
              : set_error(PLAST_E_HIP, "cannot query device occupancy");
 }
 
-size_t ungapped_ws_fixed_bytes() { return 256 + align_up(sizeof(int32_t) * kNKeys, 256) + scan_tmp_bytes(kNKeys); }
+size_t ungapped_ws_fixed_bytes() { return 256 + align_up(sizeof(int32_t) * kNKeys, 256) + 256; }
 
 int64_t ungapped_ws_max_items(size_t ws_bytes) {
   const size_t f = ungapped_ws_fixed_bytes();
@@ -819,13 +890,12 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   const int grid = persistent_grid(tile);
   if (grid <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
   const PlanShape P = shape_of(t, class_mask, tile == Tile::kMfma ? kMRows : kTileRows);
-  hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, stream, (uint32_t*)d_ws, (int64_t)kHeaderDwords, 0u);
   timing_mark(kStagePlan, false, stream);
-  hipLaunchKernelGGL(k_plan_count, dim3((kNKeys + 255) / 256), dim3(256), 0, stream, a->key_off, b->key_off, P,
-                     W.keycnt, W.cnt);
-  exclusive_scan_i32(W.keycnt, kNKeys, W.list_len, W.scan_tmp, stream);
-  hipLaunchKernelGGL(k_plan_emit, dim3(kNKeys), dim3(256), 0, stream, a->key_off, b->key_off, P,
-                     (const int32_t*)W.keycnt, W.cnt, W.max_items, err_a, err_b, W.items);
+  hipLaunchKernelGGL(k_plan_count, dim3(1), dim3(kPlanThreads), 0, stream, a->key_off, b->key_off, P, W.keycnt,
+                     W.max_items, err_a, err_b, W.cnt, W.ctr, W.list_len);
+  hipLaunchKernelGGL(k_plan_emit, dim3((kNKeys + kEmitThreads / 64 - 1) / (kEmitThreads / 64)), dim3(kEmitThreads), 0,
+                     stream, a->key_off, b->key_off, P, (const int32_t*)W.keycnt, (const UngappedCounters*)W.cnt,
+                     W.items);
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
@@ -904,7 +974,7 @@ int ungapped_extend_impl(const plast_index_t* a, const plast_index_t* b, const p
 }
 
 // ---------------------------------------------------------------- allocation-free variant
-// The BATCHED workspace (counters, per-key item counts, scan scratch, work
+// The BATCHED workspace (counters, per-key item offsets, work
 // list) of plast_ungapped_extend_noalloc lives in this fixed device array
 // instead of caller memory.  Every GPU the library runs on holds its own copy
 // until the process ends.  In host code the name `scratch` is only a host-side
@@ -942,8 +1012,8 @@ int ungapped_extend_noalloc_impl(const plast_index_t* a, const plast_index_t* b,
   void* ws = nullptr;
   const int rc = static_scratch(&ws);
   if (rc != PLAST_OK) return rc;
-  // The schedule's first kernel clears the counter header; the per-key counts,
-  // the scan scratch and the work list are written in full before being read,
+  // The schedule's first kernel sets the counter header; the per-key offsets
+  // and the work list are written in full before being read,
   // so what an earlier call left in the array does not matter.
   return ungapped_extend_impl(a, b, p, PLAST_BATCHED, ws, kStaticScratchBytes, d_hits, capacity, h_n_hits, h_n_ext,
                               stream);
