@@ -486,6 +486,7 @@ __device__ void run_item(const UngappedArgs& A, const WorkItem it, Smem& S) {
 }
 
 #include "ungapped_mfma.h"
+#include "ungapped_wave.h"
 
 constexpr int kPlainCols = 4096;  // item width of the PLAIN schedule
 
@@ -736,8 +737,9 @@ PlanShape shape_of(const plast_tuning_t& t, uint32_t mask, int rows) {
   return P;
 }
 
-// Which tile routine is exact for a matrix: the matrix cores, packed binary16 or int16.
-enum class Tile { kMfma, kF16, kI16 };
+// The kernels of the BATCHED schedule: on the matrix cores, packed binary16 or
+// int16 on a workgroup per item, and the same on a wavefront per item.
+enum class Tile { kMfma, kF16, kI16, kWaveF16, kWaveI16 };
 
 Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, const plast_ungapped_params_t* p,
                plast_hit_t* d_hits, int64_t capacity, unsigned long long* n_hits) {
@@ -771,6 +773,9 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
     const uint16_t h = (uint16_t)(int16_t)t;
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   }
+  // Small banks on both sides: an item per wavefront.
+  if (b->n_padded < kWMaxCols * kNKeys && (double)a->n_padded * (double)b->n_padded <= kWMaxCodes)
+    return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
   // The matrix-core tile counts on pairs of score 0 not being hits, and pays
   // from about 12 rows a key on: against 100,000 proteins, a query of 450 (143,000
   // codes) takes 1.25 ms on it and 1.39 on the VALU tiles, one of 200 (64,000) 0.91
@@ -792,8 +797,10 @@ int resident_grid(K kernel, int threads, int* cached) {
 }
 
 int persistent_grid(Tile t) {
-  static int cached[3] = {0, 0, 0};
+  static int cached[5] = {0, 0, 0, 0, 0};
   switch (t) {
+    case Tile::kWaveF16: return resident_grid(k_ungapped_wave<true>, kThreads, &cached[3]);
+    case Tile::kWaveI16: return resident_grid(k_ungapped_wave<false>, kThreads, &cached[4]);
     case Tile::kMfma: return resident_grid(k_ungapped_mfma, kMThreads, &cached[0]);
     case Tile::kF16: return resident_grid(k_ungapped_persistent<true>, kThreads, &cached[1]);
     default: return resident_grid(k_ungapped_persistent<false>, kThreads, &cached[2]);
@@ -830,7 +837,8 @@ int check_tuning(const plast_tuning_t* t) {
 }
 
 int ungapped_prepare() {
-  return (persistent_grid(Tile::kMfma) > 0 && persistent_grid(Tile::kF16) > 0 && persistent_grid(Tile::kI16) > 0)
+  return (persistent_grid(Tile::kMfma) > 0 && persistent_grid(Tile::kF16) > 0 && persistent_grid(Tile::kI16) > 0 &&
+          persistent_grid(Tile::kWaveF16) > 0 && persistent_grid(Tile::kWaveI16) > 0)
              ? PLAST_OK
              : set_error(PLAST_E_HIP, "cannot query device occupancy");
 }
@@ -899,7 +907,13 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
-  if (tile == Tile::kMfma)
+  if (tile == Tile::kWaveF16)
+    hipLaunchKernelGGL(k_ungapped_wave<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len);
+  else if (tile == Tile::kWaveI16)
+    hipLaunchKernelGGL(k_ungapped_wave<false>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len);
+  else if (tile == Tile::kMfma)
     hipLaunchKernelGGL(k_ungapped_mfma, dim3(grid), dim3(kMThreads), 0, stream, A, (const WorkItem*)W.items,
                        (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues);
   else if (tile == Tile::kF16)
@@ -929,7 +943,8 @@ int ungapped_extend_impl(const plast_index_t* a, const plast_index_t* b, const p
 
   if (mode == PLAST_PLAIN) {
     UngappedArgs A;
-    const bool f16 = fill_args(A, a, b, p, d_hits, capacity, &((UngappedCounters*)d_ws)->n_hits) != Tile::kI16;
+    const Tile tile = fill_args(A, a, b, p, d_hits, capacity, &((UngappedCounters*)d_ws)->n_hits);
+    const bool f16 = tile != Tile::kI16 && tile != Tile::kWaveI16;
     std::vector<int64_t> ha(kNKeys + 1), hb(kNKeys + 1);
     int rc;
     if ((rc = read_key_offsets(a, ha.data(), stream)) || (rc = read_key_offsets(b, hb.data(), stream))) return rc;

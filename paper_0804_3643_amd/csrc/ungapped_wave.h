@@ -1,0 +1,182 @@
+// The ungapped extension with a work item per wavefront (included by
+// ungapped.hip, inside its namespace), for small banks.
+//
+// With a few hundred proteins on both sides a key has a handful of rows and tens
+// of columns: a workgroup of 512 on such an item idles on all but a few lanes,
+// spends about 9 us on the item's chain of loads and barriers, and the atomic that
+// hands out items, about 12 ns each on one address, takes as long as the pairs.
+// Here every wavefront takes items of its own, by striding over the list: 16
+// wavefronts on a compute unit, each with the profile of 4 rows at a time (7 KB of
+// LDS), no barrier before the end, and the hits of a workgroup's wavefronts staged
+// together and written with one global atomic.  Bound by the latency of the loads
+// that an item begins with (work list, key table, occurrences, letters).
+//
+// Measured, against a workgroup per item: 200 x 2000 proteins (8800 items of 7 x 66
+// on average) 66 us, 164; 30 x 2000 29, 75; 3 x 300 10, 22.
+constexpr int kWWaves = kThreads / 64;
+constexpr int kWSlots = 512;
+// Chosen for a bank b of fewer than 200 codes a key, and no more pairs than two
+// banks of 2000 proteins have, so that an item is a few column groups and no
+// wavefront has many (proteins, us here and on a workgroup per item): 200 x 4000 107
+// and 181, 200 x 10,000 251 and 203, 1000 x 2000 160 and 238, 1000 x 5000 325 and 267,
+// 3000 x 2000 393 and 447, 10,000 x 300 708 and 1020, 10,000 x 2000 2990 and 1250.
+constexpr int64_t kWMaxCols = 200;
+constexpr double kWMaxCodes = 4e11;
+
+constexpr int kWMatRow = 22;                        // entries of a matrix row in LDS: dwords of two letters
+constexpr int kWRows = 8;                           // rows of an item that a wavefront takes at a time
+
+struct __align__(16) WSmem {
+  uint8_t prof[kWWaves][kProfRG];      // 8-byte entries
+  uint16_t mat[kNLet * kWMatRow];      // profile values (int16 or binary16 bits)
+  int32_t hit_a[kWSlots], hit_b[kWSlots], hit_score[kWSlots];  // occurrence indexes
+  int32_t n_hit;                       // slots reserved
+  int32_t n_fit;                       // start of the reservation that straddles the end
+  unsigned long long base;
+};
+
+__device__ __forceinline__ void w_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The record of a pair of occurrences.
+__device__ __forceinline__ void w_write(const UngappedArgs& A, unsigned long long at, int oa, int ob, int score) {
+  if (at >= (unsigned long long)A.capacity) return;
+  plast_hit_t h;
+  h.seq1 = A.a.occ_seq[oa];
+  h.pos1 = A.a.occ[oa] - (int)A.a.seq_start[h.seq1];
+  h.seq2 = A.b.occ_seq[ob];
+  h.pos2 = A.b.occ[ob] - (int)A.b.seq_start[h.seq2];
+  h.score = score;
+  A.hits[at] = h;
+}
+
+// The hits of one column per lane against 4 rows (row r of register r / 2): staged
+// if the wavefront's all fit, written directly if not.  All lanes call it.
+template <bool F16>
+__device__ __forceinline__ void w_hits(const UngappedArgs& A, WSmem& S, const vec2<F16> (&m)[2], uint32_t mask, int oa,
+                                       int ob) {
+  unsigned long long b[4];
+  int total = 0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    b[r] = __ballot((mask & row_bit(r)) != 0);
+    total += __popcll(b[r]);
+  }
+  if (total == 0) return;
+  int at = 0;
+  if (__lane_id() == 0) at = atomicAdd(&S.n_hit, total);
+  at = __builtin_amdgcn_readfirstlane(at);
+  const bool staged = at + total <= kWSlots;
+  unsigned long long g = 0;
+  if (!staged) {
+    if (__lane_id() == 0) {
+      if (at < kWSlots) S.n_fit = at;
+      g = atomicAdd(A.n_hits, (unsigned long long)total);
+    }
+    g = __shfl(g, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[r], 0u));
+    if (mask & row_bit(r)) {
+      const int score = to_int<F16>(m[r / 2], r & 1);
+      if (staged) {
+        S.hit_a[at + below] = oa + r;
+        S.hit_b[at + below] = ob;
+        S.hit_score[at + below] = score;
+      } else {
+        w_write(A, g + below, oa + r, ob, score);
+      }
+    }
+    at += __popcll(b[r]);
+    g += __popcll(b[r]);
+  }
+}
+
+// Rows row .. row + kWRows - 1 of an item (those that it has) against its columns.
+template <bool F16>
+__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int row, int wid, WSmem& S) {
+  const int lane = __lane_id();
+  const int64_t ka = A.a.key_off[it.key], ka1 = A.a.key_off[it.key + 1];
+  const int a0 = (int)ka + it.row0 + row, b0 = (int)A.b.key_off[it.key] + it.col0;
+  const int rows = min(min(kWRows, kTileRows - row), (int)ka1 - a0);
+  if (rows <= 0) return;
+  const int qrow = lane < rows ? A.a.occ[a0 + lane] : -1;
+  uint8_t* prof = S.prof[wid];
+  for (int r0 = 0; r0 < rows; r0 += 4) {
+    w_sync();  // the profile before is read
+    // Lane t writes the entries of scan step t: the scores of the 4 rows against two
+    // letters at a time, from the rows' letters at that step.
+    if (lane < kSpan) {
+      const int off = lane < kRight ? lane : -(lane - kRight + 1);
+      const uint32_t* row_of[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int q = __builtin_amdgcn_readlane(qrow, r0 + r);
+        const uint32_t letter = q >= 0 ? A.a.scan[q + off] / kScale : (uint32_t)kPadCode;
+        row_of[r] = (const uint32_t*)S.mat + letter * (kWMatRow / 2);
+      }
+      uint8_t* dst = prof + lane * kProfT;
+#pragma unroll
+      for (int c = 0; c < kNLet; c += 2) {
+        const uint32_t w0 = row_of[0][c / 2], w1 = row_of[1][c / 2], w2 = row_of[2][c / 2], w3 = row_of[3][c / 2];
+        *(uint2*)(dst + c * 8) = make_uint2(__builtin_amdgcn_perm(w1, w0, 0x05040100u), __builtin_amdgcn_perm(w3, w2, 0x05040100u));
+        if (c + 1 < kNLet)
+          *(uint2*)(dst + (c + 1) * 8) = make_uint2(__builtin_amdgcn_perm(w1, w0, 0x07060302u), __builtin_amdgcn_perm(w3, w2, 0x07060302u));
+      }
+    }
+    w_sync();
+    const uint32_t valid = valid_rows_mask(min(4, rows - r0));
+    for (int c0 = 0; c0 < it.ncols; c0 += 64) {
+      const bool active = c0 + lane < it.ncols;
+      const int ob = b0 + (active ? c0 + lane : 0);
+      const int q2 = A.b.occ[ob];
+      uint32_t raw[12], win[11];
+      load_window_raw(A, q2, raw);
+      const int sh = (q2 - kNbr) & 3;
+#pragma unroll
+      for (int i = 0; i < 11; ++i) win[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
+      vec2<F16> m[2];
+      scan_window<F16, 1>(prof, win, m);
+      w_hits<F16>(A, S, m, active ? (hit_mask<F16, 1>(A.thr, m) & valid) : 0u, a0 + r0, ob);
+    }
+  }
+}
+
+template <bool F16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const UngappedCounters* __restrict__ cnt,
+                     const int32_t* __restrict__ list_len) {
+  __shared__ WSmem S;
+  for (int i = threadIdx.x; i < kNLet * kNLet; i += kThreads) {
+    uint16_t v;
+    if constexpr (F16)
+      v = __builtin_bit_cast(uint16_t, (_Float16)A.mat[i]);
+    else
+      v = (uint16_t)A.mat[i];
+    S.mat[i / kNLet * kWMatRow + i % kNLet] = v;
+  }
+  if (threadIdx.x == 0) {
+    S.n_hit = 0;
+    S.n_fit = kWSlots;
+  }
+  __syncthreads();
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
+  // units of kWRows rows of an item, most of which have fewer rows in all
+  constexpr int kUnits = kTileRows / kWRows;
+  const int64_t n_units = (int64_t)n_items * kUnits, stride = (int64_t)gridDim.x * kWWaves;
+  for (int64_t u = (int64_t)blockIdx.x * kWWaves + wid; u < n_units; u += stride) {
+    // all first units before all second ones: neighbouring wavefronts have like work
+    const int i = (int)(u % n_items), part = (int)(u / n_items);
+    run_item_w<F16>(A, items[i], part * kWRows, wid, S);
+  }
+  __syncthreads();
+  const int n = min(S.n_hit, S.n_fit);
+  if (threadIdx.x == 0 && n > 0) S.base = atomicAdd(A.n_hits, (unsigned long long)n);
+  __syncthreads();
+  for (int e = threadIdx.x; e < n; e += kThreads) w_write(A, S.base + e, S.hit_a[e], S.hit_b[e], S.hit_score[e]);
+}
