@@ -37,7 +37,8 @@ namespace plast {
 namespace {
 
 constexpr int kANeg = -(1 << 28);
-constexpr int kSortTile = 4096;     // radix-sort elements per tile (one wavefront, 64 per lane)
+constexpr int kSortTile = 4096;     // most radix-sort elements per tile (one wavefront, 64 per lane)
+constexpr int kSortMin = 512;       // and fewest
 constexpr int kTStride = 32;        // entries per row of the LDS score table
 constexpr int kWall = -16256;       // table entry of any pair with the sentinel letter (low byte 0x80: -128 as 8 bits)
 constexpr int kYScale = 64 * 2;     // bytes per letter row of the per-lane profile (64 int16)
@@ -53,8 +54,7 @@ struct AlignHeader {
   int32_t sort_total;
   int32_t pass_total;             // passing hits (scan total of the per-wavefront counts)
   int32_t group_total;            // sequence pairs (likewise)
-  unsigned long long n_pass;
-  unsigned long long n_groups;
+  int32_t gmax, pad;              // largest gapped score of a passing hit
   unsigned long long next_group;
   unsigned long long n_out;
 };
@@ -77,7 +77,7 @@ struct AlignArgs {
 };
 
 struct AlignLayout {
-  size_t hdr, tbl, hidx, klo, khi, perm0, perm1, counts, pcount, scan_tmp, heads, tb, pieces, strip, total;
+  size_t hdr, tbl, order, key0, key1, val0, val1, counts, pcount, scan_tmp, heads, tb, pieces, strip, total;
   int64_t tiles;
   size_t tb_words_per_wave;
 };
@@ -108,15 +108,15 @@ AlignLayout align_layout(int64_t n, const plast_align_params_t& p, int64_t waves
   off = align_up(off + sizeof(AlignHeader), 256);
   L.tbl = off;
   off = align_up(off + sizeof(int16_t) * 21 * kTStride, 256);
-  L.hidx = off;
+  L.order = off;
   off = align_up(off + sizeof(int32_t) * (size_t)n, 256);
-  L.klo = off;
+  L.key0 = off;
   off = align_up(off + sizeof(uint64_t) * (size_t)n, 256);
-  L.khi = off;
+  L.key1 = off;
   off = align_up(off + sizeof(uint64_t) * (size_t)n, 256);
-  L.perm0 = off;
+  L.val0 = off;
   off = align_up(off + sizeof(int32_t) * (size_t)n, 256);
-  L.perm1 = off;
+  L.val1 = off;
   off = align_up(off + sizeof(int32_t) * (size_t)n, 256);
   L.counts = off;
   off = align_up(off + sizeof(int32_t) * 256 * (size_t)L.tiles, 256);
@@ -190,23 +190,44 @@ __device__ __forceinline__ bool align_hit_ok(const AlignArgs& A, const plast_hit
   return true;
 }
 
+// A gapped score as the sort keys hold it (14 bits).
+__device__ __forceinline__ int key_score(int g) { return min(max(g, 0), 16383); }
+
 // Compaction of the passing hits in two passes (no shared counter: one
 // atomic per wavefront on a single address serialises in L2): per-wavefront
 // counts, an exclusive scan, then each wavefront writes at its offset.
-__global__ __launch_bounds__(256) void k_align_count(AlignArgs A, const plast_hit_t* hits, const uint8_t* pass,
-                                                     int64_t n, AlignHeader* hdr, int32_t* pcount, int32_t* cover) {
+__global__ __launch_bounds__(256) void k_align_count(AlignArgs A, const plast_hit_t* hits, const int32_t* gscore,
+                                                     const uint8_t* pass, int64_t n, AlignHeader* hdr, int32_t* pcount,
+                                                     int32_t* cover) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (h < n) cover[h] = -1;
-  const uint64_t mask = __ballot(align_hit_ok(A, hits, pass, h, n, hdr, true));
+  const bool ok = align_hit_ok(A, hits, pass, h, n, hdr, true);
+  const uint64_t mask = __ballot(ok);
   if ((threadIdx.x & 63) == 0 && (h >> 6) < (n + 63) / 64) pcount[h >> 6] = (int32_t)__popcll(mask);
+  // largest score: one lane of a wavefront asks, and few find a larger one than
+  // the header holds (atomics of every lane on the one address took 80 us)
+  int g = ok ? key_score(gscore[h]) : 0;
+  for (int o = 32; o >= 1; o >>= 1) g = max(g, __shfl_xor(g, o));
+  if ((threadIdx.x & 63) == 0 && g > __hip_atomic_load(&hdr->gmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(&hdr->gmax, g);
 }
 
-// Sort keys of the compacted hits: (seq1, seq2) in khi, (16383 - gscore, pos1,
-// pos2) in klo, so ascending order is the group order.
+// How a hit's order is packed: ascending keys are the processing order.  The low
+// part is (gmax - score, pos1, pos2), the high part (seq1, seq2); one 64-bit key
+// holds both when they fit, otherwise the hits are sorted by the low parts and
+// then, stably, by the high ones.
+struct AlignKeys {
+  int gmax, bp1, bp2, b2, lo_bits;
+  bool both;
+};
+
+__device__ __forceinline__ uint64_t key_high(const AlignKeys& K, const plast_hit_t& r) {
+  return ((uint64_t)r.seq1 << K.b2) | (uint64_t)r.seq2;
+}
+
 __global__ __launch_bounds__(256) void k_align_keys(AlignArgs A, const plast_hit_t* hits, const int32_t* gscore,
-                                                    const uint8_t* pass, int64_t n, int bp1, int bp2, int b2,
-                                                    AlignHeader* hdr, const int32_t* poffset, int32_t* hidx,
-                                                    uint64_t* klo, uint64_t* khi) {
+                                                    const uint8_t* pass, int64_t n, AlignKeys K, AlignHeader* hdr,
+                                                    const int32_t* poffset, uint64_t* key, int32_t* val) {
   const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const bool ok = align_hit_ok(A, hits, pass, h, n, hdr, false);
   const uint64_t mask = __ballot(ok);
@@ -215,103 +236,123 @@ __global__ __launch_bounds__(256) void k_align_keys(AlignArgs A, const plast_hit
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   const int64_t c = (int64_t)poffset[h >> 6] + __popcll(mask & below);
   const plast_hit_t r = hits[h];
-  int g = gscore[h];
-  g = g < 0 ? 0 : (g > 16383 ? 16383 : g);
-  hidx[c] = (int32_t)h;
-  klo[c] = ((uint64_t)(16383 - g) << (bp1 + bp2)) | ((uint64_t)r.pos1 << bp2) | (uint64_t)r.pos2;
-  khi[c] = ((uint64_t)r.seq1 << b2) | (uint64_t)r.seq2;
+  uint64_t k = ((uint64_t)(K.gmax - key_score(gscore[h])) << (K.bp1 + K.bp2)) | ((uint64_t)r.pos1 << K.bp2) |
+               (uint64_t)r.pos2;
+  if (K.both) k |= key_high(K, r) << K.lo_bits;
+  key[c] = k;
+  val[c] = (int32_t)h;
+}
+
+// The high parts of hits in their order so far.
+__global__ __launch_bounds__(256) void k_align_high(const plast_hit_t* hits, AlignKeys K, int64_t m,
+                                                    const int32_t* __restrict__ val, uint64_t* __restrict__ key) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < m) key[i] = key_high(K, hits[val[i]]);
 }
 
 __global__ __launch_bounds__(64) void k_align_clear(AlignHeader* hdr) {
   if (threadIdx.x == 0) *hdr = AlignHeader{0, 0, 0, 0, 0, 0, 0, 0};
 }
 
-__global__ __launch_bounds__(64) void k_align_npass(AlignHeader* hdr) {
-  if (threadIdx.x == 0) hdr->n_pass = (unsigned long long)hdr->pass_total;
-}
-
-__global__ __launch_bounds__(256) void k_iota(int32_t* perm, const AlignHeader* hdr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < (int64_t)hdr->n_pass) perm[i] = (int32_t)i;
-}
-
-// Digit histogram of one tile (one wavefront, kSortTile elements in order).
-__global__ __launch_bounds__(64) void k_rs_count(const int32_t* perm, const uint64_t* key, int shift,
-                                                 const AlignHeader* hdr, int32_t* counts, int64_t tiles) {
+// Digit histogram of one tile (one wavefront, `tile` elements in order) of the
+// first min(m, *m_dev) elements (m_dev may be null).
+__global__ __launch_bounds__(64) void k_rs_count(const uint64_t* __restrict__ key, int shift, int64_t m,
+                                                 const int32_t* __restrict__ m_dev, int tile,
+                                                 int32_t* __restrict__ counts, int64_t tiles) {
   __shared__ int32_t hist[256];
   const int lane = threadIdx.x;
   for (int d = lane; d < 256; d += 64) hist[d] = 0;
   __syncthreads();
-  const int64_t m = (int64_t)hdr->n_pass;
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  for (int k = 0; k < kSortTile / 64; ++k) {
-    const int64_t i = base + k * 64 + lane;
-    if (i < m) atomicAdd(&hist[(int)((key[perm[i]] >> shift) & 255)], 1);
-  }
+  if (m_dev) m = min(m, (int64_t)*m_dev);
+  const int64_t base = (int64_t)blockIdx.x * tile;
+  const int64_t end = min(base + tile, m);
+#pragma unroll 8
+  for (int64_t i = base + lane; i < end; i += 64) atomicAdd(&hist[(int)((key[i] >> shift) & 255)], 1);
   __syncthreads();
   for (int d = lane; d < 256; d += 64) counts[(int64_t)d * tiles + blockIdx.x] = hist[d];
 }
 
 // Stable scatter: the tile's elements in order, ranked among equal digits of
-// the same 64-element round with ballots, after the earlier rounds' counts.
-__global__ __launch_bounds__(64) void k_rs_scatter(const int32_t* perm_in, const uint64_t* key, int shift,
-                                                   const AlignHeader* hdr, const int32_t* offsets, int64_t tiles,
-                                                   int32_t* perm_out) {
+// the same 64-element round with ballots, after the earlier rounds' counts; eight
+// rounds of loads are in flight.  key_out may be null.
+__global__ __launch_bounds__(64) void k_rs_scatter(const uint64_t* __restrict__ key, const int32_t* __restrict__ val,
+                                                   int shift, int64_t m, const int32_t* __restrict__ m_dev, int tile,
+                                                   const int32_t* __restrict__ offsets, int64_t tiles,
+                                                   uint64_t* __restrict__ key_out, int32_t* __restrict__ val_out) {
+  constexpr int kRounds = 8;
   __shared__ int32_t run[256];
   const int lane = threadIdx.x;
   for (int d = lane; d < 256; d += 64) run[d] = offsets[(int64_t)d * tiles + blockIdx.x];
   __syncthreads();
-  const int64_t m = (int64_t)hdr->n_pass;
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  if (m_dev) m = min(m, (int64_t)*m_dev);
+  const int64_t base = (int64_t)blockIdx.x * tile;
+  const int64_t end = min(base + tile, m);
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int k = 0; k < kSortTile / 64; ++k) {
-    const int64_t i = base + k * 64 + lane;
-    const bool valid = i < m;
-    const int32_t c = valid ? perm_in[i] : 0;
-    const int d = valid ? (int)((key[c] >> shift) & 255) : 0;
-    uint64_t peers = __ballot(valid);
+  for (int64_t i0 = base; i0 < end; i0 += 64 * kRounds) {
+    uint64_t k[kRounds];
+    int32_t v[kRounds];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint64_t ones = __ballot(valid && ((d >> b) & 1));
-      peers &= ((d >> b) & 1) ? ones : ~ones;
+    for (int j = 0; j < kRounds; ++j) {
+      const int64_t i = i0 + j * 64 + lane;
+      k[j] = i < end ? key[i] : 0;
+      v[j] = i < end ? val[i] : 0;
     }
-    const int rank = __popcll(peers & below);
-    const int start = run[d];
-    __syncthreads();
-    if (valid) {
-      perm_out[start + rank] = c;
-      if (rank == 0) run[d] = start + __popcll(peers);
+#pragma unroll
+    for (int j = 0; j < kRounds; ++j) {
+      const bool valid = i0 + j * 64 + lane < end;
+      const int d = (int)((k[j] >> shift) & 255);
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const uint64_t ones = __ballot(valid && ((d >> b) & 1));
+        peers &= ((d >> b) & 1) ? ones : ~ones;
+      }
+      const int rank = __popcll(peers & below);
+      const int start = run[d];
+      __syncthreads();
+      if (valid) {
+        if (key_out) key_out[start + rank] = k[j];
+        val_out[start + rank] = v[j];
+        if (rank == 0) run[d] = start + __popcll(peers);
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
 // First element of each sequence pair in sorted order, compacted in two passes
 // like the passing hits.
-__device__ __forceinline__ bool is_head(const int32_t* perm, const uint64_t* khi, const AlignHeader* hdr, int64_t i) {
-  return i < (int64_t)hdr->n_pass && (i == 0 || khi[perm[i]] != khi[perm[i - 1]]);
+__device__ __forceinline__ bool is_head(const uint64_t* __restrict__ key, int shift, int64_t m, int64_t i) {
+  return i < m && (i == 0 || key[i] >> shift != key[i - 1] >> shift);
 }
 
-__global__ __launch_bounds__(256) void k_align_head_count(const int32_t* perm, const uint64_t* khi,
-                                                          const AlignHeader* hdr, int32_t* hcount) {
+__global__ __launch_bounds__(256) void k_align_head_count(const uint64_t* __restrict__ key, int shift, int64_t m,
+                                                          int32_t* __restrict__ hcount) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t mask = __ballot(is_head(perm, khi, hdr, i));
-  if ((threadIdx.x & 63) == 0 && i < (int64_t)hdr->n_pass) hcount[i >> 6] = (int32_t)__popcll(mask);
+  const uint64_t mask = __ballot(is_head(key, shift, m, i));
+  if ((threadIdx.x & 63) == 0 && i < m) hcount[i >> 6] = (int32_t)__popcll(mask);
 }
 
-__global__ __launch_bounds__(256) void k_align_heads(const int32_t* perm, const uint64_t* khi, AlignHeader* hdr,
-                                                     const int32_t* hoffset, int32_t* heads) {
+// The heads, and for each a key by which a radix pass puts the pairs with the
+// largest rectangles first: a wavefront takes 1.4 ms over 1000 x 1000 letters, and
+// one that begins as the others end leaves the device idle.  The key is 255 less
+// the rectangle's size in eighths of an octave.
+__global__ __launch_bounds__(256) void k_align_heads(AlignArgs A, const plast_hit_t* hits,
+                                                     const uint64_t* __restrict__ key, const int32_t* __restrict__ val,
+                                                     int shift, int64_t m, const int32_t* __restrict__ hoffset,
+                                                     int32_t* __restrict__ heads, uint64_t* __restrict__ work) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool head = is_head(perm, khi, hdr, i);
+  const bool head = is_head(key, shift, m, i);
   const uint64_t mask = __ballot(head);
   if (!head) return;
   const int lane = threadIdx.x & 63;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  heads[hoffset[i >> 6] + __popcll(mask & below)] = (int32_t)i;
-}
-
-__global__ __launch_bounds__(64) void k_align_ngroups(AlignHeader* hdr) {
-  if (threadIdx.x == 0) hdr->n_groups = (unsigned long long)hdr->group_total;
+  const int64_t c = (int64_t)hoffset[i >> 6] + __popcll(mask & below);
+  const plast_hit_t r = hits[val[i]];
+  const float cells = (float)seq_len(A.a_start, r.seq1) * (float)seq_len(A.b_start, r.seq2);
+  const int octaves8 = (int)(__float_as_uint(cells) >> 20) - (127 << 3);  // 0 .. 8 * 28 for 1 .. 2^28 cells
+  heads[c] = (int32_t)i;
+  work[c] = (uint64_t)(255 - min(max(octaves8, 0), 255));
 }
 
 // ------------------------------------------------------------------ alignment
@@ -802,9 +843,9 @@ __global__ __launch_bounds__(64) void k_align_table(AlignArgs A, int16_t* __rest
 // resident workgroups to 10 per CU, so the registers cost no occupancy, and
 // with fewer the kernel spills.
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_align(
-    AlignArgs A, const int16_t* __restrict__ T, const plast_hit_t* hits, const int32_t* hidx, const int32_t* perm,
-    const uint64_t* khi, const int32_t* heads, AlignHeader* hdr, uint32_t* tb_all, size_t tb_words, Piece* pieces_all,
-    int2* strip_all, plast_alignment_t* out, int32_t* cover) {
+    AlignArgs A, const int16_t* __restrict__ T, const plast_hit_t* hits, const int32_t* __restrict__ val,
+    const uint64_t* __restrict__ key, int shift, int64_t m, const int32_t* __restrict__ heads, AlignHeader* hdr,
+    uint32_t* tb_all, size_t tb_words, Piece* pieces_all, int2* strip_all, plast_alignment_t* out, int32_t* cover) {
   extern __shared__ __align__(16) uint8_t lds[];
   int16_t* prof = (int16_t*)lds;
   uint8_t* yo = (uint8_t*)lds + 21 * 64 * kProfLaneBytes;
@@ -815,21 +856,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   uint32_t* tb = tb_all + (size_t)blockIdx.x * tb_words;
   Piece* P = pieces_all + (size_t)blockIdx.x * A.max_pieces;
   int2* strip = strip_all + (size_t)blockIdx.x * (size_t)strip_cols(A.max_len2);
-  const int64_t m = (int64_t)hdr->n_pass;
-  const int64_t n_groups = (int64_t)hdr->n_groups;
+  const unsigned n_groups = (unsigned)hdr->group_total;
   for (;;) {
     // fewer than 2^31 groups, and each wavefront overshoots the count once
     unsigned long long gq = 0;
     if (lane == 0) gq = atomicAdd(&hdr->next_group, 1ull);
     const int g = uni((int)gq);
-    if (g >= n_groups) break;
+    if ((unsigned)g >= n_groups) break;
     const int64_t k0 = heads[g];
-    const uint64_t gkey = khi[perm[k0]];
+    const uint64_t gkey = key[k0] >> shift;
     int np = 0;
     for (int64_t k = k0; k < m; ++k) {
-      const int32_t c = uni(perm[k]);
-      if (k > k0 && khi[c] != gkey) break;
-      const int32_t h = uni(hidx[c]);
+      if (k > k0 && key[k] >> shift != gkey) break;
+      const int32_t h = uni(val[k]);
       const plast_hit_t r = hits[h];
       const int s1 = uni(r.seq1), p1 = uni(r.pos1), s2 = uni(r.seq2), p2 = uni(r.pos2);
       // covered by a piece of an earlier alignment of the group?
@@ -919,10 +958,9 @@ int align_impl(const plast_index_t* a, const plast_index_t* b, const plast_hit_t
   if (ws_bytes < L.total) return set_error(PLAST_E_WORKSPACE, "alignment workspace %zu < %zu bytes", ws_bytes, L.total);
   uint8_t* ws = (uint8_t*)d_ws;
   AlignHeader* hdr = (AlignHeader*)(ws + L.hdr);
-  int32_t* hidx = (int32_t*)(ws + L.hidx);
-  uint64_t* klo = (uint64_t*)(ws + L.klo);
-  uint64_t* khi = (uint64_t*)(ws + L.khi);
-  int32_t* perm[2] = {(int32_t*)(ws + L.perm0), (int32_t*)(ws + L.perm1)};
+  uint64_t* key[2] = {(uint64_t*)(ws + L.key0), (uint64_t*)(ws + L.key1)};
+  int32_t* val[2] = {(int32_t*)(ws + L.val0), (int32_t*)(ws + L.val1)};
+  int32_t* order = (int32_t*)(ws + L.order);  // heads by work
   int32_t* counts = (int32_t*)(ws + L.counts);
   int32_t* heads = (int32_t*)(ws + L.heads);
   uint32_t* tb = (uint32_t*)(ws + L.tb);
@@ -951,52 +989,76 @@ int align_impl(const plast_index_t* a, const plast_index_t* b, const plast_hit_t
     if (t < -127 || t > 127) A.rows8 = 0;
   }
 
-  const int bp1 = bits_for(p->max_len1), bp2 = bits_for(p->max_len2);
-  const int b1 = bits_for(a->n_seqs), b2 = bits_for(b->n_seqs);
   hipLaunchKernelGGL(k_align_clear, dim3(1), dim3(64), 0, s, hdr);
   const unsigned nb = (unsigned)((n_hits + 255) / 256);
   int32_t* pcount = (int32_t*)(ws + L.pcount);
   const int64_t wave_slots = (n_hits + 63) / 64;
-  hipLaunchKernelGGL(k_align_count, dim3(nb ? nb : 1), dim3(256), 0, s, A, d_hits, d_pass, n_hits, hdr, pcount,
-                     d_cover);
+  hipLaunchKernelGGL(k_align_count, dim3(nb ? nb : 1), dim3(256), 0, s, A, d_hits, d_gscore, d_pass, n_hits, hdr,
+                     pcount, d_cover);
   exclusive_scan_i32(pcount, wave_slots, &hdr->pass_total, ws + L.scan_tmp, s);
-  hipLaunchKernelGGL(k_align_npass, dim3(1), dim3(64), 0, s, hdr);
-  hipLaunchKernelGGL(k_align_keys, dim3(nb ? nb : 1), dim3(256), 0, s, A, d_hits, d_gscore, d_pass, n_hits, bp1, bp2,
-                     b2, hdr, (const int32_t*)pcount, hidx, klo, khi);
   AlignHeader h0;
   PLAST_HIP(hipMemcpyAsync(&h0, hdr, sizeof(h0), hipMemcpyDeviceToHost, s));
   PLAST_HIP(hipStreamSynchronize(s));
-  const int64_t m = (int64_t)h0.n_pass;
+  const int64_t m = (int64_t)h0.pass_total;
   if (m > 0) {
-    const int64_t tiles = (m + kSortTile - 1) / kSortTile;
-    hipLaunchKernelGGL(k_iota, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, perm[0], hdr);
+    AlignKeys K;
+    K.gmax = h0.gmax;
+    K.bp1 = bits_for(p->max_len1);
+    K.bp2 = bits_for(p->max_len2);
+    K.b2 = bits_for(b->n_seqs);
+    K.lo_bits = bits_for(h0.gmax) + K.bp1 + K.bp2;
+    const int hi_bits = bits_for(a->n_seqs) + K.b2;
+    K.both = K.lo_bits + hi_bits <= 64;
+    hipLaunchKernelGGL(k_align_keys, dim3(nb ? nb : 1), dim3(256), 0, s, A, d_hits, d_gscore, d_pass, n_hits, K, hdr,
+                       (const int32_t*)pcount, key[0], val[0]);
+    // Tiles as small as the histograms' room (for the input hits in tiles of
+    // kSortTile) allows: a tile is one wavefront's serial work, 64 elements at a
+    // time, and over 80,000 passing hits of 800,000 a pass took 84 us in tiles of
+    // 4096 (20 wavefronts) against 16 us in tiles of 512.
+    const int64_t fit = (m + L.tiles - 1) / L.tiles;
+    const int tile = (int)((fit > kSortMin ? fit : kSortMin) + 63) / 64 * 64;
+    const int64_t tiles = (m + tile - 1) / tile;
     int cur = 0;
-    const int lo_bits = 14 + bp1 + bp2, hi_bits = b1 + b2;
-    for (int pass_key = 0; pass_key < 2; ++pass_key) {
-      const uint64_t* key = pass_key == 0 ? klo : khi;
-      const int nbits = pass_key == 0 ? lo_bits : hi_bits;
+    auto sort = [&](int nbits) {
       for (int shift = 0; shift < nbits; shift += 8) {
-        hipLaunchKernelGGL(k_rs_count, dim3((unsigned)tiles), dim3(64), 0, s, perm[cur], key, shift, hdr, counts,
-                           tiles);
+        hipLaunchKernelGGL(k_rs_count, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur], shift, m,
+                           (const int32_t*)nullptr, tile, counts, tiles);
         exclusive_scan_i32(counts, 256 * tiles, &hdr->sort_total, ws + L.scan_tmp, s);
-        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)tiles), dim3(64), 0, s, perm[cur], key, shift, hdr, counts,
-                           tiles, perm[cur ^ 1]);
+        hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur],
+                           (const int32_t*)val[cur], shift, m, (const int32_t*)nullptr, tile, (const int32_t*)counts,
+                           tiles, key[cur ^ 1], val[cur ^ 1]);
         cur ^= 1;
       }
-    }
+    };
     const unsigned mb = (unsigned)((m + 255) / 256);
-    hipLaunchKernelGGL(k_align_head_count, dim3(mb), dim3(256), 0, s, perm[cur], khi, hdr, pcount);
+    if (K.both) {
+      sort(K.lo_bits + hi_bits);
+    } else {
+      sort(K.lo_bits);
+      hipLaunchKernelGGL(k_align_high, dim3(mb), dim3(256), 0, s, d_hits, K, m, (const int32_t*)val[cur], key[cur]);
+      sort(hi_bits);
+    }
+    const int shift = K.both ? K.lo_bits : 0;
+    const uint64_t* skey = key[cur];
+    const int32_t* sval = val[cur];
+    hipLaunchKernelGGL(k_align_head_count, dim3(mb), dim3(256), 0, s, skey, shift, m, pcount);
     exclusive_scan_i32(pcount, (m + 63) / 64, &hdr->group_total, ws + L.scan_tmp, s);
-    hipLaunchKernelGGL(k_align_ngroups, dim3(1), dim3(64), 0, s, hdr);
-    hipLaunchKernelGGL(k_align_heads, dim3(mb), dim3(256), 0, s, perm[cur], khi, hdr, (const int32_t*)pcount, heads);
+    hipLaunchKernelGGL(k_align_heads, dim3(mb), dim3(256), 0, s, A, d_hits, skey, sval, shift, m,
+                       (const int32_t*)pcount, heads, key[cur ^ 1]);
+    hipLaunchKernelGGL(k_rs_count, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1], 0, m,
+                       (const int32_t*)&hdr->group_total, tile, counts, tiles);
+    exclusive_scan_i32(counts, 256 * tiles, &hdr->sort_total, ws + L.scan_tmp, s);
+    hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1],
+                       (const int32_t*)heads, 0, m, (const int32_t*)&hdr->group_total, tile, (const int32_t*)counts,
+                       tiles, (uint64_t*)nullptr, order);
     const size_t lds = align_lds_bytes(p->max_len2);
     PLAST_HIP(hipFuncSetAttribute((const void*)k_align, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int16_t* tbl = (int16_t*)(ws + L.tbl);
     hipLaunchKernelGGL(k_align_table, dim3(1), dim3(64), 0, s, A, tbl);
     timing_mark(kStageAlign, false, s);
-    hipLaunchKernelGGL(k_align, dim3((unsigned)waves), dim3(64), lds, s, A, (const int16_t*)tbl, d_hits, hidx,
-                       perm[cur], khi, heads, hdr, tb, L.tb_words_per_wave, pieces, (int2*)(ws + L.strip), d_out,
-                       d_cover);
+    hipLaunchKernelGGL(k_align, dim3((unsigned)waves), dim3(64), lds, s, A, (const int16_t*)tbl, d_hits, sval,
+                       skey, shift, m, (const int32_t*)order, hdr, tb, L.tb_words_per_wave, pieces,
+                       (int2*)(ws + L.strip), d_out, d_cover);
     timing_mark(kStageAlign, true, s);
     PLAST_HIP(hipGetLastError());
     PLAST_HIP(hipMemcpyAsync(&h0, hdr, sizeof(h0), hipMemcpyDeviceToHost, s));

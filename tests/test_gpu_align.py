@@ -244,3 +244,26 @@ def test_align_long_pair_one_workgroup_per_cu(B):
     F = {k: i for i, k in enumerate(O.ALIGN_FIELDS)}
     long = rec[(rec[:, F["seq1"]] == 0) & (rec[:, F["seq2"]] == 0)]
     assert len(long) >= 1 and (long[:, F["end1"]] - long[:, F["start1"]] > 9000).any()
+
+
+@pytest.mark.parametrize("n,passing,max_len", [(1, 1.0, 40), (300, 1.0, 40), (4097, 1.0, 40), (4097, 1.0, 16384),
+                                               (9000, 0.1, 40), (9000, 0.1, 16384)])
+def test_align_order_of_hits_by_one_key_and_by_two(B, n, passing, max_len):
+    """Hits in random order, of every 14-bit score and several to a pair: the
+    sort's tiles from 512 elements to their largest, and its key in one word (for
+    sequences of at most 40 letters) and in two (of declared 16384)."""
+    rng = np.random.default_rng(n)
+    bank1, bank2 = synth.random_bank(rng, 1100, 20, 40), synth.random_bank(rng, 1030, 20, 40)
+    s1 = rng.integers(0, 1100, n)
+    h = np.stack([s1, rng.integers(0, 20, n), (s1 * 7 + rng.integers(0, 3, n)) % 1030, rng.integers(0, 20, n),
+                  np.zeros(n, np.int64)], axis=1)
+    h = rng.permutation(np.unique(h, axis=0)).astype(np.int32)
+    g = rng.integers(0, 1 << 14, len(h)).astype(np.int32)
+    g[0] = 16383
+    p = (rng.random(len(h)) <= passing).astype(np.uint8)
+    p[0] = 1
+    ia = B.build_index(*B.bank_to_device(bank1, "cuda"))
+    ib = B.build_index(*B.bank_to_device(bank2, "cuda"))
+    dev = [torch.from_numpy(v).cuda() for v in (h, g, p)]
+    _say("align %d random hits, max_len %d" % (len(h), max_len))
+    _assert_parity(B, bank1, bank2, ia, ib, *dev, max_len1=max_len, max_len2=max_len, n_waves=4)
