@@ -52,16 +52,10 @@ SeedClasses seed_classes() {
   // A, C, f, G, i, m, n, P, q, r, t (ids in that order).
   static const char* pos2_g = "GPATSNHQEDRK";
   static const char* pos3[11] = {"A", "C", "FYW", "G", "IV", "ML", "NH", "P", "QED", "RK", "TS"};
-  SeedClasses sc{0u, 0ull, 0ull};
-  for (const char* p = pos2_g; *p; ++p) sc.pos2_g_mask |= 1u << code_of(*p);
+  SeedClasses sc{};
+  for (const char* p = pos2_g; *p; ++p) sc.pos2[code_of(*p) / 4] |= 1u << (8 * (code_of(*p) % 4));
   for (int k = 0; k < 11; ++k)
-    for (const char* p = pos3[k]; *p; ++p) {
-      int c = code_of(*p);
-      if (c < 16)
-        sc.pos3_lo |= (uint64_t)k << (4 * c);
-      else
-        sc.pos3_hi |= (uint64_t)k << (4 * (c - 16));
-    }
+    for (const char* p = pos3[k]; *p; ++p) sc.pos3x20[code_of(*p) / 4] |= (uint32_t)(20 * k) << (8 * (code_of(*p) % 4));
   return sc;
 }
 

@@ -7,20 +7,27 @@
 //
 // The sort is a two-pass LSD radix sort on the 14-bit key: the low 7 bits
 // (128 buckets), then the high 7 bits (69 buckets).  Each pass cuts its input
-// into tiles of kIxTile elements, one wavefront each (four per workgroup): a
-// counting kernel writes the tile's bucket histogram bucket-major, an
-// exclusive scan over (bucket, tile) gives every tile its first slot in each
-// bucket, and a scattering kernel ranks the tile's elements in order within
-// their bucket (one ballot per digit bit over the 64 lanes of a round) into the
-// tile's own bucket order in LDS, then writes the staged tile out bucket by
-// bucket, consecutive lanes on consecutive slots.  Both passes are stable, so
-// the order inside a key is the position order: ascending (sequence,
-// position), independent of scheduling.  Pass 1 reads the codes (staged in
-// LDS) and writes one 64-bit entry per word (position, key, and the sequence
-// as an offset from the first sequence of the position's tile, which the
-// layout check records per tile) and, beside it, the byte of its high digit
-// that pass 2's counting kernel reads; pass 2 writes occ and occ_seq, and
-// key_off follows from the two scanned histograms.
+// into tiles of kIxTile elements, one wavefront each, four to a workgroup: a
+// counting kernel writes the workgroup's bucket histogram bucket-major, an
+// exclusive scan over (bucket, workgroup) gives every workgroup its first slot in
+// each bucket, and a scattering kernel ranks each tile's elements in order within
+// their bucket (see RankLds) into the tile's own bucket order in LDS, then writes
+// the staged tile out bucket by bucket, consecutive lanes on consecutive slots.
+// Both passes are stable, so the order inside a key is the position order:
+// ascending (sequence, position), independent of scheduling.  Pass 1 reads the
+// codes and writes one 64-bit entry per word (position and sequence, from the
+// first sequence of the position's tile, which the layout check records per tile)
+// and, beside it, the byte of its high digit, which is all that pass 2 ranks by;
+// pass 2 writes occ and occ_seq, and key_off follows from the two scanned
+// histograms.
+//
+// 300,000 proteins, some 85M words, between 0.81 GB read and written at least (0.17 ms
+// at the rate of a large copy): 0.80 ms, of which pass 2's scattering 0.34, pass
+// 1's 0.27 and the counting kernels 0.12; 1.36 ms before ranks came from byte
+// tables (scattering 0.50 and 0.49), keys from packed table lookups (counting 0.14)
+// and histograms from workgroups (a column a wavefront: 0.10 more in the two
+// scans and the gathers of the columns).  The scattering kernels are bound by
+// their LDS traffic: half of the accesses fall on random banks.
 #include "plast_internal.h"
 
 namespace plast {
@@ -29,8 +36,9 @@ namespace {
 
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
-constexpr int kIxTile = 2048;                       // elements per tile (32 rounds of 64)
+constexpr int kIxTile = 2048;                       // elements per tile (32 per lane)
 constexpr int kIxWaves = 4;                         // tiles (one per wavefront) per workgroup
+constexpr int kIxGroup = kIxTile * kIxWaves;        // elements per histogram column
 constexpr int kD0Bits = 7;                          // pass-1 digit: key & 127
 constexpr int kD0 = 1 << kD0Bits;
 constexpr int kD1 = (kNKeys + kD0 - 1) >> kD0Bits;  // pass-2 digit: key >> 7, 69 values
@@ -44,6 +52,16 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The tile group of a workgroup: workgroups are dealt to the XCDs round robin, and
+// each XCD takes a contiguous eighth of the tiles.  Neighbouring tiles then write
+// their short runs (16 words of a bucket on average, starting anywhere in a line)
+// and their histogram columns through one L2: 128 and 57 us in the counting
+// kernels instead of 143 and 63 (300,000 proteins).
+__device__ __forceinline__ int64_t xcd_group() {
+  const unsigned nb = gridDim.x, k = blockIdx.x % kMaxQueues;
+  return (int64_t)k * (nb / kMaxQueues) + min(k, nb % kMaxQueues) + blockIdx.x / kMaxQueues;
 }
 
 // Layout check, and the tile table: tile_seq[t] is the sequence holding
@@ -94,162 +112,241 @@ __global__ __launch_bounds__(kLayoutThreads) void k_layout_check_one(const int64
   }
 }
 
-// Loads starts s0 + 1 .. s0 + 64 * K of the sequences (INT64_MAX past the
-// last) into a wavefront's LDS table, one coalesced load per 64.
-template <int K>
-__device__ __forceinline__ void load_starts(const int64_t* __restrict__ seq_start, int32_t n_seqs, int s0,
-                                            int64_t* st, int lane) {
+// ---------------------------------------------------------------- words of a tile
+// A lane works on kPer = 32 consecutive elements of its wavefront's tile, so the
+// stable order inside a bucket is (lane, element of the lane).
+constexpr int kPer = kIxTile / 64;
+static_assert(kPer == 32 && kPadCode < 128, "a lane's residue flags fill one dword; packed compares of codes");
+
+// The kPer + 4 codes from the lane's first position as dwords (separators past n_padded).
+__device__ __forceinline__ void lane_codes(const uint8_t* __restrict__ codes, int64_t beg, int64_t n_padded,
+                                           uint32_t (&w)[kPer / 4 + 1]) {
+  if ((reinterpret_cast<uintptr_t>(codes + beg) & 15) == 0 && beg + kPer + 4 <= n_padded) {
+    const uint4 a = *(const uint4*)(codes + beg), b = *(const uint4*)(codes + beg + 16);
+    w[0] = a.x, w[1] = a.y, w[2] = a.z, w[3] = a.w;
+    w[4] = b.x, w[5] = b.y, w[6] = b.z, w[7] = b.w;
+    w[8] = *(const uint32_t*)(codes + beg + kPer);
+  } else {
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int64_t idx = (int64_t)s0 + 1 + k * 64 + lane;
-    st[k * 64 + lane] = idx < n_seqs ? seq_start[idx] : INT64_MAX;
+    for (int j = 0; j <= kPer / 4; ++j) {
+      w[j] = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        w[j] |= (uint32_t)(beg + 4 * j + k < n_padded ? codes[beg + 4 * j + k] : (uint8_t)kPadCode) << (8 * k);
+    }
   }
 }
 
+// What the words meeting four codes need of them, a byte per code.
+struct CodeBytes {
+  uint32_t letter;  // the code, 0 where it is no residue
+  uint32_t class2;  // class at the seed's second position
+  uint32_t class3;  // 20 x class at its third
+  uint32_t none;    // 128 where the code is no residue
+};
 
-// Lanes of the wavefront holding a valid element with the same 7-bit digit.
-__device__ __forceinline__ uint64_t digit_peers(int d, bool valid) {
-  uint64_t peers = __ballot(valid);
-#pragma unroll
-  for (int b = 0; b < 7; ++b) {
-    const int bit = (d >> b) & 1;
-    const uint64_t m = __ballot(bit);
-    peers &= bit ? m : ~m;
-  }
-  return peers;
+// Bytes of the 20-entry table t at the codes of four bytes; sel, half and top are
+// the codes' bits 0-2, 3 and 4 as byte selectors.
+__device__ __forceinline__ uint32_t lookup20(const uint32_t (&t)[5], uint32_t sel, uint32_t half, uint32_t top) {
+  const uint32_t p0 = __builtin_amdgcn_perm(t[1], t[0], sel), p1 = __builtin_amdgcn_perm(t[3], t[2], sel);
+  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[4], t[4], sel), __builtin_amdgcn_perm(p1, p0, half), top);
 }
 
-// A tile's bucket tables from the scanned histogram (bucket-major over
-// tiles, n_total words in all): gst[d] is the tile's first slot in bucket d,
-// lst[d] the first slot of bucket d in the tile's own bucket order, cur[d] a
-// running copy of lst[d].  Returns the tile's word count.
+// ((w + 108 per byte) | w) has a byte's top bit set iff that byte is >= 20, once
+// the carries out of bytes >= 148 are kept from the next byte.
+__device__ __forceinline__ uint32_t no_residue(uint32_t w) { return (((w & 0x7F7F7F7Fu) + 0x6C6C6C6Cu) | w) & 0x80808080u; }
+__device__ __forceinline__ uint32_t byte_mask(uint32_t top_bits) { return (top_bits << 1) - (top_bits >> 7); }
+
+__device__ __forceinline__ CodeBytes code_bytes(uint32_t w, const SeedClasses& sc) {
+  CodeBytes b;
+  b.none = no_residue(w);
+  b.letter = w & ~byte_mask(b.none);
+  const uint32_t sel = b.letter & 0x07070707u;
+  const uint32_t half = ((b.letter >> 1) & 0x04040404u) | 0x03020100u;
+  const uint32_t top = ((b.letter >> 2) & 0x04040404u) | 0x03020100u;
+  b.class2 = lookup20(sc.pos2, sel, half, top);
+  b.class3 = lookup20(sc.pos3x20, sel, half, top);
+  return b;
+}
+
+// Seed keys of the four words starting in lo's bytes (hi: the next four codes), -1
+// unless all four codes of the word are residues.  A key is ((2 w0 + class2(w1)) *
+// 11 + class3(w2)) * 20 + w3: a byte 2 w0 + class2 <= 39 and a byte 20 class3 + w3
+// <= 219, formed for four words at once.
+__device__ __forceinline__ void word_keys4(const CodeBytes& lo, const CodeBytes& hi, int (&key)[4]) {
+  const uint32_t a = 2 * lo.letter + __builtin_amdgcn_alignbyte(hi.class2, lo.class2, 1);
+  const uint32_t b = __builtin_amdgcn_alignbyte(hi.class3, lo.class3, 2) +
+                     __builtin_amdgcn_alignbyte(hi.letter, lo.letter, 3);
+  const uint32_t none = lo.none | __builtin_amdgcn_alignbyte(hi.none, lo.none, 1) |
+                        __builtin_amdgcn_alignbyte(hi.none, lo.none, 2) |
+                        __builtin_amdgcn_alignbyte(hi.none, lo.none, 3);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int v = (int)__umul24((a >> (8 * k)) & 255u, 220u) + (int)((b >> (8 * k)) & 255u);
+    key[k] = (none >> (8 * k)) & 128u ? -1 : v;
+  }
+}
+
+// ---------------------------------------------------------------- ranks in a tile
+// Stable ranks within ND buckets, of elements held kPer to a lane.  A table in LDS
+// has a byte per (bucket, lane), 16 dwords to a bucket: the element's lane adds 1
+// to its byte with a returning atomic on the dword, which gives the element's rank
+// among the lane's own (a lane's atomics are served in order, and the other bytes
+// of the dword are other lanes'), with no wait between elements.  The bytes of
+// each 8 lanes are then replaced by their exclusive prefix sums (at most 7 x 32),
+// and a 16-bit entry per (bucket, 8 lanes) gets the first slot of those lanes in
+// the tile's bucket order.
+// A ballot per digit bit and a running counter per bucket, 64 elements a round,
+// took some 60 vector instructions and a dependent LDS read and write a round.
 template <int ND>
-__device__ __forceinline__ int tile_tables(const int32_t* __restrict__ offs, int64_t tiles, int64_t tile,
-                                           int64_t n_total, int32_t* gst, int32_t* lst, int32_t* cur, int lane) {
-  int c[2], g[2], incl[2], tot[2];
+struct RankLds {
+  uint32_t count[ND * 16];
+  uint16_t first[ND * 8];
+};
+
+template <int ND>
+__device__ __forceinline__ void rank_clear(RankLds<ND>& r, int lane) {
+  for (int j = lane; j < ND * 4; j += 64) ((uint4*)r.count)[j] = make_uint4(0, 0, 0, 0);
+}
+
+template <int ND>
+__device__ __forceinline__ uint32_t rank_add(RankLds<ND>& r, int d, bool valid, int lane) {
+  const int sh = 8 * (lane & 3);
+  return __builtin_amdgcn_ubfe(atomicAdd(&r.count[d * 16 + (lane >> 2)], valid ? 1u << sh : 0u), sh, 8);
+}
+
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15, 31
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
+// Of bucket lane + 64 h: tot[h] its elements in the tile, lst[h] its first slot in
+// the tile's bucket order.  Returns the tile's elements.
+template <int ND>
+__device__ __forceinline__ int rank_scan(RankLds<ND>& r, uint32_t (&tot)[2], uint32_t (&lst)[2], int lane) {
+  uint4 v[2][4];
+  uint32_t total = 0;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int d = lane + 64 * h;
-    g[h] = 0;
-    c[h] = 0;
-    if (d < ND) {
-      const int64_t idx = (int64_t)d * tiles + tile;
-      g[h] = offs[idx];
-      c[h] = (int)((idx + 1 < (int64_t)ND * tiles ? (int64_t)offs[idx + 1] : n_total) - g[h]);
-    }
-    incl[h] = c[h];
+    const bool on = lane + 64 * h < ND;
+    tot[h] = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl[h], o);
-      if (lane >= o) incl[h] += t;
+    for (int q = 0; q < 4; ++q) {
+      v[h][q] = on ? ((const uint4*)(r.count + (lane + 64 * h) * 16))[q] : make_uint4(0, 0, 0, 0);
+      tot[h] = __builtin_amdgcn_sad_u8(v[h][q].x, 0, tot[h]);
+      tot[h] = __builtin_amdgcn_sad_u8(v[h][q].y, 0, tot[h]);
+      tot[h] = __builtin_amdgcn_sad_u8(v[h][q].z, 0, tot[h]);
+      tot[h] = __builtin_amdgcn_sad_u8(v[h][q].w, 0, tot[h]);
     }
-    tot[h] = __shfl(incl[h], 63);
+    const uint32_t incl = wave_incl_scan(tot[h]);
+    lst[h] = total + incl - tot[h];
+    total += __builtin_amdgcn_readlane(incl, 63);
   }
-  const int l0 = incl[0] - c[0], l1 = tot[0] + incl[1] - c[1];
-  gst[lane] = g[0];
-  gst[lane + 64] = g[1];
-  lst[lane] = cur[lane] = l0;
-  lst[lane + 64] = cur[lane + 64] = l1;
-  return tot[0] + tot[1];
-}
-
-// Stable rank of the round's valid lanes within their digit: writes every
-// valid lane's tile-local slot and advances the digit's running counter.
-__device__ __forceinline__ int rank_in_tile(int d, bool valid, int32_t* cur, uint64_t below) {
-  const uint64_t peers = digit_peers(d, valid);
-  const int start = valid ? cur[d] : 0;
-  wave_sync();
-  const int l = start + __popcll(peers & below);
-  if (valid && (peers & below) == 0) cur[d] = start + __popcll(peers);
-  wave_sync();
-  return l;
-}
-
-// The word arrays between the passes hold one 64-bit entry per word: the
-// position (bits 0-31), the sequence as an offset from the first sequence of
-// the position's pass-1 tile (bits 32-38) and the key (bits 39-52).
-__device__ __forceinline__ uint64_t word_entry(int64_t q, int seq_off, int key) {
-  return (uint64_t)(uint32_t)q | ((uint64_t)seq_off << 32) | ((uint64_t)key << 39);
-}
-
-// Pass 1, scattering.  The tile's codes are staged in LDS; every word, in
-// position order, is ranked within its low digit into the tile's own bucket
-// order in LDS (key | position offset << 14 | sequence offset << 25), and the
-// staged words are then written out bucket by bucket, consecutive lanes to
-// consecutive slots.  Runs only on a valid layout (the tile table is complete,
-// a tile meets at most 103 sequence starts and the words fit the word array).
-constexpr int kTileStarts = 2;  // 128 starts
-static_assert(kIxTile == 2048, "word staging packs a position offset in 11 bits");
-
-// A tile's codes [beg, beg + kIxTile + 64) into LDS as dwords (separators past
-// n_padded), with dword loads when the codes are 4-byte aligned.
-__device__ __forceinline__ void stage_codes(const uint8_t* __restrict__ codes, int64_t beg, int64_t n_padded,
-                                            uint32_t* cl32, int lane) {
-  const int nb = (int)max(min(n_padded - beg, (int64_t)(kIxTile + 64)), (int64_t)0);  // code bytes in range
-  const bool aligned = (reinterpret_cast<uintptr_t>(codes) & 3) == 0;
 #pragma unroll
-  for (int r = 0; r < ((kIxTile + 64) / 4 + 63) / 64; ++r) {
-    const int j = r * 64 + lane;
-    if (j < (kIxTile + 64) / 4) {
-      const int o = 4 * j;
-      uint32_t v;
-      if (aligned && o + 4 <= nb) {
-        v = *(const uint32_t*)(codes + beg + o);
-      } else {
-        v = 0;
+  for (int h = 0; h < 2; ++h) {
+    uint32_t run = lst[h], packed[4];
+    auto eight = [&](uint32_t& x0, uint32_t& x1) {  // returns the first slot of the eight lanes
+      uint32_t t0 = x0 + (x0 << 8), t1 = x1 + (x1 << 8);
+      t0 += t0 << 16;
+      t1 += t1 << 16;
+      const uint32_t first = run;
+      run += (t0 >> 24) + (t1 >> 24);
+      x1 = t1 - x1 + __builtin_amdgcn_perm(t0, t0, 0x03030303u);
+      x0 = t0 - x0;
+      return first;
+    };
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v |= (uint32_t)(o + k < nb ? codes[beg + o + k] : (uint8_t)kPadCode) << (8 * k);
-      }
-      cl32[j] = v;
+    for (int q = 0; q < 4; ++q) {
+      packed[q] = eight(v[h][q].x, v[h][q].y);
+      packed[q] |= eight(v[h][q].z, v[h][q].w) << 16;
+    }
+    if (lane + 64 * h < ND) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) ((uint4*)(r.count + (lane + 64 * h) * 16))[q] = v[h][q];
+      *(uint4*)(r.first + (lane + 64 * h) * 8) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
     }
   }
+  return (int)total;
 }
 
-// Seed key of the word whose four codes are the bytes of w, or -1 unless all
-// four are residues (< 20).  ((w + 108 per byte) | w) has a byte's top bit set
-// iff that byte is >= 20; a carry out of a byte comes only from a byte >= 148,
-// which has its own top bit set.
-__device__ __forceinline__ int word_key4(uint32_t w, const SeedClasses& sc) {
-  if (((w + 0x6C6C6C6Cu) | w) & 0x80808080u) return -1;
-  return seed_key_dev(sc, (int)(w & 0xffu), (int)((w >> 8) & 0xffu), (int)((w >> 16) & 0xffu), (int)(w >> 24));
+template <int ND>
+__device__ __forceinline__ uint32_t rank_slot(const RankLds<ND>& r, int d, uint32_t own, int lane) {
+  return r.first[d * 8 + (lane >> 3)] + ((const uint8_t*)r.count)[d * 64 + lane] + own;
 }
 
-// Seed key of the word starting at byte off of the staged codes (-1 unless all
-// four codes are residues): two aligned dword reads and a funnel shift.
-__device__ __forceinline__ int word_key_at(const uint32_t* cl32, int off, const SeedClasses& sc) {
-  return word_key4(__builtin_amdgcn_alignbyte(cl32[(off >> 2) + 1], cl32[off >> 2], (uint32_t)(off & 3)), sc);
+// The scanned histogram has a column per workgroup: goff[h] is its first global slot
+// in bucket lane + 64 h.  Wavefront wv's tile follows those before it, whose counts
+// tot_all holds; delta[d] is what added to a slot of bucket d in the tile's own
+// order gives the global slot.  Contains a barrier.
+template <int ND>
+__device__ __forceinline__ void load_column(const int32_t* __restrict__ offs, int64_t groups, int64_t group,
+                                            int32_t (&goff)[2], int lane) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) goff[h] = lane + 64 * h < ND ? offs[(int64_t)(lane + 64 * h) * groups + group] : 0;
+}
+
+template <int ND>
+__device__ __forceinline__ void tile_delta(const int32_t (&goff)[2], const uint32_t (&tot)[2], const uint32_t (&lst)[2],
+                                           uint16_t (&tot_all)[kIxWaves][2 * 64], int32_t* delta, int wv, int lane) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) tot_all[wv][lane + 64 * h] = (uint16_t)tot[h];
+  __syncthreads();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    int32_t g = goff[h] - (int32_t)lst[h];
+#pragma unroll
+    for (int k = 0; k < kIxWaves - 1; ++k) g += k < wv ? (int)tot_all[k][lane + 64 * h] : 0;
+    if (lane + 64 * h < ND) delta[lane + 64 * h] = g;
+  }
+  wave_sync();
+}
+
+// A workgroup's histogram column from its wavefronts' counts.  Contains a barrier.
+template <int ND>
+__device__ __forceinline__ void store_column(const int32_t (&cnt)[kIxWaves][kD0], int32_t* __restrict__ hist,
+                                             int64_t groups, int64_t group) {
+  __syncthreads();
+  const int d = threadIdx.x;
+  if (d >= ND || group >= groups) return;
+  int32_t v = 0;
+#pragma unroll
+  for (int k = 0; k < kIxWaves; ++k) v += cnt[k][d];
+  hist[(int64_t)d * groups + group] = v;
 }
 
 // Pass 1, counting, fused with the validation of the bank and the writing of
-// the scan codes: one wavefront per tile of kIxTile positions (tiles past the
-// bank write the scan codes' tail slack only).  The tile's codes (and the 64
-// after it) are staged in LDS once.  Validation: position p is a residue iff
-// some sequence s has seq_start[s] <= p < seq_start[s + 1] - kPadLen; residues
-// must be < 20 and every other position below n_padded the separator.  The
-// residue positions of the tile come as a bitmap: the state at the tile's first
-// position, toggled at every sequence start and every residue end inside the
-// tile (a sequence with no residue toggles twice at one position), resolved by
-// a prefix xor within each lane's 32 positions and a prefix parity across the
-// lanes.  The scan codes are the validated codes times kScale.  The histogram
-// counts the low digit of the key of every word starting in the tile, from the
-// raw codes, as the scattering pass does (four word starts per lane and round):
-// on a valid bank a word of four codes < 20 lies inside one sequence.  After a
-// layout error nothing is validated or written but the histogram.
+// the scan codes: one wavefront per tile of kIxTile positions, kPer of them a lane
+// (tiles past the bank write the scan codes' tail slack only).  Validation:
+// position p is a residue iff some sequence s has seq_start[s] <= p <
+// seq_start[s + 1] - kPadLen; residues must be < 20 and every other position
+// below n_padded the separator.  The residue positions of the tile come as a
+// bitmap, a dword per lane: the state at the tile's first position, toggled at
+// every sequence start and every residue end inside the tile (a sequence with no
+// residue toggles twice at one position), resolved by a prefix xor within each
+// lane's 32 positions and a prefix parity across the lanes.  The scan codes are
+// the validated codes times kScale.  The histogram counts the low digit of the key
+// of every word starting in the tile, from the raw codes, as the scattering pass
+// does: on a valid bank a word of four codes < 20 lies inside one sequence.  After
+// a layout error nothing is validated or written but the histogram.
 __global__ __launch_bounds__(64 * kIxWaves) void k_ix_check_count1(
     const uint8_t* __restrict__ codes, const int64_t* __restrict__ seq_start, int32_t n_seqs, int64_t n_padded,
     const int32_t* __restrict__ tile_seq, int64_t tiles, uint8_t* __restrict__ scan, int64_t scan_len, SeedClasses sc,
-    int32_t* __restrict__ hist, int32_t* __restrict__ err) {
+    int32_t* __restrict__ hist, int64_t groups, int32_t* __restrict__ err) {
   __shared__ int32_t cnt_all[kIxWaves][kD0];
   __shared__ uint32_t rb_all[kIxWaves][kIxTile / 32];
-  __shared__ uint32_t cl_all[kIxWaves][(kIxTile + 64) / 4];
   const int lane = lane_id(), wv = threadIdx.x >> 6;
-  const int64_t tile = (int64_t)blockIdx.x * kIxWaves + wv;
+  const int64_t group = xcd_group(), tile = group * kIxWaves + wv;
   const int64_t beg = tile * kIxTile;
-  if (tile >= tiles && beg >= scan_len) return;
   int32_t* cnt = cnt_all[wv];
   uint32_t* rb = rb_all[wv];
-  uint32_t* cl32 = cl_all[wv];
-  stage_codes(codes, beg, n_padded, cl32, lane);
+  const int64_t lane_beg = beg + kPer * lane;
+  uint32_t w[kPer / 4 + 1];
+  lane_codes(codes, lane_beg, n_padded, w);
   cnt[lane] = 0;
   cnt[lane + 64] = 0;
   rb[lane] = 0;
@@ -278,284 +375,269 @@ __global__ __launch_bounds__(64 * kIxWaves) void k_ix_check_count1(
       }
     }
     wave_sync();
-    {
-      const uint32_t tog = rb[lane];
-      uint32_t x = tog;
-      x ^= x << 1;
-      x ^= x << 2;
-      x ^= x << 4;
-      x ^= x << 8;
-      x ^= x << 16;
-      const uint64_t odd = __ballot(__popc(tog) & 1);
-      const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-      const bool flip = ((__popcll(odd & below) & 1) != 0) != init;
-      rb[lane] = flip ? ~x : x;
-    }
-    wave_sync();
-    bool bad = false;
-    const int64_t vend = min(beg + kIxTile, scan_len);
-    // 256 positions per round, four consecutive ones per lane (scan is
-    // 256-byte aligned and scan_len a multiple of 256: one dword per lane)
-    for (int64_t base = beg; base < vend; base += 256) {
-      const int off = (int)(base - beg) + 4 * lane;
-      const uint32_t raw = cl32[off >> 2];
-      const uint32_t res = (rb[off >> 5] >> (off & 31)) & 15u;
-      uint32_t out = 0;
+    const uint32_t tog = rb[lane];
+    uint32_t x = tog;
+    x ^= x << 1;
+    x ^= x << 2;
+    x ^= x << 4;
+    x ^= x << 8;
+    x ^= x << 16;
+    const uint64_t odd = __ballot(__popc(tog) & 1);
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+    const bool flip = ((__popcll(odd & below) & 1) != 0) != init;
+    const uint32_t residues = flip ? ~x : x;
+    uint32_t bad = 0, out[kPer / 4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        uint32_t c = kPadCode;
-        if (beg + off + k < n_padded) {
-          const bool residue = (res >> k) & 1u;
-          c = (raw >> (8 * k)) & 0xffu;
-          bad |= residue ? (c >= 20) : (c != kPadCode);
-          if (!(residue && c < 20)) c = kPadCode;
-        }
-        out |= (c * kScale) << (8 * k);
-      }
-      *(uint32_t*)(scan + beg + off) = out;
+    for (int j = 0; j < kPer / 4; ++j) {
+      // the four flags as byte masks
+      const uint32_t res = byte_mask((__umul24((residues >> (4 * j)) & 15u, 0x204081u) << 7) & 0x80808080u);
+      const uint32_t none = no_residue(w[j]);
+      bad |= ((w[j] ^ (0x01010101u * kPadCode)) & ~res) | (none & res);
+      const uint32_t keep = res & ~byte_mask(none);
+      out[j] = ((w[j] & keep) | ((0x01010101u * kPadCode) & ~keep)) * kScale;
     }
-    if (bad) atomicOr(err, 2);
+    // scan is 256-byte aligned and scan_len a multiple of 256
+    if (lane_beg < scan_len) {
+      uint4* dst = (uint4*)(scan + lane_beg);
+      dst[0] = make_uint4(out[0], out[1], out[2], out[3]);
+      dst[1] = make_uint4(out[4], out[5], out[6], out[7]);
+    }
+    if (__ballot(bad != 0) != 0 && lane == 0) atomicOr(err, 2);
   }
-  if (tile >= tiles) return;
-  const int nw = (int)(min(beg + kIxTile, n_padded - (kSeed - 1)) - beg);  // word starts [beg, beg + nw)
-#pragma unroll 2
-  for (int r = 0; r < kIxTile / 256; ++r) {
-    const int o = r * 256 + 4 * lane;
-    if (o < nw) {
-      const uint32_t lo = cl32[o >> 2], hi = cl32[(o >> 2) + 1];
+  CodeBytes lo = code_bytes(w[0], sc);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int key = word_key4(__builtin_amdgcn_alignbyte(hi, lo, k), sc);
-        if (o + k < nw && key >= 0) atomicAdd(&cnt[key & (kD0 - 1)], 1);
-      }
-    }
+  for (int j = 0; j < kPer / 4; ++j) {
+    const CodeBytes hi = code_bytes(w[j + 1], sc);
+    int key[4];
+    word_keys4(lo, hi, key);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (key[k] >= 0) atomicAdd(&cnt[key[k] & (kD0 - 1)], 1);
+    lo = hi;
   }
-  wave_sync();
-  hist[(int64_t)lane * tiles + tile] = cnt[lane];
-  hist[(int64_t)(lane + 64) * tiles + tile] = cnt[lane + 64];
+  store_column<kD0>(cnt_all, hist, groups, group);
 }
+
+// Pass 1, scattering: the tile's words, ranked within their low digit, are put in
+// the tile's own bucket order in LDS (key | position offset << 14 | sequence offset
+// << 25) and written out from there bucket by bucket, consecutive lanes to
+// consecutive slots: the position and sequence as one 64-bit entry, the high digit
+// beside it.  Runs only on a valid layout (the tile table is complete, a tile meets
+// at most 103 sequence starts and the words fit the word array).
+// 300,000 proteins, some 85M words: 272 us, 490 us when ranked by ballots (75% of the
+// vector issue rate).
+static_assert(kIxTile == 2048, "word staging packs a position offset in 11 bits");
 
 __global__ __launch_bounds__(64 * kIxWaves) void k_ix_scatter1(
     const uint8_t* __restrict__ codes, const int64_t* __restrict__ seq_start, int32_t n_seqs, int64_t n_padded,
-    int64_t tiles, SeedClasses sc, const int32_t* __restrict__ tile_seq, const int32_t* __restrict__ err,
-    const int32_t* __restrict__ offs, int64_t cap, uint64_t* __restrict__ words, uint8_t* __restrict__ digits) {
-  __shared__ int32_t gst_all[kIxWaves][kD0], lst_all[kIxWaves][kD0], cur_all[kIxWaves][kD0];
-  __shared__ int64_t st_all[kIxWaves][64 * kTileStarts];
-  __shared__ uint32_t stage_all[kIxWaves][kIxTile];
-  __shared__ uint32_t cl_all[kIxWaves][(kIxTile + 64) / 4];
-  __shared__ uint32_t sbits_all[kIxWaves][kIxTile / 32], spre_all[kIxWaves][kIxTile / 32];
+    int64_t tiles, int64_t groups, SeedClasses sc, const int32_t* __restrict__ tile_seq,
+    const int32_t* __restrict__ err, const int32_t* __restrict__ offs, int64_t cap, uint2* __restrict__ words, uint8_t* __restrict__ digits) {
+  union Lds {  // the ranks' table is read before the stage is written
+    RankLds<kD0> rank;
+    uint32_t stage[kIxTile];
+  };
+  __shared__ __align__(16) Lds lds_all[kIxWaves];
+  __shared__ int32_t delta_all[kIxWaves][kD0];
+  __shared__ uint32_t sbits_all[kIxWaves][64];
+  __shared__ uint16_t tot_all[kIxWaves][2 * 64];
   const int lane = lane_id(), wv = threadIdx.x >> 6;
-  const int64_t tile = (int64_t)blockIdx.x * kIxWaves + wv;
-  if (tile >= tiles || n_seqs == 0 || (*err & 1)) return;
-  int32_t *gst = gst_all[wv], *lst = lst_all[wv], *cur = cur_all[wv];
-  int64_t* st = st_all[wv];
-  uint32_t* stage = stage_all[wv];
-  uint32_t* cl32 = cl_all[wv];
-  uint32_t *sbits = sbits_all[wv], *spre = spre_all[wv];
+  const int64_t group = xcd_group(), tile = group * kIxWaves + wv;
+  if (n_seqs == 0 || (*err & 1)) return;  // (a tile past the last holds no word)
+  RankLds<kD0>& rank = lds_all[wv].rank;
+  uint32_t* stage = lds_all[wv].stage;
+  int32_t* delta = delta_all[wv];
+  uint32_t* sbits = sbits_all[wv];
   const int64_t beg = tile * kIxTile;
-  const int64_t end = min(beg + kIxTile, n_padded - (kSeed - 1));  // word starts [beg, end)
-  stage_codes(codes, beg, n_padded, cl32, lane);
-  const int s0 = min(max(tile_seq[tile], 0), n_seqs - 1);
-  load_starts<kTileStarts>(seq_start, n_seqs, s0, st, lane);
+  uint32_t w[kPer / 4 + 1];
+  lane_codes(codes, beg + kPer * lane, n_padded, w);
+  int32_t goff[2];
+  load_column<kD0>(offs, groups, group, goff, lane);
+  const int s0 = min(max(tile_seq[min(tile, tiles - 1)], 0), n_seqs - 1);
+  // The sequence starts s0 + 1 .. s0 + 128 inside the tile as a bitmap, a dword per
+  // lane: a position's sequence is s0 + the starts at or before it.
   sbits[lane] = 0;
-  const int nt = tile_tables<kD0>(offs, tiles, tile, (int64_t)err[1], gst, lst, cur, lane);
+  rank_clear(rank, lane);
   wave_sync();
-  // The sequence of a position, s0 + the number of sequence starts in the tile
-  // at or before it: a bitmap of the starts (one 32-bit word per lane; at most
-  // 103 starts fall in a tile, all after its first position) and the count of
-  // starts before each word.
 #pragma unroll
-  for (int k = 0; k < kTileStarts; ++k) {
-    const int64_t o = st[k * 64 + lane] - beg;
+  for (int k = 0; k < 2; ++k) {
+    const int64_t idx = (int64_t)s0 + 1 + k * 64 + lane;
+    const int64_t o = (idx < n_seqs ? seq_start[idx] : INT64_MAX) - beg;
     if (o > 0 && o < kIxTile) atomicOr(&sbits[o >> 5], 1u << (o & 31));
   }
   wave_sync();
+  const uint32_t starts = sbits[lane];
+  int seq = (int)wave_incl_scan(__popc(starts)) - __popc(starts);
+  uint32_t e[kPer], own[kPer];
   {
-    const uint32_t b = sbits[lane];
-    int incl = __popc(b);
+    CodeBytes lo = code_bytes(w[0], sc);
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    spre[lane] = (uint32_t)(incl - __popc(b));
-  }
-  wave_sync();
-  auto seq_at = [&](int off) {  // off = position - beg, in [0, kIxTile)
-    const int w = off >> 5;
-    return s0 + (int)spre[w] + __popc(sbits[w] & (~0u >> (31 - (off & 31))));
-  };
-  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  auto entry = [&](int key, int off, int s) {
-    return (uint32_t)key | ((uint32_t)(off + lane) << 14) | ((uint32_t)min(s - s0, 127) << 25);
-  };
-  if (nt <= kIxTile / 2) {
-    // Sparse tile (translated fragments: most positions are separators): the
-    // words are first compacted in position order into the upper half of the
-    // stage, then ranked from there into the lower half, ceil(nt / 64) rounds
-    // instead of one per 64 positions; the halves do not overlap.
-    // Four consecutive word starts per lane and round (two aligned dword reads);
-    // a word's place is the valid words of the lanes below plus those of its
-    // own lane before it, and its sequence the bitmap count at its position
-    // (the four positions share one 32-bit word of the bitmap).
-    uint32_t* comp = stage + kIxTile / 2;
-    int nw = 0;
-    const int nwp = (int)(end - beg);  // word starts in the tile (none if <= 0)
-    for (int o0 = 0; o0 < nwp; o0 += 256) {
-      const int o = o0 + 4 * lane;
-      const uint32_t lo = cl32[o >> 2], hi = cl32[(o >> 2) + 1];
+    for (int j = 0; j < kPer / 4; ++j) {
+      const CodeBytes hi = code_bytes(w[j + 1], sc);
       int key[4];
-      uint64_t bal[4];
-      int before = 0;
+      word_keys4(lo, hi, key);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        key[k] = o + k < nwp ? word_key4(__builtin_amdgcn_alignbyte(hi, lo, (uint32_t)k), sc) : -1;
-        bal[k] = __ballot(key[k] >= 0);
-        before += __popcll(bal[k] & below);
+        const int i = 4 * j + k;
+        seq += (int)((starts >> i) & 1u);
+        own[i] = rank_add(rank, key[k] & (kD0 - 1), key[k] >= 0, lane);
+        e[i] = key[k] < 0 ? ~0u  // no key is 16383
+                          : (uint32_t)key[k] | ((uint32_t)(kPer * lane + i) << 14) | ((uint32_t)min(seq, 127) << 25);
       }
-      const uint32_t sb = sbits[o >> 5];
-      const int sp = s0 + (int)spre[o >> 5];
-      int at = nw + before;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (key[k] >= 0) {
-          const int s = sp + __popc(sb & (~0u >> (31 - ((o + k) & 31))));
-          if (at < kIxTile / 2)
-            comp[at] = (uint32_t)key[k] | ((uint32_t)(o + k) << 14) | ((uint32_t)min(s - s0, 127) << 25);
-          ++at;
-        }
-      }
-      nw += __popcll(bal[0]) + __popcll(bal[1]) + __popcll(bal[2]) + __popcll(bal[3]);
-    }
-    wave_sync();
-    nw = min(nw, kIxTile / 2);
-    for (int c = 0; c < nw; c += 64) {
-      const bool valid = c + lane < nw;
-      const uint32_t e = valid ? comp[c + lane] : 0u;
-      const int l = rank_in_tile((int)(e & (kD0 - 1)), valid, cur, below);
-      if (valid && (unsigned)l < (unsigned)(kIxTile / 2)) stage[l] = e;
-    }
-  } else {
-    for (int off = 0; beg + off < end; off += 64) {
-      const int64_t q = beg + off + lane;
-      const int key = q < end ? word_key_at(cl32, off + lane, sc) : -1;
-      const int l = rank_in_tile(key & (kD0 - 1), key >= 0, cur, below);
-      if (key >= 0 && (unsigned)l < (unsigned)kIxTile) stage[l] = entry(key, off, seq_at(off + lane));
+      lo = hi;
     }
   }
   wave_sync();
+  uint32_t tot[2], lst[2];
+  const int nt = rank_scan(rank, tot, lst, lane);
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) own[i] = rank_slot(rank, (int)(e[i] & (kD0 - 1)), own[i], lane);
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i)
+    if (e[i] != ~0u && own[i] < (uint32_t)kIxTile) stage[own[i]] = e[i];
+  tile_delta<kD0>(goff, tot, lst, tot_all, delta, wv, lane);
+#pragma unroll 4
   for (int l = lane; l < min(nt, kIxTile); l += 64) {
-    const uint32_t e = stage[l];
-    const int key = (int)(e & 0x3fffu);
-    const int d = key & (kD0 - 1);
-    const int64_t slot = (int64_t)gst[d] + (l - lst[d]);
+    const uint32_t v = stage[l];
+    const int key = (int)(v & 0x3fffu);
+    const int64_t slot = (int64_t)delta[key & (kD0 - 1)] + l;
     if (slot >= 0 && slot < cap) {
-      words[slot] = word_entry(beg + ((e >> 14) & 2047u), (int)(e >> 25), key);
+      words[slot] = make_uint2((uint32_t)beg + ((v >> 14) & 2047u), (uint32_t)s0 + (v >> 25));
       digits[slot] = (uint8_t)min(key >> kD0Bits, kD1 - 1);
     }
   }
 }
 
-// Pass 2, counting: histogram of the high digit over the tile's words, read
-// from the byte per word that pass 1 writes beside each entry (four per lane
-// and round; the array is 256-byte aligned and padded, so a dword that
-// straddles the end stays inside it).
+// Pass 2, counting: histogram of the high digit over the words of a workgroup's
+// tiles, read from the byte per word that pass 1 writes beside each entry (the array
+// is 256-byte aligned and padded, so 16 bytes that straddle the end stay inside it).
 __global__ __launch_bounds__(64 * kIxWaves) void k_ix_count2(const uint8_t* __restrict__ digits,
                                                             const int32_t* __restrict__ err, int64_t cap,
-                                                            int64_t tiles, int32_t* __restrict__ hist) {
+                                                            int64_t groups, int32_t* __restrict__ hist) {
   __shared__ int32_t cnt_all[kIxWaves][kD0];
-  const int lane = lane_id();
-  const int64_t tile = (int64_t)blockIdx.x * kIxWaves + (threadIdx.x >> 6);
-  if (tile >= tiles || (*err & 1)) return;
-  int32_t* cnt = cnt_all[threadIdx.x >> 6];
+  const int lane = lane_id(), wv = threadIdx.x >> 6;
+  const int64_t group = xcd_group();
+  if (*err & 1) return;
+  int32_t* cnt = cnt_all[wv];
   cnt[lane] = 0;
   cnt[lane + 64] = 0;
   wave_sync();
   const int64_t n = min((int64_t)err[1], cap);
-  const int64_t beg = tile * kIxTile;
-  const int64_t end = min(beg + kIxTile, n);
-  for (int64_t i = beg + 4 * lane; i < end; i += 256) {
-    const uint32_t d4 = *(const uint32_t*)(digits + i);
+  const int64_t beg = group * kIxGroup + wv * kIxTile;
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (i + k < end) atomicAdd(&cnt[min((int)((d4 >> (8 * k)) & 0xffu), kD1 - 1)], 1);
+  for (int r = 0; r < kIxTile / 1024; ++r) {
+    const int64_t i = beg + r * 1024 + 16 * lane;
+    if (i < n) {
+      const uint4 v = *(const uint4*)(digits + i);
+      const uint32_t d4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (i + k < n) atomicAdd(&cnt[min((int)((d4[k >> 2] >> (8 * (k & 3))) & 0xffu), kD1 - 1)], 1);
+    }
   }
-  wave_sync();
-  if (lane < kD1) hist[(int64_t)lane * tiles + tile] = cnt[lane];
-  if (lane + 64 < kD1) hist[(int64_t)(lane + 64) * tiles + tile] = cnt[lane + 64];
+  store_column<kD1>(cnt_all, hist, groups, group);
 }
 
-// Pass 2, scattering: the tile's words ranked within their high digit into
-// the tile's bucket order in LDS, eight rounds of loads in flight ahead of
-// the ranking, then written out bucket by bucket as occ and occ_seq, eight
-// slots per lane at a time.
-constexpr int kBatch = 8;
-
-__global__ __launch_bounds__(64 * kIxWaves) void k_ix_scatter2(
-    const uint64_t* __restrict__ words, const int32_t* __restrict__ tile_seq, int64_t tiles1,
-    const int32_t* __restrict__ err, int64_t cap, int64_t tiles, const int32_t* __restrict__ offs, int32_t* __restrict__ occ,
-    int32_t* __restrict__ occ_seq) {
-  __shared__ int32_t gst_all[kIxWaves][kD0], lst_all[kIxWaves][kD0], cur_all[kIxWaves][kD0];
-  __shared__ uint64_t stage_all[kIxWaves][kIxTile];
+// Pass 2, scattering: a lane ranks the words of its 32 digits; the slots go back
+// through LDS to the lanes that read the words, consecutive lanes consecutive
+// words, which put them in the tile's bucket order in LDS, to be written out as occ
+// and occ_seq.  some 85M words: 342 us, 499 us when ranked by ballots; positions and
+// sequences staged one after the other in half the LDS: 395 us.
+__global__ __launch_bounds__(64 * kIxWaves) void k_ix_scatter2(const uint2* __restrict__ words,
+                                                               const uint8_t* __restrict__ digits,
+                                                               const int32_t* __restrict__ err, int64_t cap,
+                                                               int64_t groups, const int32_t* __restrict__ offs,
+                                                               int32_t* __restrict__ occ,
+                                                               int32_t* __restrict__ occ_seq) {
+  union Lds {  // each is read before the next one is written
+    RankLds<kD1> rank;
+    uint16_t slot[kIxTile];
+    uint2 stage[kIxTile];
+  };
+  __shared__ __align__(16) Lds lds_all[kIxWaves];
+  __shared__ uint8_t dig_all[kIxWaves][kIxTile];  // digits in bucket order
+  __shared__ int32_t delta_all[kIxWaves][kD1];
+  __shared__ uint16_t tot_all[kIxWaves][2 * 64];
   const int lane = lane_id(), wv = threadIdx.x >> 6;
-  const int64_t tile = (int64_t)blockIdx.x * kIxWaves + wv;
-  if (tile >= tiles || (*err & 1)) return;
-  int32_t *gst = gst_all[wv], *lst = lst_all[wv], *cur = cur_all[wv];
-  uint64_t* stage = stage_all[wv];
+  const int64_t group = xcd_group();
+  RankLds<kD1>& rank = lds_all[wv].rank;
+  uint2* stage = lds_all[wv].stage;
+  uint8_t* dig = dig_all[wv];
+  int32_t* delta = delta_all[wv];
   const int64_t n = min((int64_t)err[1], cap);
-  const int64_t beg = tile * kIxTile;
-  const int64_t end = min(beg + kIxTile, n);
-  const int nt = tile_tables<kD1>(offs, tiles, tile, n, gst, lst, cur, lane);
-  wave_sync();
-  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  uint64_t e_cur[kBatch], e_nxt[kBatch];
-#pragma unroll
-  for (int k = 0; k < kBatch; ++k) {
-    const int64_t i = beg + k * 64 + lane;
-    e_cur[k] = i < end ? words[i] : 0;
+  if ((*err & 1) || group * kIxGroup >= n) return;
+  const int64_t beg = group * kIxGroup + wv * kIxTile;
+  const int nw = (int)max(min((int64_t)kIxTile, n - beg), (int64_t)0);  // the tile's words
+  int32_t goff[2];
+  load_column<kD1>(offs, groups, group, goff, lane);
+  // Elements past the last word take the last digit and so the slots past it.
+  const int mine = nw - kPer * lane;  // words of the lane
+  uint32_t d4[kPer / 4];
+  {
+    uint4 a = make_uint4(~0u, ~0u, ~0u, ~0u), b = a;
+    if (mine > 0) {  // the array's end is a multiple of 256 past its start
+      a = *(const uint4*)(digits + beg + kPer * lane);
+      b = *(const uint4*)(digits + beg + kPer * lane + 16);
+    }
+    d4[0] = a.x, d4[1] = a.y, d4[2] = a.z, d4[3] = a.w;
+    d4[4] = b.x, d4[5] = b.y, d4[6] = b.z, d4[7] = b.w;
   }
-  for (int64_t b0 = beg; b0 < end; b0 += 64 * kBatch) {
+  uint2 e[kPer];
+  if (nw == kIxTile) {
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int64_t i = b0 + (kBatch + k) * 64 + lane;
-      e_nxt[k] = i < end ? words[i] : 0;
+    for (int i = 0; i < kPer; ++i) e[i] = words[beg + i * 64 + lane];
+  } else {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) e[i] = words[min(beg + i * 64 + lane, n - 1)];
+#pragma unroll
+    for (int j = 0; j < kPer / 4; ++j) {
+      const int past = min(max(4 * (j + 1) - mine, 0), 4);  // bytes of the dword past the last word
+      d4[j] |= past ? ~0u << (32 - 8 * past) : 0u;
     }
+  }
+  rank_clear(rank, lane);
+  wave_sync();
+  auto digit = [&](int i) { return min((int)__builtin_amdgcn_ubfe(d4[i >> 2], 8 * (i & 3), 8), kD1 - 1); };
+  uint32_t slot[kPer / 2];  // 16 bits each
+  {
+    uint32_t own[kPer];
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const bool valid = b0 + k * 64 + lane < end;
-      const int l = rank_in_tile(min((int)(e_cur[k] >> (39 + kD0Bits)), kD1 - 1), valid, cur, below);
-      if (valid && (unsigned)l < (unsigned)kIxTile) stage[l] = e_cur[k];
+    for (int i = 0; i < kPer; ++i) own[i] = rank_add(rank, digit(i), true, lane);
+    wave_sync();
+    uint32_t tot[2], lst[2];
+    rank_scan(rank, tot, lst, lane);
+    const int past = kIxTile - nw;  // elements past the last word, counted with the last digit
+    if (lane == (kD1 - 1) % 64) tot[(kD1 - 1) / 64] -= past;
+    tile_delta<kD1>(goff, tot, lst, tot_all, delta, wv, lane);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const uint32_t at = min(rank_slot(rank, digit(i), own[i], lane), (uint32_t)kIxTile - 1);
+      dig[at] = (uint8_t)digit(i);
+      slot[i / 2] = i & 1 ? slot[i / 2] | (at << 16) : at;
     }
-#pragma unroll
-    for (int k = 0; k < kBatch; ++k) e_cur[k] = e_nxt[k];
   }
   wave_sync();
-  // eight slots per lane at a time, so that their tile-table loads are in
-  // flight together
-  const int nl = min(nt, kIxTile);
-  for (int l0 = 0; l0 < nl; l0 += 64 * kBatch) {
-    uint64_t e[kBatch];
-    int32_t ts[kBatch];
+  uint4* dst = (uint4*)(lds_all[wv].slot + kPer * lane);
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int l = l0 + k * 64 + lane;
-      e[k] = l < nl ? stage[l] : 0;
-    }
+  for (int q = 0; q < kPer / 8; ++q)
+    dst[q] = make_uint4(slot[4 * q], slot[4 * q + 1], slot[4 * q + 2], slot[4 * q + 3]);
+  wave_sync();
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const uint32_t t1 = (uint32_t)e[k] >> 11;
-      ts[k] = (int64_t)t1 < tiles1 ? tile_seq[t1] : -1;
-    }
+  for (int i = 0; i < kPer; i += 2)
+    slot[i / 2] = lds_all[wv].slot[i * 64 + lane] | ((uint32_t)lds_all[wv].slot[i * 64 + 64 + lane] << 16);
+  auto slot_of = [&](int i) { return (slot[i / 2] >> (16 * (i & 1))) & 0xffffu; };
+  wave_sync();
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) {
-      const int l = l0 + k * 64 + lane;
-      if (l >= nl) continue;
-      const int key = (int)(e[k] >> 39);
-      const int d = min(key >> kD0Bits, kD1 - 1);
-      const int64_t slot = (int64_t)gst[d] + (l - lst[d]);
-      if (slot < 0 || slot >= n) continue;
-      occ[slot] = (int32_t)(uint32_t)e[k];
-      occ_seq[slot] = ts[k] >= 0 ? ts[k] + (int)((e[k] >> 32) & 127u) : -1;
+  for (int i = 0; i < kPer; ++i) stage[slot_of(i)] = e[i];
+  wave_sync();
+#pragma unroll 8
+  for (int l = lane; l < nw; l += 64) {
+    const uint2 v = stage[l];
+    const int g = delta[min((int)dig[l], kD1 - 1)] + l;
+    if ((unsigned)g < (unsigned)n) {
+      occ[g] = (int32_t)v.x;
+      occ_seq[g] = (int32_t)v.y;
     }
   }
 }
@@ -566,18 +648,18 @@ __global__ void k_clear2(int32_t* __restrict__ p) {
 
 // key_off from the two scanned histograms, with no pass over the sorted words.
 // After pass 1 the word array is ordered by the low digit: the words whose low
-// digit is below lo are its first offs1[lo * tiles1] entries.  Pass 2 cuts that
-// array into tiles of kIxTile entries, and its scanned histogram holds, for
-// high digit d and tile t, the words of high digit below d plus those of high
-// digit d in the tiles before t.  So the words with key below k = d * 128 + lo
-// number offs2[d * tiles2 + t] for the tile t holding entry offs1[lo * tiles1],
-// plus the words of high digit d in that tile before the entry, which one
-// workgroup per low digit counts (fewer than kIxTile entries).  A key with no
+// digit is below lo are its first offs1[lo * groups1] entries.  Pass 2 cuts that
+// array into groups of kIxGroup entries, and its scanned histogram holds, for
+// high digit d and group t, the words of high digit below d plus those of high
+// digit d in the groups before t.  So the words with key below k = d * 128 + lo
+// number offs2[d * groups2 + t] for the group t holding entry offs1[lo * groups1],
+// plus the words of high digit d in that group before the entry, which one
+// workgroup per low digit counts (fewer than kIxGroup entries).  A key with no
 // word gets the first slot of the next key that has one, n_words past the
 // last.  After a layout error the index holds no word.
-__global__ __launch_bounds__(256) void k_ix_key_off(const uint64_t* __restrict__ words,
-                                                    const int32_t* __restrict__ offs1, int64_t tiles1,
-                                                    const int32_t* __restrict__ offs2, int64_t tiles2,
+__global__ __launch_bounds__(256) void k_ix_key_off(const uint8_t* __restrict__ digits,
+                                                    const int32_t* __restrict__ offs1, int64_t groups1,
+                                                    const int32_t* __restrict__ offs2, int64_t groups2,
                                                     const int32_t* __restrict__ err, int64_t cap,
                                                     int64_t* __restrict__ key_off) {
   __shared__ int32_t cnt[kD1];
@@ -586,18 +668,23 @@ __global__ __launch_bounds__(256) void k_ix_key_off(const uint64_t* __restrict__
   const int64_t n = none ? 0 : min((int64_t)err[1], cap);
   for (int d = threadIdx.x; d < kD1; d += blockDim.x) cnt[d] = 0;
   __syncthreads();
-  const int64_t start = none ? 0 : min(max((int64_t)offs1[(int64_t)lo * tiles1], (int64_t)0), n);
-  const int64_t t = start / kIxTile;
-  for (int64_t i = t * kIxTile + threadIdx.x; i < start; i += blockDim.x)
-    atomicAdd(&cnt[min((int)(words[i] >> (39 + kD0Bits)), kD1 - 1)], 1);
+  const int64_t start = none ? 0 : min(max((int64_t)offs1[(int64_t)lo * groups1], (int64_t)0), n);
+  const int64_t t = start / kIxGroup;
+  for (int64_t i = t * kIxGroup + 16 * threadIdx.x; i < start; i += 16 * blockDim.x) {
+    const uint4 v = *(const uint4*)(digits + i);  // (the array's end is a multiple of 256 past its start)
+    const uint32_t d4[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (i + k < start) atomicAdd(&cnt[min((int)((d4[k >> 2] >> (8 * (k & 3))) & 0xffu), kD1 - 1)], 1);
+  }
   __syncthreads();
   for (int d = threadIdx.x; d < kD1; d += blockDim.x) {
     const int k = d * kD0 + lo;
     if (k >= kNKeys) continue;
     int64_t v = 0;
     if (!none) {
-      const int64_t idx = (int64_t)d * tiles2 + t;
-      v = min((idx < (int64_t)kD1 * tiles2 ? (int64_t)offs2[idx] : n) + cnt[d], n);
+      const int64_t idx = (int64_t)d * groups2 + t;
+      v = min((idx < (int64_t)kD1 * groups2 ? (int64_t)offs2[idx] : n) + cnt[d], n);
     }
     key_off[k] = v;
   }
@@ -802,7 +889,7 @@ IndexLayout index_layout(int64_t n_padded) {
 // layout that grows with n_padded alone, so a workspace sized for the largest
 // bank serves every smaller one whatever its number of sequences.
 struct IxWs {
-  int64_t tiles1, tiles2, cap;
+  int64_t tiles1, groups1, groups2, cap;
   size_t tile_seq, hist1, hist2, tmp, words, digits, total;
 };
 
@@ -811,17 +898,18 @@ IxWs ix_ws(int64_t n_padded) {
   w.cap = n_padded > kPadLen ? n_padded - kPadLen : 0;
   w.tiles1 = (n_padded + kIxTile - 1) / kIxTile;
   if (w.tiles1 < 1) w.tiles1 = 1;
-  w.tiles2 = (w.cap + kIxTile - 1) / kIxTile;
-  if (w.tiles2 < 1) w.tiles2 = 1;
+  w.groups1 = (w.tiles1 + kIxWaves - 1) / kIxWaves;
+  w.groups2 = (w.cap + kIxGroup - 1) / kIxGroup;
+  if (w.groups2 < 1) w.groups2 = 1;
   size_t off = 256;
   w.tile_seq = off;
   off = align_up(off + sizeof(int32_t) * (size_t)w.tiles1, 256);
   w.hist1 = off;
-  off = align_up(off + sizeof(int32_t) * (size_t)(kD0 * w.tiles1), 256);
+  off = align_up(off + sizeof(int32_t) * (size_t)(kD0 * w.groups1), 256);
   w.hist2 = off;
-  off = align_up(off + sizeof(int32_t) * (size_t)(kD1 * w.tiles2), 256);
+  off = align_up(off + sizeof(int32_t) * (size_t)(kD1 * w.groups2), 256);
   w.tmp = off;
-  const int64_t scan_n = kD0 * w.tiles1 > kD1 * w.tiles2 ? kD0 * w.tiles1 : kD1 * w.tiles2;
+  const int64_t scan_n = kD0 * w.groups1 > kD1 * w.groups2 ? kD0 * w.groups1 : kD1 * w.groups2;
   off = align_up(off + scan_tmp_bytes(scan_n), 256);
   w.words = off;
   off = align_up(off + sizeof(uint64_t) * (size_t)w.cap, 256);
@@ -850,7 +938,7 @@ int index_enqueue(const uint8_t* d_codes, const int64_t* d_seq_start, int32_t n_
   int32_t* hist1 = (int32_t*)(ws + W.hist1);
   int32_t* hist2 = (int32_t*)(ws + W.hist2);
   void* tmp = ws + W.tmp;
-  uint64_t* words = (uint64_t*)(ws + W.words);
+  uint2* words = (uint2*)(ws + W.words);
   uint8_t* digits = ws + W.digits;
 
   SeedClasses sc = seed_classes();
@@ -866,25 +954,23 @@ int index_enqueue(const uint8_t* d_codes, const int64_t* d_seq_start, int32_t n_
   }
   // After a layout error the passes that read the tile table or the word
   // arrays return at once and key_off says the index holds no word.
-  const unsigned g1 = (unsigned)((W.tiles1 + kIxWaves - 1) / kIxWaves);
-  const unsigned g2 = (unsigned)((W.tiles2 + kIxWaves - 1) / kIxWaves);
-  const int64_t tiles_scan = (scan_len + kIxTile - 1) / kIxTile;  // tiles covering the scan codes and their slack
-  const int64_t tiles_c = tiles_scan > W.tiles1 ? tiles_scan : W.tiles1;
-  hipLaunchKernelGGL(k_ix_check_count1, dim3((unsigned)((tiles_c + kIxWaves - 1) / kIxWaves)), dim3(64 * kIxWaves), 0,
-                     stream, d_codes, d_seq_start, n_seqs, n_padded, (const int32_t*)tile_seq, W.tiles1, scan,
-                     scan_len, sc, hist1, d_err);
-  exclusive_scan_i32(hist1, kD0 * W.tiles1, total, tmp, stream);
-  hipLaunchKernelGGL(k_ix_scatter1, dim3(g1), dim3(64 * kIxWaves), 0, stream, d_codes, d_seq_start, n_seqs,
-                     n_padded, W.tiles1, sc, (const int32_t*)tile_seq, (const int32_t*)d_err, (const int32_t*)hist1,
-                     W.cap, words, digits);
-  hipLaunchKernelGGL(k_ix_count2, dim3(g2), dim3(64 * kIxWaves), 0, stream, (const uint8_t*)digits,
-                     (const int32_t*)d_err, W.cap, W.tiles2, hist2);
-  exclusive_scan_i32(hist2, kD1 * W.tiles2, nullptr, tmp, stream);
-  hipLaunchKernelGGL(k_ix_scatter2, dim3(g2), dim3(64 * kIxWaves), 0, stream, (const uint64_t*)words,
-                     (const int32_t*)tile_seq, W.tiles1, (const int32_t*)d_err, W.cap, W.tiles2,
-                     (const int32_t*)hist2, occ, occ_seq);
-  hipLaunchKernelGGL(k_ix_key_off, dim3(kD0), dim3(256), 0, stream, (const uint64_t*)words, (const int32_t*)hist1,
-                     W.tiles1, (const int32_t*)hist2, W.tiles2, (const int32_t*)d_err, W.cap, key_off);
+  const unsigned g1 = (unsigned)W.groups1, g2 = (unsigned)W.groups2;
+  const int64_t groups_scan = (scan_len + kIxGroup - 1) / kIxGroup;  // covering the scan codes and their slack
+  const unsigned gc = (unsigned)(groups_scan > W.groups1 ? groups_scan : W.groups1);
+  const dim3 block(64 * kIxWaves);
+  hipLaunchKernelGGL(k_ix_check_count1, dim3(gc), block, 0, stream, d_codes, d_seq_start, n_seqs, n_padded,
+                     (const int32_t*)tile_seq, W.tiles1, scan, scan_len, sc, hist1, W.groups1, d_err);
+  exclusive_scan_i32(hist1, kD0 * W.groups1, total, tmp, stream);
+  hipLaunchKernelGGL(k_ix_scatter1, dim3(g1), block, 0, stream, d_codes, d_seq_start, n_seqs, n_padded, W.tiles1,
+                     W.groups1, sc, (const int32_t*)tile_seq, (const int32_t*)d_err, (const int32_t*)hist1, W.cap, words,
+                     digits);
+  hipLaunchKernelGGL(k_ix_count2, dim3(g2), block, 0, stream, (const uint8_t*)digits, (const int32_t*)d_err, W.cap,
+                     W.groups2, hist2);
+  exclusive_scan_i32(hist2, kD1 * W.groups2, nullptr, tmp, stream);
+  hipLaunchKernelGGL(k_ix_scatter2, dim3(g2), block, 0, stream, (const uint2*)words, (const uint8_t*)digits,
+                     (const int32_t*)d_err, W.cap, W.groups2, (const int32_t*)hist2, occ, occ_seq);
+  hipLaunchKernelGGL(k_ix_key_off, dim3(kD0), dim3(256), 0, stream, (const uint8_t*)digits, (const int32_t*)hist1,
+                     W.groups1, (const int32_t*)hist2, W.groups2, (const int32_t*)d_err, W.cap, key_off);
   timing_mark(kStageIndex, true, stream);
   PLAST_HIP(hipGetLastError());
 

@@ -29,20 +29,13 @@ extern const int8_t kBlosum62Ncbi[20][20];
 void blosum62_code_order(int8_t* m);
 
 // Subset seed of Sec. 3.3.1: position 2 has two classes, position 3 eleven.
-// Class ids are packed 4 bits per residue code (code c at bits 4c of a
-// 128-bit value split in two words) so kernels evaluate them in registers.
+// One byte per residue code, code c in byte c % 4 of dword c / 4, so that kernels
+// look four codes up at once in registers.
 struct SeedClasses {
-  uint32_t pos2_g_mask;   // bit c set iff residue c is in class g (id 1), else class c (id 0)
-  uint64_t pos3_lo;       // codes 0..15
-  uint64_t pos3_hi;       // codes 16..19
+  uint32_t pos2[5];     // class id at position 2 (0 or 1)
+  uint32_t pos3x20[5];  // 20 x class id at position 3
 };
 SeedClasses seed_classes();
-
-__device__ __forceinline__ int seed_key_dev(const SeedClasses& sc, int w0, int w1, int w2, int w3) {
-  int c2 = (sc.pos2_g_mask >> w1) & 1;
-  int c3 = (int)((w2 < 16 ? (sc.pos3_lo >> (4 * w2)) : (sc.pos3_hi >> (4 * (w2 - 16)))) & 15u);
-  return ((w0 * 2 + c2) * 11 + c3) * 20 + w3;
-}
 
 // ---------------------------------------------------------------- errors
 int set_error(int code, const char* fmt, ...);
