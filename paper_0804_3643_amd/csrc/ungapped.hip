@@ -18,10 +18,11 @@
 // separators and its best prefix is the clipped one.
 //
 // Two arithmetic variants give identical integers:
-//   * f16 (used when |M| <= 23, which covers BLOSUM62): every partial sum is an
-//     integer of magnitude <= 44 * 23 < 1024, exactly representable in binary16,
-//     so packed f16 adds are exact; two steps cost two v_pk_add_f16 and one
-//     v_pk_maximum3_f16 per register;
+//   * f16 (used when |M| <= 46, which covers BLOSUM62 in units down to an eighth
+//     of a bit): every partial sum is an integer of magnitude <= 44 * 46 < 2048,
+//     exactly representable in binary16, so packed f16 adds are exact; two steps
+//     cost two v_pk_add_f16 and one v_pk_maximum3_f16 per register (1,500 x 30,000
+//     proteins with entries up to 33: 1.23 ms, 1.39 in int16);
 //   * int16 (any int8 matrix): v_pk_add_u16 / v_pk_max_i16, one add and one max
 //     per step and register.
 //
@@ -60,7 +61,7 @@ typedef short s16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSepScore = -4;
-constexpr int kF16MaxEntry = 23;                  // 44 * 23 = 1012 < 1024
+constexpr int kF16MaxEntry = 46;                  // 44 * 46 = 2024 < 2048
 constexpr int kProfT = kNLet * 8;                 // bytes per scan step
 constexpr int kProfRG = kSpan * kProfT;           // bytes per 4-row group
 constexpr int kProfBytes = kRowGroups * kProfRG;  // 59136
@@ -68,7 +69,7 @@ constexpr int kPairs = 2 * kRowGroups;            // packed registers per lane (
 static_assert(kProfBytes + 4096 < 65536, "profile offsets must fit the LDS instruction offset field");
 static_assert(kPadCode * kScale < 256, "scaled codes must fit a byte");
 static_assert(kTileRows == 32 && kPairs == 16, "row mask layout assumes at most 32 rows");
-static_assert(kSpan * kF16MaxEntry < 1024, "f16 partial sums must stay exact");
+static_assert(kSpan * kF16MaxEntry < 2048, "f16 partial sums must stay exact");
 
 struct BankView {
   const int64_t* key_off;
@@ -80,7 +81,7 @@ struct BankView {
 
 struct UngappedArgs {
   BankView a, b;
-  uint32_t thr;                // packed pair: threshold - 1 (int16) or threshold - 0.5 (f16)
+  uint32_t thr;                // packed pair: threshold - 1 (int16 or f16)
   int32_t s1;
   plast_hit_t* hits;
   int64_t capacity;
@@ -764,8 +765,9 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
   const bool f16 = maxabs <= kF16MaxEntry;
   // Threshold register: hit iff thr - best < 0.  Scores lie in [0, 44 * maxabs].
   if (f16) {
-    // best is an integer in [0, 1012]: thr = s1 - 1/2 clamped to [-1/2, 1012.5], exact in binary16
-    const float t = (float)min(max(p->s1, 0), kSpan * kF16MaxEntry + 1) - 0.5f;
+    // best is an integer in [0, 2024]: thr = s1 - 1 clamped to [-1, 2024], exact in
+    // binary16, and the difference too (0 is not negative)
+    const float t = (float)(min(max(p->s1, 0), kSpan * kF16MaxEntry + 1) - 1);
     const uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)t);
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   } else {

@@ -107,3 +107,15 @@ def test_heavy_keys(B, seed, path):
     b2 = synth.random_bank(rng, 400, 4, 120, 3 + seed)
     m = O.BLOSUM62.astype(np.int8) if seed % 2 else None
     _check(B, path, b1, b2, 45, matrix=m, tuning={"item_cols": [1024, 512, 2048, 16384], "xcd_queues": 8 if seed < 2 else 1})
+
+
+@pytest.mark.parametrize("entry,s1", [(46, 1), (46, 2023), (46, 2024), (46, 2025), (47, 2068), (-46, 700), (-47, 700)])
+@pytest.mark.parametrize("path", ["wave", "valu"])
+def test_largest_entries_in_binary16(B, entry, s1, path):
+    """Entries all 46 (the best is 2024, every integer below it exact in binary16) or 47 (16-bit integers), at the
+    thresholds around the best, and random signs of them."""
+    rng = np.random.default_rng(13)
+    m = (np.full((20, 20), entry) if entry > 0 else rng.choice([-entry, entry], (20, 20))).astype(np.int8)
+    b1, b2 = _word_bank(rng, 90), _word_bank(rng, 200)
+    ref = _check(B, path, b1, b2, s1, matrix=m)
+    assert (len(ref) > 0) == (s1 <= 44 * abs(entry))
