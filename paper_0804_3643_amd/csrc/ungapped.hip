@@ -775,8 +775,9 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
     const uint16_t h = (uint16_t)(int16_t)t;
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   }
-  // Small banks on both sides: an item per wavefront.
-  if (b->n_padded < kWMaxCols * kNKeys && (double)a->n_padded * (double)b->n_padded <= kWMaxCodes)
+  // Small banks: an item per wavefront.
+  const double codes2 = (double)a->n_padded * (double)b->n_padded;
+  if (codes2 <= kWCodes || (codes2 <= kWMaxCodes && b->n_padded < kWMaxCols * kNKeys) || a->n_padded < kNKeys / 2)
     return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
   // The matrix-core tile counts on pairs of score 0 not being hits, and pays
   // from about 12 rows a key on: against 100,000 proteins, a query of 450 (143,000

@@ -11,20 +11,29 @@
 // together and written with one global atomic.  Bound by the latency of the loads
 // that an item begins with (work list, key table, occurrences, letters).
 //
-// Measured, against a workgroup per item: 200 x 2000 proteins (8800 items of 7 x 66
-// on average) 66 us, 164; 30 x 2000 29, 75; 3 x 300 10, 22.
+// A list of fewer items than wavefronts is cut further, into slices of the items'
+// columns.  Where bank b is large every column's window is a line or two from a
+// random place, and that bounds the kernel: 3 proteins against 1M, 50M windows at
+// some 6 TB/s.
+//
+// Measured, against a workgroup per item (proteins, us): 200 x 2000 66 and 164, 30 x
+// 2000 27 and 72, 3 x 300 10 and 22, 100 x 10,000 119 and 172, 3 x 100,000 113 and
+// 128, 3 x 1M 1186 and 1563.
 constexpr int kWWaves = kThreads / 64;
 constexpr int kWSlots = 512;
-// Chosen for a bank b of fewer than 200 codes a key, and no more pairs than two
-// banks of 2000 proteins have, so that an item is a few column groups and no
-// wavefront has many (proteins, us here and on a workgroup per item): 200 x 4000 107
-// and 181, 200 x 10,000 251 and 203, 1000 x 2000 160 and 238, 1000 x 5000 325 and 267,
-// 3000 x 2000 393 and 447, 10,000 x 300 708 and 1020, 10,000 x 2000 2990 and 1250.
-constexpr int64_t kWMaxCols = 200;
+// Chosen for few pairs in all, as the product of the banks' codes says, and for more
+// of them where a key has few columns or hardly a row (us here and on a workgroup per
+// item): 200 x 4000 95 and 180, 400 x 5000 172 and 209, 200 x 10,000 202 and 202, 20 x
+// 100,000 414 and 411 (2.6e11), 1000 x 2000 189 and 237, 10 x 300,000 759 and 929, but
+// 100 x 30,000 313 and 234 (3.9e11), 30 x 100,000 502 and 466; 1000 x 5000 325 and
+// 267, 10,000 x 2000 2990 and 1250.
+constexpr double kWCodes = 2.5e11;
 constexpr double kWMaxCodes = 4e11;
+constexpr int64_t kWMaxCols = 200;                  // codes of bank b per key
 
 constexpr int kWMatRow = 22;                        // entries of a matrix row in LDS: dwords of two letters
 constexpr int kWRows = 8;                           // rows of an item that a wavefront takes at a time
+constexpr int kWSlices = 16;                        // most slices of an item's columns
 
 struct __align__(16) WSmem {
   uint8_t prof[kWWaves][kProfRG];      // 8-byte entries
@@ -96,14 +105,16 @@ __device__ __forceinline__ void w_hits(const UngappedArgs& A, WSmem& S, const ve
   }
 }
 
-// Rows row .. row + kWRows - 1 of an item (those that it has) against its columns.
+// Rows row .. row + kWRows - 1 of an item (those that it has) against its columns
+// in groups of 64, the groups slice, slice + slices, ...
 template <bool F16>
-__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int row, int wid, WSmem& S) {
+__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int row, int slice, int slices,
+                                           int wid, WSmem& S) {
   const int lane = __lane_id();
   const int64_t ka = A.a.key_off[it.key], ka1 = A.a.key_off[it.key + 1];
   const int a0 = (int)ka + it.row0 + row, b0 = (int)A.b.key_off[it.key] + it.col0;
   const int rows = min(min(kWRows, kTileRows - row), (int)ka1 - a0);
-  if (rows <= 0) return;
+  if (rows <= 0 || slice * 64 >= it.ncols) return;
   const int qrow = lane < rows ? A.a.occ[a0 + lane] : -1;
   uint8_t* prof = S.prof[wid];
   for (int r0 = 0; r0 < rows; r0 += 4) {
@@ -130,15 +141,22 @@ __device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem
     }
     w_sync();
     const uint32_t valid = valid_rows_mask(min(4, rows - r0));
-    for (int c0 = 0; c0 < it.ncols; c0 += 64) {
+    // the next group's occurrence and window are in flight
+    auto occ_of = [&](int c0) { return b0 + (c0 + lane < it.ncols ? c0 + lane : 0); };
+    int q2 = A.b.occ[occ_of(slice * 64)];
+    uint32_t raw[12];
+    load_window_raw(A, q2, raw);
+    for (int c0 = slice * 64; c0 < it.ncols; c0 += slices * 64) {
       const bool active = c0 + lane < it.ncols;
-      const int ob = b0 + (active ? c0 + lane : 0);
-      const int q2 = A.b.occ[ob];
-      uint32_t raw[12], win[11];
-      load_window_raw(A, q2, raw);
+      const int ob = occ_of(c0);
+      uint32_t win[11];
       const int sh = (q2 - kNbr) & 3;
 #pragma unroll
       for (int i = 0; i < 11; ++i) win[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
+      if (c0 + slices * 64 < it.ncols) {
+        q2 = A.b.occ[occ_of(c0 + slices * 64)];
+        load_window_raw(A, q2, raw);
+      }
       vec2<F16> m[2];
       scan_window<F16, 1>(prof, win, m);
       w_hits<F16>(A, S, m, active ? (hit_mask<F16, 1>(A.thr, m) & valid) : 0u, a0 + r0, ob);
@@ -168,11 +186,14 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
   const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
   // units of kWRows rows of an item, most of which have fewer rows in all
   constexpr int kUnits = kTileRows / kWRows;
-  const int64_t n_units = (int64_t)n_items * kUnits, stride = (int64_t)gridDim.x * kWWaves;
+  const int64_t stride = (int64_t)gridDim.x * kWWaves;
+  // and of a slice of its columns where the list has few items for the wavefronts
+  const int slices = (int)min((int64_t)kWSlices, 1 + 4 * stride / max(n_items, 1));
+  const int64_t n_units = (int64_t)n_items * kUnits * slices;
   for (int64_t u = (int64_t)blockIdx.x * kWWaves + wid; u < n_units; u += stride) {
     // all first units before all second ones: neighbouring wavefronts have like work
     const int i = (int)(u % n_items), part = (int)(u / n_items);
-    run_item_w<F16>(A, items[i], part * kWRows, wid, S);
+    run_item_w<F16>(A, items[i], part / slices * kWRows, part % slices, slices, wid, S);
   }
   __syncthreads();
   const int n = min(S.n_hit, S.n_fit);

@@ -14,7 +14,7 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
 # Codes that banks a and b are brought to with empty sequences (20 codes each): the kernel is chosen by them.
-PATHS = {"wave": (0, 0), "valu": (0, 1_800_000), "matrix": (110_000, 1_800_000)}
+PATHS = {"wave": (0, 0), "valu": (100_000, 2_600_000), "matrix": (110_000, 2_600_000)}
 
 
 @pytest.fixture(scope="module")
