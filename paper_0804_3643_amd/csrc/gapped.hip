@@ -536,17 +536,169 @@ __device__ __forceinline__ void gapped_hit_f16(const GappedArgs& G, const uint32
   }
 }
 
+// ---------------------------------------------------------------- packed path, few hits
+// A lane per hit takes 50 us from the first row to the last whatever their number,
+// which is what a search of small banks waits for.  Up to kFewHits hits are taken by
+// 32 lanes each instead, sweeping the anti-diagonals a = i + j with the same packed
+// arithmetic: lane p holds the cells d = 2p - 16 of the even and d = 2p - 15 of the
+// odd ones (17 and 16 cells of the band), so the diagonal neighbour is the lane's
+// own cell of two steps ago, and of the left and the upper one the one is its own
+// and the other the next lane's.  Letters and scores come from LDS, eight pairs of
+// steps at a time.  128 steps of some 14 instructions for 2 hits of a wavefront are
+// three times the work per hit: 12 us for up to 2000 hits, 24 for 8192, 42 for 16384
+// and 50 for 20,000, where a lane per hit takes 53 up to 50,000.
+constexpr int kFewHits = 16384;
+constexpr int kFewLanes = 32;
+constexpr int kFewLet = 96;     // letters of a sequence by index + 8
+constexpr int kFewPairs = 8;    // pairs of steps per block
+static_assert(kGMaxBand == 16 && kFewLet >= kGMaxWin + 8 + 16, "17 lanes of the band; indices -8 .. 72 and a block ahead");
+
+struct FewLetters {
+  uint32_t x[kFewLet], y[kFewLet];  // score-table offsets: x letter 42, y letter 2 (right side, left side << 16)
+};
+
+// Orders a wavefront's accesses of its own LDS across lanes.
+__device__ __forceinline__ void few_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ void gapped_few_f16(const GappedArgs& G, const uint16_t* tb, FewLetters& S,
+                                               const plast_hit_t* __restrict__ hits, int64_t h, int64_t n_hits,
+                                               int32_t* __restrict__ gscore, uint8_t* __restrict__ pass) {
+  const int lane = __lane_id() & (kFewLanes - 1);
+  const bool live = h < n_hits;
+  const plast_hit_t hit = live ? hits[h] : plast_hit_t{0, 0, 0, 0, 0};
+  bool sane = live && hit.seq1 >= 0 && hit.seq1 < G.a_nseq && hit.seq2 >= 0 && hit.seq2 < G.b_nseq;
+  int64_t sa = 0, sb = 0;
+  int la = 0, lb = 0;
+  if (sane) {
+    sa = G.a_seq_start[hit.seq1];
+    sb = G.b_seq_start[hit.seq2];
+    la = (int)(G.a_seq_start[hit.seq1 + 1] - sa - kPadLen);
+    lb = (int)(G.b_seq_start[hit.seq2 + 1] - sb - kPadLen);
+    sane = hit.pos1 >= 0 && hit.pos1 < la && hit.pos2 >= 0 && hit.pos2 < lb;
+  }
+  const int lxR = sane ? min(G.window, la - hit.pos1) : 0, lxL = sane ? min(G.window, hit.pos1) : 0;
+  const int lyR = sane ? min(G.window, lb - hit.pos2) : 0, lyL = sane ? min(G.window, hit.pos2) : 0;
+  const uint8_t* xa = G.a_scan + (sane ? sa + hit.pos1 : 0);
+  const uint8_t* yb = G.b_scan + (sane ? sb + hit.pos2 : 0);
+#pragma unroll
+  for (int k0 = 0; k0 < kFewLet; k0 += kFewLanes) {
+    const int k = k0 + lane, i = k - 8;
+    if (k < kFewLet) {
+      const uint32_t xr = i >= 1 && i <= lxR ? xa[i - 1] : kWall8, xl = i >= 1 && i <= lxL ? xa[-i] : kWall8;
+      const uint32_t yr = i >= 1 && i <= lyR ? yb[i - 1] : kWall8, yl = i >= 1 && i <= lyL ? yb[-i] : kWall8;
+      S.x[k] = (xr | (xl << 16)) / kScale * (2 * kNLet);
+      S.y[k] = (yr | (yl << 16)) / kScale * 2;
+    }
+  }
+  few_sync();
+  const int p = min(lane, kGMaxBand);
+  const bool in_odd = lane < kGMaxBand;  // a lane past 15 holds no cell of an odd anti-diagonal
+  const _Float16 ninf = -__builtin_inff16();
+  const _Float16 op = (_Float16)G.gap_open, ex = (_Float16)G.gap_extend;
+  const gh2 NEG = {ninf, ninf}, OP = {op, op}, EX = {ex, ex};
+  const int neg = __builtin_bit_cast(int, NEG);
+  // a = 0: cell (0, 0) in lane 8
+  gh2 he = NEG, ho = NEG;
+  if (lane == 8) he = gh2{(_Float16)0, (_Float16)0};
+  gh2 e = he - OP, f = e;                        // from the last step's cells to their right and lower neighbours
+  gh2 best = {(_Float16)0, (_Float16)0};         // plus a times extend
+  const uint32_t* xs = S.x + 16 - p;
+  const uint32_t* ys = S.y + 1 + p;
+  uint32_t x[kFewPairs + 1], y[kFewPairs];
+  x[0] = xs[0];
+#pragma unroll
+  for (int t = 0; t < kFewPairs; ++t) {
+    x[t + 1] = xs[t + 1];
+    y[t] = ys[t];
+  }
+  const int last = max(lxR + lyR, lxL + lyL);  // no cell of a later anti-diagonal counts
+  auto score = [&](uint32_t o) {
+    const uint32_t r = *(const uint16_t*)((const char*)tb + (o & 0xffffu));
+    const uint32_t l = *(const uint16_t*)((const char*)tb + (o >> 16));
+    return __builtin_bit_cast(gh2, r | (l << 16));
+  };
+  int m = 0;
+  for (; __builtin_amdgcn_readfirstlane(__ballot(2 * m < last) != 0) && m < kGMaxWin; m += kFewPairs) {
+    gh2 so[kFewPairs], se[kFewPairs];
+#pragma unroll
+    for (int t = 0; t < kFewPairs; ++t) {
+      so[t] = score(x[t] + y[t]);
+      se[t] = score(x[t + 1] + y[t]);
+    }
+    x[0] = x[kFewPairs];
+#pragma unroll
+    for (int t = 0; t < kFewPairs; ++t) {
+      x[t + 1] = xs[min(m + kFewPairs, kGMaxWin) + t + 1];
+      y[t] = ys[min(m + kFewPairs, kGMaxWin) + t];
+    }
+#pragma unroll
+    for (int t = 0; t < kFewPairs; ++t) {
+      {  // a = 2 (m + t) + 1: from above in the next lane (rows of 16 lanes 1 and 3 hold none)
+        const gh2 ein = in_odd ? e : NEG;
+        const gh2 fin = __builtin_bit_cast(
+            gh2, __builtin_amdgcn_update_dpp(neg, __builtin_bit_cast(int, f), 0x130, 0x5, 0xf, false));
+        ho = gmax3(ho + so[t], ein, fin);
+        const gh2 o = ho - OP;
+        e = gmax(ein, o);
+        f = gmax(fin, o);
+        best = gmax(best + EX, ho);
+      }
+      {  // a = 2 (m + t) + 2: from the left in the lane before
+        const gh2 ein = __builtin_bit_cast(
+            gh2, __builtin_amdgcn_update_dpp(neg, __builtin_bit_cast(int, e), 0x138, 0xf, 0xf, false));
+        he = gmax3(he + se[t], ein, f);
+        const gh2 o = he - OP;
+        e = gmax(ein, o);
+        f = gmax(f, o);
+        best = gmax(best + EX, he);
+      }
+    }
+  }
+  const _Float16 a_end = (_Float16)(2 * m * G.gap_extend);
+  best = best - gh2{a_end, a_end};
+  for (int o = kFewLanes / 2; o >= 1; o >>= 1)
+    best = gmax(best, __builtin_bit_cast(gh2, __shfl_xor(__builtin_bit_cast(int, best), o)));
+  if (live && lane == 0) {
+    const int total = sane ? (int)best.x + (int)best.y : -1;
+    gscore[h] = total;
+    pass[h] = (sane && total >= G.s2) ? 1 : 0;
+  }
+  few_sync();  // the letters are read
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
 void k_gapped_f16(GappedArgs G, const plast_hit_t* __restrict__ hits, int64_t n_hits,
                   const unsigned long long* __restrict__ n_dev, int32_t* __restrict__ gscore,
                   uint8_t* __restrict__ pass) {
-  __shared__ uint32_t tbl[kPairDwords];  // filled once per workgroup
+  struct Few {
+    uint16_t tbl[(kNLet * kNLet + 1) & ~1];
+    FewLetters letters[NT / kFewLanes];
+  };
+  __shared__ union {
+    uint32_t tbl[kPairDwords];  // filled once per workgroup
+    Few few;
+  } S;
+  if (n_dev) n_hits = min(n_hits, (int64_t)*n_dev);
+  if (__builtin_expect(n_hits <= kFewHits, 0)) {
+    for (int i = threadIdx.x; i < kNLet * kNLet; i += NT) S.few.tbl[i] = G.tbl16[i];
+    __syncthreads();
+    constexpr int kGroups = NT / kFewLanes;
+    const int g = threadIdx.x / kFewLanes;
+    for (int64_t h = (int64_t)blockIdx.x * kGroups + g; h - g < n_hits; h += (int64_t)gridDim.x * kGroups)
+      gapped_few_f16(G, S.few.tbl, S.few.letters[g], hits, h, n_hits, gscore, pass);
+    return;
+  }
+  if ((int64_t)blockIdx.x * NT >= n_hits) return;
+  uint32_t* tbl = S.tbl;
   for (int i = threadIdx.x; i < kPairDwords; i += NT) {
     const int x = i / kPairRow, y1 = (i / kNLet) % kNLet, y2 = i % kNLet;
     tbl[i] = (uint32_t)G.tbl16[x * kNLet + y1] | ((uint32_t)G.tbl16[x * kNLet + y2] << 16);
   }
-  if (n_dev) n_hits = min(n_hits, (int64_t)*n_dev);
   __syncthreads();
   // grid-stride over blocks of NT hits; no barrier inside the loop
   for (int64_t h = (int64_t)blockIdx.x * NT + threadIdx.x; h - threadIdx.x < n_hits; h += (int64_t)gridDim.x * NT)
@@ -665,7 +817,11 @@ int gapped_filter_impl(const plast_index_t* a, const plast_index_t* b, const pla
   const GappedForm f = form(i);
   const int64_t most = form_resident(i);
   if (most <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
-  const int64_t need = (n_hits + f.hits - 1) / f.hits;
+  // 32 lanes a hit where there are, or where the device may count, up to kFewHits.
+  const int64_t n_few = n_hits < kFewHits ? n_hits : kFewHits;
+  const int64_t few = fast && (d_n || n_hits <= kFewHits) ? (n_few * kFewLanes + f.threads - 1) / f.threads : 0;
+  int64_t need = (n_hits + f.hits - 1) / f.hits;
+  if (need < few) need = few;
   timing_mark(kStageGapped, false, stream);
   hipLaunchKernelGGL(f.kernel, dim3((unsigned)(need < most ? need : most)), dim3(f.threads), 0, stream, G, d_hits,
                      n_hits, d_n, d_gscore, d_pass);

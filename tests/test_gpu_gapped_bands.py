@@ -52,3 +52,23 @@ def test_every_band(B, banks, band, window, gap_open, gap_extend):
     ref = C.gapped_scores(b1, b2, h, **par)
     assert np.array_equal(gs.cpu().numpy().astype(np.int64), ref)
     assert np.array_equal(ps.cpu().numpy().astype(bool), ref >= 40)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 1000, 16383, 16384, 16385, 40000])
+@pytest.mark.parametrize("window,gap_open,gap_extend,threads", [(64, 2, 1, 256), (63, 11, 1, 128), (17, 3, 0, 512),
+                                                                (1, 0, 1, 256)])
+def test_few_hits_and_many(B, banks, n, window, gap_open, gap_extend, threads):
+    """Around the number of hits up to which a hit takes half a wavefront instead of a lane; some name no sequence."""
+    b1, b2 = banks
+    ia, ib = (B.build_index(*B.bank_to_device(b, "cuda")) for b in banks)
+    hits, _ = B.ungapped_extend(ia, ib, 20)
+    rng = np.random.default_rng(n)
+    h = hits.cpu().numpy()[rng.integers(0, hits.shape[0], n)]
+    par = dict(window=window, gap_open=gap_open, gap_extend=gap_extend)
+    ref = C.gapped_scores(b1, b2, h.astype(np.int64), **par)
+    bad = (rng.random(n) < 0.01) & (np.arange(n) > 0)
+    h[bad, rng.integers(0, 4)] = -1
+    ref[bad] = -1
+    gs, ps = B.gapped_filter(ia, ib, torch.from_numpy(h).cuda(), 40, tuning={"gapped_threads": threads}, **par)
+    assert np.array_equal(gs.cpu().numpy().astype(np.int64), ref)
+    assert np.array_equal(ps.cpu().numpy().astype(bool), ref >= 40)
