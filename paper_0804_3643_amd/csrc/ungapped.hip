@@ -777,7 +777,8 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
   }
   // Small banks: an item per wavefront.
   const double codes2 = (double)a->n_padded * (double)b->n_padded;
-  if (codes2 <= kWCodes || (codes2 <= kWMaxCodes && b->n_padded < kWMaxCols * kNKeys) || a->n_padded < kNKeys / 2)
+  if (codes2 <= kWCodes || (codes2 <= kWMaxCodes && b->n_padded < kWMaxCols * kNKeys) || a->n_padded < kNKeys / 2 ||
+      (w_shared(b) && a->n_padded < 3 * kNKeys / 2))
     return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
   // The matrix-core tile counts on pairs of score 0 not being hits, and pays
   // from about 12 rows a key on: against 100,000 proteins, a query of 450 (143,000
@@ -910,12 +911,13 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
+  const bool xcd = w_shared(b);
   if (tile == Tile::kWaveF16)
     hipLaunchKernelGGL(k_ungapped_wave<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
-                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len);
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, xcd);
   else if (tile == Tile::kWaveI16)
     hipLaunchKernelGGL(k_ungapped_wave<false>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
-                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len);
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, xcd);
   else if (tile == Tile::kMfma)
     hipLaunchKernelGGL(k_ungapped_mfma, dim3(grid), dim3(kMThreads), 0, stream, A, (const WorkItem*)W.items,
                        (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues);

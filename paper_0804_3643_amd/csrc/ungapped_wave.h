@@ -12,23 +12,28 @@
 // that an item begins with (work list, key table, occurrences, letters).
 //
 // A list of fewer items than wavefronts is cut further, into slices of the items'
-// columns.  Where bank b is large every column's window is a line or two from a
-// random place, and that bounds the kernel: 3 proteins against 1M, 50M windows at
-// some 6 TB/s.
+// columns.  Where bank b is larger than an L2, a column's window comes from a random
+// place past it; while an eighth of the bank about fits one, each XCD takes the columns
+// of its eighth of the bank.
 //
 // Measured, against a workgroup per item (proteins, us): 200 x 2000 66 and 164, 30 x
-// 2000 27 and 72, 3 x 300 10 and 22, 100 x 10,000 119 and 172, 3 x 100,000 113 and
-// 128, 3 x 1M 1186 and 1563.
+// 2000 27 and 72, 3 x 300 10 and 22, 100 x 10,000 119 and 172, 3 x 100,000 90 and 128
+// (112 without the XCDs' shares), 30 x 100,000 388 and 466 (504), 3 x 1M 1186 and 1563.
 constexpr int kWWaves = kThreads / 64;
 constexpr int kWSlots = 512;
 // Chosen for few pairs in all, as the product of the banks' codes says, and for more
 // of them where a key has few columns or hardly a row (us here and on a workgroup per
-// item): 200 x 4000 95 and 180, 400 x 5000 172 and 209, 200 x 10,000 202 and 202, 20 x
-// 100,000 414 and 411 (2.6e11), 1000 x 2000 189 and 237, 10 x 300,000 759 and 929, but
-// 100 x 30,000 313 and 234 (3.9e11), 30 x 100,000 502 and 466; 1000 x 5000 325 and
-// 267, 10,000 x 2000 2990 and 1250.
+// item): 200 x 4000 95 and 180, 400 x 5000 172 and 209, 200 x 10,000 202 and 202 (2.6e11),
+// 1000 x 2000 189 and 237, 30 x 100,000 388 and 466, 10 x 300,000 759 and 929, 10 x 1M 2605
+// and 3386, but 100 x 30,000 261 and 234 (3.9e11); 1000 x 5000 325 and 267, 10,000 x 2000
+// 2990 and 1250.
 constexpr double kWCodes = 2.5e11;
 constexpr double kWMaxCodes = 4e11;
+// Codes of bank b from which the XCDs share its columns (512 a key: an XCD's share of a
+// key is a group of 64; 100 x 10,000, fewer, would take 135 us instead of 123), and up
+// to which (300,000 proteins, 1.1e8 codes, 338 and 342 us; 1M 1454 and 1187).
+constexpr int64_t kWXcdMin = 512 * (int64_t)kNKeys, kWXcdMax = 64000000;
+inline bool w_shared(const plast_index_t* b) { return b->n_padded >= kWXcdMin && b->n_padded <= kWXcdMax; }
 constexpr int64_t kWMaxCols = 200;                  // codes of bank b per key
 
 constexpr int kWMatRow = 22;                        // entries of a matrix row in LDS: dwords of two letters
@@ -105,16 +110,16 @@ __device__ __forceinline__ void w_hits(const UngappedArgs& A, WSmem& S, const ve
   }
 }
 
-// Rows row .. row + kWRows - 1 of an item (those that it has) against its columns
-// in groups of 64, the groups slice, slice + slices, ...
+// Rows row .. row + kWRows - 1 of an item (those that it has; ka and ka1: its key's
+// first occurrence in bank a and the next key's, kb: its first in bank b) against
+// the columns from .. to - 1 of the key in groups of 64, every slices-th of them.
 template <bool F16>
-__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int row, int slice, int slices,
-                                           int wid, WSmem& S) {
+__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int64_t ka, int64_t ka1, int64_t kb,
+                                           int row, int from, int to, int slices, int wid, WSmem& S) {
   const int lane = __lane_id();
-  const int64_t ka = A.a.key_off[it.key], ka1 = A.a.key_off[it.key + 1];
-  const int a0 = (int)ka + it.row0 + row, b0 = (int)A.b.key_off[it.key] + it.col0;
+  const int a0 = (int)ka + it.row0 + row, b0 = (int)kb;
   const int rows = min(min(kWRows, kTileRows - row), (int)ka1 - a0);
-  if (rows <= 0 || slice * 64 >= it.ncols) return;
+  if (rows <= 0 || from >= to) return;
   const int qrow = lane < rows ? A.a.occ[a0 + lane] : -1;
   uint8_t* prof = S.prof[wid];
   for (int r0 = 0; r0 < rows; r0 += 4) {
@@ -142,18 +147,18 @@ __device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem
     w_sync();
     const uint32_t valid = valid_rows_mask(min(4, rows - r0));
     // the next group's occurrence and window are in flight
-    auto occ_of = [&](int c0) { return b0 + (c0 + lane < it.ncols ? c0 + lane : 0); };
-    int q2 = A.b.occ[occ_of(slice * 64)];
+    auto occ_of = [&](int c0) { return b0 + min(c0 + lane, to - 1); };
+    int q2 = A.b.occ[occ_of(from)];
     uint32_t raw[12];
     load_window_raw(A, q2, raw);
-    for (int c0 = slice * 64; c0 < it.ncols; c0 += slices * 64) {
-      const bool active = c0 + lane < it.ncols;
+    for (int c0 = from; c0 < to; c0 += slices * 64) {
+      const bool active = c0 + lane < to;
       const int ob = occ_of(c0);
       uint32_t win[11];
       const int sh = (q2 - kNbr) & 3;
 #pragma unroll
       for (int i = 0; i < 11; ++i) win[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
-      if (c0 + slices * 64 < it.ncols) {
+      if (c0 + slices * 64 < to) {
         q2 = A.b.occ[occ_of(c0 + slices * 64)];
         load_window_raw(A, q2, raw);
       }
@@ -167,7 +172,7 @@ __device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem
 template <bool F16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const UngappedCounters* __restrict__ cnt,
-                     const int32_t* __restrict__ list_len) {
+                     const int32_t* __restrict__ list_len, bool xcd) {
   __shared__ WSmem S;
   for (int i = threadIdx.x; i < kNLet * kNLet; i += kThreads) {
     uint16_t v;
@@ -184,16 +189,37 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
   __syncthreads();
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
-  // units of kWRows rows of an item, most of which have fewer rows in all
-  constexpr int kUnits = kTileRows / kWRows;
-  const int64_t stride = (int64_t)gridDim.x * kWWaves;
-  // and of a slice of its columns where the list has few items for the wavefronts
-  const int slices = (int)min((int64_t)kWSlices, 1 + 4 * stride / max(n_items, 1));
-  const int64_t n_units = (int64_t)n_items * kUnits * slices;
-  for (int64_t u = (int64_t)blockIdx.x * kWWaves + wid; u < n_units; u += stride) {
-    // all first units before all second ones: neighbouring wavefronts have like work
-    const int i = (int)(u % n_items), part = (int)(u / n_items);
-    run_item_w<F16>(A, items[i], part / slices * kWRows, part % slices, slices, wid, S);
+  if (xcd) {
+    // Each XCD (workgroups are dealt to them round robin) takes an eighth of every
+    // key's columns, which lie in the same eighth of the bank: its L2 then serves
+    // most windows.  A unit is a slice of an item's columns there.
+    const int x = blockIdx.x % kMaxQueues;
+    const int waves = ((int)gridDim.x - x + kMaxQueues - 1) / kMaxQueues * kWWaves;
+    const int slices = min(kWSlices, 1 + 8 * waves / max(n_items, 1));
+    const int64_t n_units = (int64_t)n_items * slices;
+    for (int64_t u = (int64_t)(blockIdx.x / kMaxQueues) * kWWaves + wid; u < n_units; u += waves) {
+      const WorkItem it = items[u % n_items];
+      const int64_t ka = A.a.key_off[it.key], ka1 = A.a.key_off[it.key + 1];
+      const int64_t kb = A.b.key_off[it.key], n2 = A.b.key_off[it.key + 1] - kb;
+      const int from = max(it.col0, (int)(n2 * x / kMaxQueues));
+      const int to = min(it.col0 + it.ncols, (int)(n2 * (x + 1) / kMaxQueues));
+      for (int row = 0; row < kTileRows; row += kWRows)
+        run_item_w<F16>(A, it, ka, ka1, kb, row, from + (int)(u / n_items) * 64, to, slices, wid, S);
+    }
+  } else {
+    // units of kWRows rows of an item, most of which have fewer rows in all
+    constexpr int kUnits = kTileRows / kWRows;
+    const int64_t stride = (int64_t)gridDim.x * kWWaves;
+    // and of a slice of its columns where the list has few items for the wavefronts
+    const int slices = (int)min((int64_t)kWSlices, 1 + 4 * stride / max(n_items, 1));
+    const int64_t n_units = (int64_t)n_items * kUnits * slices;
+    for (int64_t u = (int64_t)blockIdx.x * kWWaves + wid; u < n_units; u += stride) {
+      // all first units before all second ones: neighbouring wavefronts have like work
+      const int i = (int)(u % n_items), part = (int)(u / n_items);
+      const WorkItem it = items[i];
+      run_item_w<F16>(A, it, A.a.key_off[it.key], A.a.key_off[it.key + 1], A.b.key_off[it.key], part / slices * kWRows,
+                      it.col0 + part % slices * 64, it.col0 + it.ncols, slices, wid, S);
+    }
   }
   __syncthreads();
   const int n = min(S.n_hit, S.n_fit);

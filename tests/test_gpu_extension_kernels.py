@@ -119,3 +119,18 @@ def test_largest_entries_in_binary16(B, entry, s1, path):
     b1, b2 = _word_bank(rng, 90), _word_bank(rng, 200)
     ref = _check(B, path, b1, b2, s1, matrix=m)
     assert (len(ref) > 0) == (s1 <= 44 * abs(entry))
+
+
+@pytest.mark.parametrize("codes", [4_400_000, 4_600_000])
+def test_columns_shared_between_xcds(B, codes):
+    """Bank b below and past the size from which every XCD takes an eighth of a key's columns (512 codes a key): keys of
+    fewer columns than XCDs, of one item and of several, and of more than 8 rows."""
+    rng = np.random.default_rng(19)
+    b1 = synth.random_bank(rng, 40, 5, 60, 5)
+    b2 = synth.Bank.from_seqs([rng.integers(0, 5 if i % 3 else 20, n).astype(np.uint8)
+                               for i, n in enumerate(rng.integers(0, 80, 3000))])
+    b2 = _padded(b2, codes)
+    ia, ib = B.build_index(*B.bank_to_device(b1, "cuda")), B.build_index(*B.bank_to_device(b2, "cuda"))
+    hits, _ = B.ungapped_extend(ia, ib, 25, tuning={"item_cols": [512, 512, 512, 512]})
+    ref, _ = C.ungapped_hits(b1, b2, 25, matrix=O.BLOSUM62)
+    assert len(ref) > 1000 and np.array_equal(B.canonical_hits(hits), ref)
