@@ -22,7 +22,7 @@
 // histograms.
 //
 // 300,000 proteins, some 85M words, between 0.81 GB read and written at least (0.17 ms
-// at the rate of a large copy): 0.80 ms, of which pass 2's scattering 0.34, pass
+// at the rate of a large copy): 0.78 ms, of which pass 2's scattering 0.32, pass
 // 1's 0.27 and the counting kernels 0.12; 1.36 ms before ranks came from byte
 // tables (scattering 0.50 and 0.49), keys from packed table lookups (counting 0.14)
 // and histograms from workgroups (a column a wavefront: 0.10 more in the two
@@ -55,13 +55,19 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // The tile group of a workgroup: workgroups are dealt to the XCDs round robin, and
-// each XCD takes a contiguous eighth of the tiles.  Neighbouring tiles then write
+// each XCD takes runs of kXcdRun consecutive groups.  Neighbouring tiles then write
 // their short runs (16 words of a bucket on average, starting anywhere in a line)
-// and their histogram columns through one L2: 128 and 57 us in the counting
-// kernels instead of 143 and 63 (300,000 proteins).
+// and their histogram columns through one L2.  300,000 proteins 777 us, 864 in
+// order; 12M fragments 1854 and 2026; runs of 4 groups 804 and 1885, of 64 785 and
+// 1855, and an eighth of the groups each 801 and 2799 (pass 2 has fewer words than
+// positions, and the last XCDs none of them).
+constexpr unsigned kXcdRun = 16;
+
 __device__ __forceinline__ int64_t xcd_group() {
-  const unsigned nb = gridDim.x, k = blockIdx.x % kMaxQueues;
-  return (int64_t)k * (nb / kMaxQueues) + min(k, nb % kMaxQueues) + blockIdx.x / kMaxQueues;
+  constexpr unsigned kPerRun = kMaxQueues * kXcdRun;
+  const unsigned base = blockIdx.x / kPerRun * kPerRun, r = blockIdx.x - base;
+  if (base + kPerRun > gridDim.x) return blockIdx.x;  // the rest in order
+  return base + r % kMaxQueues * kXcdRun + r / kMaxQueues;
 }
 
 // Layout check, and the tile table: tile_seq[t] is the sequence holding
@@ -542,7 +548,7 @@ __global__ __launch_bounds__(64 * kIxWaves) void k_ix_count2(const uint8_t* __re
 // Pass 2, scattering: a lane ranks the words of its 32 digits; the slots go back
 // through LDS to the lanes that read the words, consecutive lanes consecutive
 // words, which put them in the tile's bucket order in LDS, to be written out as occ
-// and occ_seq.  some 85M words: 342 us, 499 us when ranked by ballots; positions and
+// and occ_seq.  Some 85M words: 317 us, 499 us when ranked by ballots; positions and
 // sequences staged one after the other in half the LDS: 395 us.
 __global__ __launch_bounds__(64 * kIxWaves) void k_ix_scatter2(const uint2* __restrict__ words,
                                                                const uint8_t* __restrict__ digits,
