@@ -49,6 +49,9 @@ METRIC = "ungapped extensions/sec and bank-vs-bank wall time (plain vs batched, 
 # maxima and its LDS work is 88 bytes; counting the lookups as ALU operations
 # too gives 132 operations per pair.
 OPS_PER_EXT = 88
+MFMA_MIN_CODES = 12 * 8800          # codes of bank 1 from which the extension runs on the matrix cores
+MFMA_FLOPS_PER_EXT = 22 * 2 * 64    # 22 MFMAs of 32 x 32 x 64 per 1024 pairs
+PEAK_F6F4_TFLOPS = 256 * 4 * 2 * 32 * 32 * 64 / 32 * 2.4e9 / 1e12  # a 32 x 32 x 64 in 32 clocks of each of 1024 SIMDs
 OPS_PER_EXT_WITH_LOOKUPS = 132
 LDS_BYTES_PER_EXT = 88
 # MI355X: 256 CUs x 64 VALU lanes x 2 int16 ops per packed instruction x 2.4 GHz
@@ -66,6 +69,7 @@ ALIGN_OPS_PER_CELL = 7
 PEAK_INT32_TOPS = 256 * 64 * 2.4e9 / 1e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "ungapped_persistent_cfg1_traffic.md")
 KERNEL_SRC = os.path.join(ROOT, "paper_0804_3643_amd", "csrc", "ungapped.hip")
+MFMA_SRC = os.path.join(ROOT, "paper_0804_3643_amd", "csrc", "ungapped_mfma.h")
 
 
 def log(msg):
@@ -501,7 +505,7 @@ def run_serving(args):
         log("MISMATCH in the serving run: %s" % leg["bit_exact"])
         sys.exit(1)
     out = {"metric": "serving: p50/p99 request latency and extensions/s under Poisson arrivals",
-           "n_gpus": 1, "higher_is_better": True, "dtype": "int16 (exact, carried in binary16)",
+           "n_gpus": 1, "higher_is_better": True, "dtype": "int16 (exact, carried in binary16 and float32)",
            "data": "synthetic", "config": {"workload": leg.pop("workload"),
                                            "resident_residues": leg.pop("resident_residues"),
                                            "query_proteins": leg.pop("query_proteins")}}
@@ -667,7 +671,7 @@ def run_translated(args, plastx=False):
         "metric": "%s: ungapped extensions/s, whole step including the six-frame translation%s"
                   % (name, " of both banks" if plastx else ""),
         "value": n_ext / (ms * 1e-3), "unit": "ext/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
-        "ms_per_step": ms, "higher_is_better": True, "dtype": "int16 (exact, carried in binary16)",
+        "ms_per_step": ms, "higher_is_better": True, "dtype": "int16 (exact, carried in binary16 and float32)",
         "data": "synthetic",
         "stages_device_ms": {"translate": stage[0], "index": stage[1], "ungapped": stage[2], "gapped": stage[3]},
         "bit_exact": {"oracle_golden_whole_run": gcheck},
@@ -981,10 +985,12 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "int16 (exact, carried in binary16)",
-        "dtype_note": ("exact integer arithmetic: every score and partial sum is an integer of magnitude < 2048, "
-                       "carried in packed binary16 registers where that is exact (BLOSUM62); an int16 ungapped path "
-                       "and an int32 gapped path serve matrices outside that range"),
+        "dtype": "int16 (exact, carried in binary16 and float32)",
+        "dtype_note": ("exact integer arithmetic: every score and partial sum is an integer of magnitude < 2048, summed "
+                       "in float32 by the matrix instructions of the ungapped extension (scores halved in 6 bits, "
+                       "one-hot letters in 4) and in packed binary16 by its VALU tiles and the gapped filter, where "
+                       "that is exact (BLOSUM62); an int16 ungapped path and an int32 gapped path serve matrices "
+                       "outside that range"),
         "data": "synthetic",
         "config": {
             "workload": "PLAST-P configuration %d: %s; seeded lognormal lengths (mean 300, clamped 50-1000), "
@@ -1018,29 +1024,32 @@ def main():
         "roofline": {
             "bound": "alu", "achieved": achieved, "peak": PEAK_INT16_TOPS, "unit": "TOP/s",
             "frac": achieved / PEAK_INT16_TOPS,
-            "traffic": recorded_traffic(traffic_file("ungapped_persistent", args.config)),
-            "kernel": "k_ungapped_persistent", "ops_per_ext": OPS_PER_EXT,
+            "traffic": recorded_traffic(traffic_file("ungapped_mfma", args.config), MFMA_SRC),
+            "kernel": "k_ungapped_mfma" if w.bank1.codes.shape[0] >= MFMA_MIN_CODES else "k_ungapped_wave",
+            "ops_per_ext": OPS_PER_EXT,
             "kernel_ms": batched_kernel_ms, "extensions_per_launch": n_ext,
             "measured_peak": peaks["valu_pk_f16"]["rate"] / 1e12,
             "frac_of_measured_peak": achieved / (peaks["valu_pk_f16"]["rate"] / 1e12),
             "note": "88 algorithmic operations per extension (44 additions, 44 maxima) against 2 packed "
-                    "16-bit operations per lane per clock; the kernel's three-way maximum does two maxima "
-                    "per half in one instruction, so this fraction can pass 1 by a little: the instruction "
-                    "stream (about 41 lane instructions per extension, profiles/sq_counters_cfg1.md) uses "
-                    "about 0.9 of the VALU issue slots",
+                    "16-bit operations per lane per clock; the additions are done by the matrix cores and a "
+                    "three-way maximum takes four prefixes, so this fraction passes 1",
+            "matrix": {"bound": "mfma", "flops_per_ext": MFMA_FLOPS_PER_EXT,
+                       "achieved": achieved / OPS_PER_EXT * MFMA_FLOPS_PER_EXT, "peak": PEAK_F6F4_TFLOPS,
+                       "unit": "TFLOP/s", "frac": achieved / OPS_PER_EXT * MFMA_FLOPS_PER_EXT / PEAK_F6F4_TFLOPS,
+                       "note": "22 v_mfma_f32_32x32x64_f8f6f4 per 1024 pairs, padding not counted; with them go 176 "
+                               "v_max3_f32, which share the SIMD's issue"},
             "with_lookups_as_alu_ops": {
                 "ops_per_ext": OPS_PER_EXT_WITH_LOOKUPS,
                 "achieved": achieved * OPS_PER_EXT_WITH_LOOKUPS / OPS_PER_EXT,
                 "frac": achieved * OPS_PER_EXT_WITH_LOOKUPS / OPS_PER_EXT / PEAK_INT16_TOPS,
-                "note": "counts the 44 substitution lookups per pair as ALU operations; the kernel serves them "
-                        "from LDS (one ds_read_b64 gives 4 rows), so this fraction can exceed 1 and the VALU "
-                        "(88 ops) and LDS (88 bytes) fractions are the binding ones"},
+                "note": "counts the 44 substitution lookups per pair as ALU operations; the matrix cores' operands "
+                        "or the LDS serve them, so this fraction exceeds 1"},
             "lds": {"bound": "lds", "achieved": lds_achieved, "peak": PEAK_LDS_TBS, "unit": "TB/s",
                     "frac": lds_achieved / PEAK_LDS_TBS, "bytes_per_ext": LDS_BYTES_PER_EXT,
                     "measured_peak": peaks["lds_b64"]["rate"] / 1e12,
                     "frac_of_measured_peak": lds_achieved / (peaks["lds_b64"]["rate"] / 1e12),
-                    "note": "profile lookups: 44 scores of 2 bytes per pair, read 4 rows at a time with "
-                            "ds_read_b64, against 256 B per CU per clock"},
+                    "note": "profile lookups of the VALU tiles: 44 scores of 2 bytes per pair, read 4 rows at a time "
+                            "with ds_read_b64, against 256 B per CU per clock"},
             "gapped": {"bound": "alu", "kernel": "k_gapped_f16", "achieved": gapped_achieved,
                        "peak": PEAK_INT16_TOPS, "unit": "TOP/s", "frac": gapped_achieved / PEAK_INT16_TOPS,
                        "kernel_ms": gapped_kernel_ms, "dp_cells": cells, "ops_per_cell": GAPPED_OPS_PER_CELL,
