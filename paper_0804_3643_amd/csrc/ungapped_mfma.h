@@ -32,17 +32,18 @@
 // 2k, of the upper half those of step 2k + 1 (s+); slots 20..29 are the letters
 // 0..9 (lower half) and 10..19 (upper half) of step 2k - 1 (s-).  The rows of an
 // item (two tiles of 32) are laid out in LDS once (33.8 KB a tile) and read by
-// every wavefront in order, 24 bytes a lane per MFMA; a wavefront keeps the
-// one-hot operands of 32 columns in 88 registers over both tiles and gets them
-// from two 168-byte tables in LDS, without bank conflicts; it builds those of one
-// side at a time (48 registers, then 40).  78 KB per workgroup of 4 wavefronts: two
-// workgroups on a compute unit, so that one works while the other builds its
-// profile.
+// every wavefront in order, 24 bytes a lane per MFMA; a wavefront builds the one-hot
+// operands of 32 columns from two 168-byte tables in LDS, without bank conflicts, one
+// side at a time (48 registers, then 40), and uses them for both tiles.  78 KB per
+// workgroup of 4 wavefronts: two workgroups on a compute unit, so that one works while
+// the other builds its profile.
 //
 // Measured: 10,000 x 100,000 proteins (1.65e10 pairs) 12.8 ms, 19.6 on the VALU tile
 // alone; 1,001 proteins against 1.5M fragments 1.31 and 1.75 ms.  A tile takes about
 // 1900 cycles of a SIMD: 1050 for the MFMAs and maxima, 400 for the columns of two
-// tiles (per tile half), 200 for its hits, 200 for the item's profile and end.
+// tiles (per tile half), 200 for its hits, 200 for the item's profile and end.  With few
+// rows a key and a bank b that no cache holds, the windows are the bound as well: 450
+// proteins against 1M read 60 GB of lines in 11.7 ms.
 constexpr int kMThreads = 256;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kMTile = 32;

@@ -16,15 +16,15 @@
 // place past it; while an eighth of the bank about fits one, each XCD takes the columns
 // of its eighth of the bank.
 //
-// Measured, against a workgroup per item (proteins, us): 200 x 2000 66 and 164, 30 x
-// 2000 27 and 72, 3 x 300 10 and 22, 100 x 10,000 119 and 172, 3 x 100,000 90 and 128
-// (112 without the XCDs' shares), 30 x 100,000 388 and 466 (504), 3 x 1M 1186 and 1563.
+// Measured, against a workgroup per item (proteins, us): 200 x 2000 62 and 164, 30 x
+// 2000 26 and 72, 3 x 300 10 and 22, 100 x 10,000 115 and 172, 3 x 100,000 87 and 128
+// (112 without the XCDs' shares), 30 x 100,000 361 and 466 (504), 3 x 1M 1186 and 1563.
 constexpr int kWWaves = kThreads / 64;
 constexpr int kWSlots = 512;
 // Chosen for few pairs in all, as the product of the banks' codes says, and for more
 // of them where a key has few columns or hardly a row (us here and on a workgroup per
-// item): 200 x 4000 95 and 180, 400 x 5000 172 and 209, 200 x 10,000 202 and 202 (2.6e11),
-// 1000 x 2000 189 and 237, 30 x 100,000 388 and 466, 10 x 300,000 759 and 929, 10 x 1M 2605
+// item): 200 x 4000 95 and 180, 400 x 5000 167 and 209, 200 x 10,000 202 and 202 (2.6e11),
+// 1000 x 2000 189 and 237, 30 x 100,000 361 and 466, 10 x 300,000 759 and 929, 10 x 1M 2605
 // and 3386, but 100 x 30,000 261 and 234 (3.9e11); 1000 x 5000 325 and 267, 10,000 x 2000
 // 2990 and 1250.
 constexpr double kWCodes = 2.5e11;
