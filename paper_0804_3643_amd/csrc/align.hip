@@ -39,6 +39,7 @@ namespace {
 constexpr int kANeg = -(1 << 28);
 constexpr int kSortTile = 4096;     // most radix-sort elements per tile (one wavefront, 64 per lane)
 constexpr int kSortMin = 512;       // and fewest
+constexpr int64_t kByWork = 100;    // most passing hits a wavefront for which pairs are taken by work
 constexpr int kTStride = 32;        // entries per row of the LDS score table
 constexpr int kWall = -16256;       // table entry of any pair with the sentinel letter (low byte 0x80: -128 as 8 bits)
 constexpr int kYScale = 64 * 2;     // bytes per letter row of the per-lane profile (64 int16)
@@ -1045,19 +1046,26 @@ int align_impl(const plast_index_t* a, const plast_index_t* b, const plast_hit_t
     exclusive_scan_i32(pcount, (m + 63) / 64, &hdr->group_total, ws + L.scan_tmp, s);
     hipLaunchKernelGGL(k_align_heads, dim3(mb), dim3(256), 0, s, A, d_hits, skey, sval, shift, m,
                        (const int32_t*)pcount, heads, key[cur ^ 1]);
-    hipLaunchKernelGGL(k_rs_count, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1], 0, m,
-                       (const int32_t*)&hdr->group_total, tile, counts, tiles);
-    exclusive_scan_i32(counts, 256 * tiles, &hdr->sort_total, ws + L.scan_tmp, s);
-    hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1],
-                       (const int32_t*)heads, 0, m, (const int32_t*)&hdr->group_total, tile, (const int32_t*)counts,
-                       tiles, (uint64_t*)nullptr, order);
+    // Few pairs a wavefront: the largest first, so that the last to start are short
+    // (26 hits a wavefront: kernel 2.37 ms, 2.50 in order).  With many, the order of
+    // sequences is worth more (350 a wavefront: 27.6 ms in order, 28.0), since
+    // wavefronts then read the same bank-a sequence together.
+    const bool by_work = m <= kByWork * waves;
+    if (by_work) {
+      hipLaunchKernelGGL(k_rs_count, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1], 0, m,
+                         (const int32_t*)&hdr->group_total, tile, counts, tiles);
+      exclusive_scan_i32(counts, 256 * tiles, &hdr->sort_total, ws + L.scan_tmp, s);
+      hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)tiles), dim3(64), 0, s, (const uint64_t*)key[cur ^ 1],
+                         (const int32_t*)heads, 0, m, (const int32_t*)&hdr->group_total, tile, (const int32_t*)counts,
+                         tiles, (uint64_t*)nullptr, order);
+    }
     const size_t lds = align_lds_bytes(p->max_len2);
     PLAST_HIP(hipFuncSetAttribute((const void*)k_align, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int16_t* tbl = (int16_t*)(ws + L.tbl);
     hipLaunchKernelGGL(k_align_table, dim3(1), dim3(64), 0, s, A, tbl);
     timing_mark(kStageAlign, false, s);
     hipLaunchKernelGGL(k_align, dim3((unsigned)waves), dim3(64), lds, s, A, (const int16_t*)tbl, d_hits, sval,
-                       skey, shift, m, (const int32_t*)order, hdr, tb, L.tb_words_per_wave, pieces,
+                       skey, shift, m, (const int32_t*)(by_work ? order : heads), hdr, tb, L.tb_words_per_wave, pieces,
                        (int2*)(ws + L.strip), d_out, d_cover);
     timing_mark(kStageAlign, true, s);
     PLAST_HIP(hipGetLastError());
