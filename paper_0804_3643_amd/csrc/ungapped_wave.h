@@ -7,9 +7,10 @@
 // hands out items, about 12 ns each on one address, takes as long as the pairs.
 // Here every wavefront takes items of its own, by striding over the list: 16
 // wavefronts on a compute unit, each with the profile of 4 rows at a time (7 KB of
-// LDS), no barrier before the end, and the hits of a workgroup's wavefronts staged
-// together and written with one global atomic.  Bound by the latency of the loads
-// that an item begins with (work list, key table, occurrences, letters).
+// LDS) and a staging area for its hits, and no barrier before the end, when the hits
+// that are left in a workgroup are written with one global atomic.  Bound by the
+// latency of the loads that an item begins with (work list, key table, occurrences,
+// letters).
 //
 // A list of fewer items than wavefronts is cut further, into slices of the items'
 // columns.  Where bank b is larger than an L2, a column's window comes from a random
@@ -20,7 +21,6 @@
 // 2000 26 and 72, 3 x 300 10 and 22, 100 x 10,000 115 and 172, 3 x 100,000 87 and 128
 // (112 without the XCDs' shares), 30 x 100,000 361 and 466 (504), 3 x 1M 1186 and 1563.
 constexpr int kWWaves = kThreads / 64;
-constexpr int kWSlots = 512;
 // Chosen for few pairs in all, as the product of the banks' codes says, and for more
 // of them where a key has few columns or hardly a row (us here and on a workgroup per
 // item): 200 x 4000 95 and 180, 400 x 5000 167 and 209, 200 x 10,000 202 and 202 (2.6e11),
@@ -40,14 +40,22 @@ constexpr int kWMatRow = 22;                        // entries of a matrix row i
 constexpr int kWRows = 8;                           // rows of an item that a wavefront takes at a time
 constexpr int kWSlices = 16;                        // most slices of an item's columns
 
+// Hits are staged by each wavefront as occurrence indexes and a score: as many as a
+// group of 64 columns and 4 rows can have, so that a group always fits an empty area.
+// (One area of 512 a workgroup, written out at the end alone, left every group that found
+// it full an atomic of its own, 14 ns each on the one counter: 200 x 10,000 proteins at a
+// threshold of 25 instead of 38 took 1.92 ms, 0.24 now.)
+constexpr int kWSlots = 4 * 64;
 struct __align__(16) WSmem {
   uint8_t prof[kWWaves][kProfRG];      // 8-byte entries
   uint16_t mat[kNLet * kWMatRow];      // profile values (int16 or binary16 bits)
-  int32_t hit_a[kWSlots], hit_b[kWSlots], hit_score[kWSlots];  // occurrence indexes
-  int32_t n_hit;                       // slots reserved
-  int32_t n_fit;                       // start of the reservation that straddles the end
+  int32_t hit_a[kWWaves][kWSlots], hit_b[kWWaves][kWSlots];
+  uint16_t hit_score[kWWaves][kWSlots];
+  int32_t n_hit[kWWaves];              // staged when the wavefront has ended
   unsigned long long base;
 };
+static_assert(sizeof(WSmem) <= 80 * 1024, "two workgroups on a compute unit");
+static_assert(kSpan * 128 < 1 << 16, "a staged score has 16 bits");
 
 __device__ __forceinline__ void w_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -55,71 +63,70 @@ __device__ __forceinline__ void w_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The record of a pair of occurrences.
-__device__ __forceinline__ void w_write(const UngappedArgs& A, unsigned long long at, int oa, int ob, int score) {
-  if (at >= (unsigned long long)A.capacity) return;
-  plast_hit_t h;
-  h.seq1 = A.a.occ_seq[oa];
-  h.pos1 = A.a.occ[oa] - (int)A.a.seq_start[h.seq1];
-  h.seq2 = A.b.occ_seq[ob];
-  h.pos2 = A.b.occ[ob] - (int)A.b.seq_start[h.seq2];
-  h.score = score;
-  A.hits[at] = h;
+// Writes a wavefront's staged hits 0 .. n - 1 at hits[base ..).
+__device__ __forceinline__ void w_write(const UngappedArgs& A, const WSmem& S, int wid, int n,
+                                        unsigned long long base) {
+  for (int e = __lane_id(); e < n; e += 64) {
+    if (base + e >= (unsigned long long)A.capacity) continue;
+    const int oa = S.hit_a[wid][e], ob = S.hit_b[wid][e];
+    plast_hit_t h;
+    h.seq1 = A.a.occ_seq[oa];
+    h.pos1 = A.a.occ[oa] - (int)A.a.seq_start[h.seq1];
+    h.seq2 = A.b.occ_seq[ob];
+    h.pos2 = A.b.occ[ob] - (int)A.b.seq_start[h.seq2];
+    h.score = S.hit_score[wid][e];
+    A.hits[base + e] = h;
+  }
 }
 
-// The hits of one column per lane against 4 rows (row r of register r / 2): staged
-// if the wavefront's all fit, written directly if not.  All lanes call it.
+// Stages the hits of one column per lane against 4 rows (row r of register r / 2)
+// after the n staged before, which are written out first, with one global atomic, if
+// the new ones do not fit beside them.  Returns how many are staged then.  All lanes
+// call it.
 template <bool F16>
-__device__ __forceinline__ void w_hits(const UngappedArgs& A, WSmem& S, const vec2<F16> (&m)[2], uint32_t mask, int oa,
-                                       int ob) {
+__device__ __forceinline__ int w_hits(const UngappedArgs& A, WSmem& S, const vec2<F16> (&m)[2], uint32_t mask, int oa,
+                                      int ob, int wid, int n) {
   unsigned long long b[4];
   int total = 0;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     b[r] = __ballot((mask & row_bit(r)) != 0);
-    total += __popcll(b[r]);
+    total += (int)__popcll(b[r]);
   }
-  if (total == 0) return;
-  int at = 0;
-  if (__lane_id() == 0) at = atomicAdd(&S.n_hit, total);
-  at = __builtin_amdgcn_readfirstlane(at);
-  const bool staged = at + total <= kWSlots;
-  unsigned long long g = 0;
-  if (!staged) {
-    if (__lane_id() == 0) {
-      if (at < kWSlots) S.n_fit = at;
-      g = atomicAdd(A.n_hits, (unsigned long long)total);
-    }
-    g = __shfl(g, 0);
+  if (total == 0) return n;
+  if (n + total > kWSlots) {
+    w_sync();
+    unsigned long long base = 0;
+    if (__lane_id() == 0) base = atomicAdd(A.n_hits, (unsigned long long)n);
+    w_write(A, S, wid, n, __shfl(base, 0));
+    w_sync();
+    n = 0;
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[r], 0u));
     if (mask & row_bit(r)) {
-      const int score = to_int<F16>(m[r / 2], r & 1);
-      if (staged) {
-        S.hit_a[at + below] = oa + r;
-        S.hit_b[at + below] = ob;
-        S.hit_score[at + below] = score;
-      } else {
-        w_write(A, g + below, oa + r, ob, score);
-      }
+      const int at =
+          n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[r], 0u));
+      S.hit_a[wid][at] = oa + r;
+      S.hit_b[wid][at] = ob;
+      S.hit_score[wid][at] = (uint16_t)to_int<F16>(m[r / 2], r & 1);
     }
-    at += __popcll(b[r]);
-    g += __popcll(b[r]);
+    n += (int)__popcll(b[r]);
   }
+  return n;
 }
 
 // Rows row .. row + kWRows - 1 of an item (those that it has; ka and ka1: its key's
 // first occurrence in bank a and the next key's, kb: its first in bank b) against
 // the columns from .. to - 1 of the key in groups of 64, every slices-th of them.
+// n hits are staged before; returns how many are after.
 template <bool F16>
-__device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem it, int64_t ka, int64_t ka1, int64_t kb,
-                                           int row, int from, int to, int slices, int wid, WSmem& S) {
+__device__ __forceinline__ int run_item_w(const UngappedArgs& A, const WorkItem it, int64_t ka, int64_t ka1, int64_t kb,
+                                          int row, int from, int to, int slices, int wid, int n, WSmem& S) {
   const int lane = __lane_id();
   const int a0 = (int)ka + it.row0 + row, b0 = (int)kb;
   const int rows = min(min(kWRows, kTileRows - row), (int)ka1 - a0);
-  if (rows <= 0 || from >= to) return;
+  if (rows <= 0 || from >= to) return n;
   const int qrow = lane < rows ? A.a.occ[a0 + lane] : -1;
   uint8_t* prof = S.prof[wid];
   for (int r0 = 0; r0 < rows; r0 += 4) {
@@ -164,9 +171,10 @@ __device__ __forceinline__ void run_item_w(const UngappedArgs& A, const WorkItem
       }
       vec2<F16> m[2];
       scan_window<F16, 1>(prof, win, m);
-      w_hits<F16>(A, S, m, active ? (hit_mask<F16, 1>(A.thr, m) & valid) : 0u, a0 + r0, ob);
+      n = w_hits<F16>(A, S, m, active ? (hit_mask<F16, 1>(A.thr, m) & valid) : 0u, a0 + r0, ob, wid, n);
     }
   }
+  return n;
 }
 
 template <bool F16>
@@ -182,13 +190,10 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
       v = (uint16_t)A.mat[i];
     S.mat[i / kNLet * kWMatRow + i % kNLet] = v;
   }
-  if (threadIdx.x == 0) {
-    S.n_hit = 0;
-    S.n_fit = kWSlots;
-  }
   __syncthreads();
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
+  int n = 0;  // staged hits
   if (xcd) {
     // Each XCD (workgroups are dealt to them round robin) takes an eighth of every
     // key's columns, which lie in the same eighth of the bank: its L2 then serves
@@ -204,7 +209,7 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
       const int from = max(it.col0, (int)(n2 * x / kMaxQueues));
       const int to = min(it.col0 + it.ncols, (int)(n2 * (x + 1) / kMaxQueues));
       for (int row = 0; row < kTileRows; row += kWRows)
-        run_item_w<F16>(A, it, ka, ka1, kb, row, from + (int)(u / n_items) * 64, to, slices, wid, S);
+        n = run_item_w<F16>(A, it, ka, ka1, kb, row, from + (int)(u / n_items) * 64, to, slices, wid, n, S);
     }
   } else {
     // units of kWRows rows of an item, most of which have fewer rows in all
@@ -217,13 +222,20 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
       // all first units before all second ones: neighbouring wavefronts have like work
       const int i = (int)(u % n_items), part = (int)(u / n_items);
       const WorkItem it = items[i];
-      run_item_w<F16>(A, it, A.a.key_off[it.key], A.a.key_off[it.key + 1], A.b.key_off[it.key], part / slices * kWRows,
-                      it.col0 + part % slices * 64, it.col0 + it.ncols, slices, wid, S);
+      n = run_item_w<F16>(A, it, A.a.key_off[it.key], A.a.key_off[it.key + 1], A.b.key_off[it.key],
+                          part / slices * kWRows, it.col0 + part % slices * 64, it.col0 + it.ncols, slices, wid, n, S);
     }
   }
+  // what the wavefronts have left goes out with one global atomic
+  if (__lane_id() == 0) S.n_hit[wid] = n;
   __syncthreads();
-  const int n = min(S.n_hit, S.n_fit);
-  if (threadIdx.x == 0 && n > 0) S.base = atomicAdd(A.n_hits, (unsigned long long)n);
+  if (threadIdx.x == 0) {
+    int total = 0;
+    for (int w = 0; w < kWWaves; ++w) total += S.n_hit[w];
+    S.base = total ? atomicAdd(A.n_hits, (unsigned long long)total) : 0ull;
+  }
   __syncthreads();
-  for (int e = threadIdx.x; e < n; e += kThreads) w_write(A, S.base + e, S.hit_a[e], S.hit_b[e], S.hit_score[e]);
+  unsigned long long base = S.base;
+  for (int w = 0; w < wid; ++w) base += S.n_hit[w];
+  w_write(A, S, wid, n, base);
 }
