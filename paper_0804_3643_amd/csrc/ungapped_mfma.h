@@ -53,6 +53,11 @@ constexpr int kMRight = kRight / 2;           // of which rightward (12)
 constexpr int kMaxEntry = 15;                 // |score| that E2M3 holds at half its value
 constexpr int kMAhead = 4;                    // profile operands in flight
 constexpr int kMSlots = 256;                  // staged hits of a wavefront
+// Hits are counted before they are written where the staging area has filled, a
+// wavefront's groups of 32 columns have had kMHotHits on average and more than kMHotRest
+// of them are left (1000 x 30,000 proteins at thresholds of 30 and 25: 869 and 1418 us;
+// from 48 hits on 914 and 1542, from 160 on 870 and 1507).
+constexpr int kMHotHits = 96, kMHotRest = 2;
 static_assert(kRight % 2 == 0 && kNbr % 2 == 0 && kMRight % 2 == 0 && kMSteps % 2 == 0, "two steps per MFMA, two MFMAs per maximum");
 static_assert(kMSlots >= 4 * 64, "staged hits: four registers of a tile");
 static_assert(kMaxItemCols <= 1 << 14 && kMRows <= 1 << 6 && kSpan * kMaxEntry < 1 << 10, "a staged hit packs row, score and column in 30 bits");
@@ -288,16 +293,6 @@ __device__ __forceinline__ void m_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Writes a wavefront's n staged hits with a global atomic of their own.
-__device__ __forceinline__ void m_flush(const UngappedArgs& A, const MSmem& S, const WorkItem& it, int64_t b0, int wid,
-                                        int n) {
-  m_wave_sync();
-  unsigned long long base = 0;
-  if (__lane_id() == 0) base = atomicAdd(A.n_hits, (unsigned long long)n);
-  m_write(A, S, it, b0, wid, n, __shfl(base, 0));
-  m_wave_sync();
-}
-
 // Stages the hits of one accumulator register (row r in the lower half of the
 // wavefront, r + 4 in the upper) from slot n on; returns how many.
 __device__ __forceinline__ int m_stage(const UngappedArgs& A, MSmem& S, int wid, int r, int g, int n, unsigned long long hits, float score) {
@@ -311,24 +306,76 @@ __device__ __forceinline__ int m_stage(const UngappedArgs& A, MSmem& S, int wid,
   return __popcll(hits);
 }
 
-// Finishes tile t of the column group g: its hits into the staging area (n staged
-// before; returns how many are staged after).  Register i holds rows
-// 8 (i / 4) + i % 4 (lower half of the wavefront) and the ones 4 below (upper
-// half); one or two registers of a tile hold a hit, so four at a time are tested
-// first.
-__device__ __forceinline__ int m_finish(const UngappedArgs& A, MSmem& S, const WorkItem& it, int64_t b0, int wid, int g,
-                                        int t, int n, const mf16& m) {
+// The hits of a tile, counted.
+__device__ __forceinline__ int m_count(const UngappedArgs& A, const mf16& m) {
+  int total = 0;
 #pragma unroll
-  for (int i0 = 0; i0 < 16; i0 += 4) {
-    const float top = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m[i0], m[i0 + 1]), m[i0 + 2]), m[i0 + 3]);
-    const unsigned long long any = __ballot(top >= A.thrf);
-    if (!any) continue;
-    if (n + 4 * (int)__popcll(any) > kMSlots) {  // the staging area may not hold them: write it out
-      m_flush(A, S, it, b0, wid, n);
-      n = 0;
+  for (int i = 0; i < 16; ++i) total += (int)__popcll(__ballot(m[i] >= A.thrf));
+  return total;
+}
+
+// The hits of tile t of the column group g, written at hits[at ..).
+__device__ __forceinline__ void m_put(const UngappedArgs& A, const MSmem& S, const WorkItem& it, int64_t b0, int g, int t,
+                                      unsigned long long at, const mf16& m) {
+  int lane = __lane_id();
+  asm volatile("" : "+v"(lane));  // the addresses below are formed here, not kept in registers over the loop
+  const int j = g * 32 + (lane & 31);
+  const int64_t o = b0 + it.col0 + (j < it.ncols ? j : 0);  // (a column past the item's has no hit)
+  plast_hit_t h;
+  h.seq2 = A.b.occ_seq[o];
+  h.pos2 = A.b.occ[o] - (int)A.b.seq_start[h.seq2];
+  const int r0 = t * kMTile + 4 * (lane >> 5);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const unsigned long long hits = __ballot(m[i] >= A.thrf);
+    if (!hits) continue;
+    const unsigned long long to =
+        at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+    if (m[i] >= A.thrf && to < (unsigned long long)A.capacity) {
+      h.seq1 = S.rowseq[r0 + 8 * (i / 4) + i % 4];
+      h.pos1 = S.rowpos[r0 + 8 * (i / 4) + i % 4];
+      h.score = (int)m[i];
+      A.hits[to] = h;
     }
+    at += __popcll(hits);
+  }
+}
+
+// Finishes tile t of the column group g: its hits into the staging area (n staged
+// before; returns how many are staged after, and adds to `out` those written out).
+// Register i holds rows 8 (i / 4) + i % 4 (lower half of the wavefront) and the ones 4
+// below (upper half); one or two registers of a tile hold a hit, so four at a time are
+// tested first.  A tile that may not fit the area is written out with the staged hits.
+__device__ __forceinline__ int m_finish(const UngappedArgs& A, MSmem& S, const WorkItem& it, int64_t b0, int wid, int g,
+                                        int t, int n, const mf16& m, int& out) {
+  unsigned long long any[4];
+  int most = 0;
 #pragma unroll
-    for (int i = i0; i < i0 + 4; ++i) {
+  for (int k = 0; k < 4; ++k) {
+    const float top = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(m[4 * k], m[4 * k + 1]), m[4 * k + 2]), m[4 * k + 3]);
+    any[k] = __ballot(top >= A.thrf);
+    most += 4 * (int)__popcll(any[k]);
+  }
+  if (most == 0) return n;
+  if (n + most > kMSlots) {
+    const int total = m_count(A, m);
+    if (n + total > kMSlots) {
+      m_wave_sync();
+      unsigned long long base = 0;
+      if (__lane_id() == 0) base = atomicAdd(A.n_hits, (unsigned long long)(n + total));
+      base = __shfl(base, 0);
+      m_write(A, S, it, b0, wid, n, base);
+      m_put(A, S, it, b0, g, t, base + n, m);
+      m_wave_sync();
+      out += n + total;
+      return 0;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (!any[k]) continue;
+#pragma unroll
+    for (int i = 4 * k; i < 4 * k + 4; ++i) {
       const unsigned long long hits = __ballot(m[i] >= A.thrf);
       if (hits) n += m_stage(A, S, wid, t * kMTile + 8 * (i / 4) + i % 4, g, n, hits, m[i]);
     }
@@ -348,6 +395,15 @@ __device__ __forceinline__ void run_narrow(const UngappedArgs& A, const WorkItem
 
 // All threads of the workgroup call run_item_m with the same item (it contains
 // barriers).
+//
+// Hits are staged, and written out when the staging area is full or the item ends.
+// Where they are many (banks that share low-complexity words, a low threshold), that is
+// every few groups, and the atomics on the one counter, 14 ns each whoever makes them,
+// take longer than the tiles: the rest of the wavefront's groups then runs twice, to
+// count the hits and, with the room for them taken by one atomic, to write them.  1000 x
+// 30,000 proteins at a threshold of 20 (117M hits): 1.76 ms, 11.4 without, 3.60 on the
+// VALU tile; with runs over the same two letters in a tenth of both banks (1.12G hits)
+// 5.0, 58.4 and 11.4 ms.
 __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -369,46 +425,74 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
     const int j = g * 32 + c;
     return A.b.occ[b0 + it.col0 + (j < it.ncols ? j : 0)];
   };
-  int n = 0;  // staged hits
-  int q = 0, q_nxt = 0;
-  uint32_t raw[12];
-  if (wid < groups) {
-    q = occ_of(wid);
-    load_window_raw(A, q, raw);
-  }
-  if (wid + kMWaves < groups) q_nxt = occ_of(wid + kMWaves);
-  for (int g = wid; g < groups; g += kMWaves) {
-    uint32_t win[11];
-    const int sh = (q - kNbr) & 3;
-#pragma unroll
-    for (int i = 0; i < 11; ++i) win[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
-    // A column past the item's is a window of separators: it scores 0, like a
-    // row past the item's, and 0 is below the threshold.
-    if (it.ncols - g * 32 < 32) {
-#pragma unroll
-      for (int i = 0; i < 11; ++i) win[i] = g * 32 + c < it.ncols ? win[i] : kPadCode * kScale * 0x01010101u;
-    }
-    uint4 B[kMRight];
-    mf16 m0, m1;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) m0[i] = m1[i] = 0.f;
-    m_columns<true>(S, win, B);
-    if (g + kMWaves < groups) {
-      q = q_nxt;
+  enum { kStage, kCount, kWrite };
+  int mode = kStage;
+  int first = wid;                 // the group where counting began
+  int counted = 0;                 // hits from there on
+  unsigned long long at = 0;       // where they go
+  int n = 0, out = 0;              // hits staged now, and written out before
+  for (;;) {
+    int q = 0, q_nxt = 0;
+    uint32_t raw[12];
+    if (first < groups) {
+      q = occ_of(first);
       load_window_raw(A, q, raw);
     }
-    if (g + 2 * kMWaves < groups) q_nxt = occ_of(g + 2 * kMWaves);
-    const mf16 zero = m0;
-    m_side<0, kMRight>(S, 0, lane, B, zero, m0);
-    if (tiles > 1) m_side<0, kMRight>(S, 1, lane, B, zero, m1);
-    m_columns<false>(S, win, B);
-    const mf16 r0 = m0, r1 = m1;
-    m_side<kMRight, kMSteps>(S, 0, lane, B, r0, m0);
-    n = m_finish(A, S, it, b0, wid, g, 0, n, m0);
-    if (tiles > 1) {
-      m_side<kMRight, kMSteps>(S, 1, lane, B, r1, m1);
-      n = m_finish(A, S, it, b0, wid, g, 1, n, m1);
+    if (first + kMWaves < groups) q_nxt = occ_of(first + kMWaves);
+    for (int g = first; g < groups; g += kMWaves) {
+      uint32_t win[11];
+      const int sh = (q - kNbr) & 3;
+#pragma unroll
+      for (int i = 0; i < 11; ++i) win[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
+      // A column past the item's is a window of separators: it scores 0, like a
+      // row past the item's, and 0 is below the threshold.
+      if (it.ncols - g * 32 < 32) {
+#pragma unroll
+        for (int i = 0; i < 11; ++i) win[i] = g * 32 + c < it.ncols ? win[i] : kPadCode * kScale * 0x01010101u;
+      }
+      uint4 B[kMRight];
+      mf16 m0, m1;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) m0[i] = m1[i] = 0.f;
+      m_columns<true>(S, win, B);
+      if (g + kMWaves < groups) {
+        q = q_nxt;
+        load_window_raw(A, q, raw);
+      }
+      if (g + 2 * kMWaves < groups) q_nxt = occ_of(g + 2 * kMWaves);
+      const mf16 zero = m0;
+      m_side<0, kMRight>(S, 0, lane, B, zero, m0);
+      if (tiles > 1) m_side<0, kMRight>(S, 1, lane, B, zero, m1);
+      m_columns<false>(S, win, B);
+      const mf16 r0 = m0, r1 = m1;
+      auto finish = [&](int t, const mf16& m) {
+        if (mode == kStage) {
+          n = m_finish(A, S, it, b0, wid, g, t, n, m, out);
+          return;
+        }
+        const int hits = m_count(A, m);
+        if (mode == kCount) {
+          counted += hits;
+        } else if (hits) {
+          m_put(A, S, it, b0, g, t, at, m);
+          at += hits;
+        }
+      };
+      m_side<kMRight, kMSteps>(S, 0, lane, B, r0, m0);
+      finish(0, m0);
+      if (tiles > 1) {
+        m_side<kMRight, kMSteps>(S, 1, lane, B, r1, m1);
+        finish(1, m1);
+      }
+      if (mode == kStage && out > 0 && out + n >= kMHotHits * ((g >> 2) + 1) && groups - g > kMHotRest * kMWaves) {
+        mode = kCount;
+        first = g + kMWaves;
+      }
     }
+    if (mode != kCount || counted == 0) break;
+    if (lane == 0) at = atomicAdd(A.n_hits, (unsigned long long)counted);
+    at = __shfl(at, 0);
+    mode = kWrite;
   }
   // the item's hits go out with one global atomic
   if (lane == 0) S.n_hit[wid] = n;
