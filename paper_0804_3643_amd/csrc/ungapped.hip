@@ -483,33 +483,6 @@ __device__ void run_item(const UngappedArgs& A, const WorkItem it, Smem& S) {
     run_tile<F16, kRowGroups, kThreads>(A, it, a0, b0, rows, S);
 }
 
-#include "ungapped_mfma.h"
-#include "ungapped_wave.h"
-
-constexpr int kPlainCols = 4096;  // item width of the PLAIN schedule
-
-template <bool F16>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void k_ungapped_plain(UngappedArgs A, int32_t key, int32_t n_row_tiles, int32_t n2) {
-  __shared__ Smem S;
-  smem_init<F16, kThreads>(A, S);
-  __syncthreads();
-  WorkItem it;
-  it.key = key;
-  it.row0 = (int32_t)(blockIdx.x % n_row_tiles) * kTileRows;
-  it.col0 = (int32_t)(blockIdx.x / n_row_tiles) * kPlainCols;
-  it.ncols = min(kPlainCols, n2 - it.col0);
-  run_item<F16>(A, it, S);
-}
-
-// Workspace header of the BATCHED schedule: UngappedCounters at 0, queue
-// counters at 32 (kMaxQueues int32), the length of the list at 64, all set by the
-// first kernel.
-constexpr int kCtrOffset = 32;
-constexpr int kListOffset = 64;
-static_assert(sizeof(UngappedCounters) <= kCtrOffset, "counter header");
-static_assert(kCtrOffset + 4 * kMaxQueues <= kListOffset && kListOffset + 4 <= 256, "queue counters");
-
 // Pops the items of the work list until every queue is empty.
 template <typename Run>
 __device__ __forceinline__ void work_loop(int n_items, int32_t* __restrict__ ctr, int32_t n_queues, int32_t* slot,
@@ -533,6 +506,33 @@ __device__ __forceinline__ void work_loop(int n_items, int32_t* __restrict__ ctr
     }
   }
 }
+
+#include "ungapped_mfma.h"
+#include "ungapped_wave.h"
+
+constexpr int kPlainCols = 4096;  // item width of the PLAIN schedule
+
+template <bool F16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_ungapped_plain(UngappedArgs A, int32_t key, int32_t n_row_tiles, int32_t n2) {
+  __shared__ Smem S;
+  smem_init<F16, kThreads>(A, S);
+  __syncthreads();
+  WorkItem it;
+  it.key = key;
+  it.row0 = (int32_t)(blockIdx.x % n_row_tiles) * kTileRows;
+  it.col0 = (int32_t)(blockIdx.x / n_row_tiles) * kPlainCols;
+  it.ncols = min(kPlainCols, n2 - it.col0);
+  run_item<F16>(A, it, S);
+}
+
+// Workspace header of the BATCHED schedule: UngappedCounters at 0, queue
+// counters at 32 (kMaxQueues int32), the lengths of the list and of its first part and
+// the kernel that runs it at 64, all set by the first kernel.
+constexpr int kCtrOffset = 32;
+constexpr int kListOffset = 64;
+static_assert(sizeof(UngappedCounters) <= kCtrOffset, "counter header");
+static_assert(kCtrOffset + 4 * kMaxQueues <= kListOffset && kListOffset + 12 <= 256, "queue counters");
 
 template <bool F16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
@@ -561,6 +561,9 @@ struct PlanShape {
   int32_t cols[kClasses];
   uint32_t mask;  // classes that get items
   int32_t rows;   // rows of an item of the list that is run (kTileRows or kMRows)
+  int32_t large;  // rows x columns of an item, of up to kWLargeCols columns, from which its
+                  // key's items stand first in that list
+  int32_t tile;   // the kernel that runs it (Tile), for the header
 };
 
 // Column ranges of a key (occurrence counts are below 2^31: 32-bit divisions).
@@ -586,9 +589,16 @@ __host__ __device__ __forceinline__ uint32_t row_items(const PlanShape& P, int64
   return ((uint32_t)n1 + (uint32_t)P.rows - 1) / (uint32_t)P.rows;
 }
 
+// Whether a key's items stand in the first part of the list.
+__host__ __device__ __forceinline__ bool large_items(const PlanShape& P, int64_t n1, int64_t n2, int32_t width) {
+  return min(n1, (int64_t)P.rows) * min(n2, (int64_t)min(width, kWLargeCols)) >= P.large;
+}
+
 // The header and the per-key offsets of the list, by one workgroup: the counts,
-// their scan and the checks in one launch.  The list stays empty (overflow set) when it is longer than the
-// workspace holds (1) or a bank had an error (2).
+// their scan and the checks in one launch.  list_len[0] is the list's length,
+// list_len[1] that of its first part, list_len[2] the kernel that runs it.  The list
+// stays empty (overflow set) when it is longer than the workspace holds (1) or a bank
+// had an error (2).
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanPer = (kNKeys + kPlanThreads - 1) / kPlanThreads;
 
@@ -596,7 +606,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(
     const int64_t* __restrict__ a_off, const int64_t* __restrict__ b_off, PlanShape P, int32_t* __restrict__ keyoff,
     int64_t max_items, const int32_t* __restrict__ err_a, const int32_t* __restrict__ err_b,
     UngappedCounters* __restrict__ cnt, int32_t* __restrict__ ctr, int32_t* __restrict__ list_len) {
-  __shared__ int wrun[kPlanThreads / 64];
+  __shared__ int wrun[2][kPlanThreads / 64];
   __shared__ unsigned long long wext[kPlanThreads / 64], witems[kPlanThreads / 64];
   __shared__ int32_t count[kPlanPer * kPlanThreads];
   const int lane = __lane_id(), wid = threadIdx.x >> 6;
@@ -613,42 +623,54 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(
         ext += (unsigned long long)(n1 * n2);
         items += (unsigned long long)all;
         c = (int32_t)min((int64_t)row_items(P, n1) * col_items(n2, w), (int64_t)INT32_MAX);
+        if (large_items(P, n1, n2, w)) c = -c;
       }
     }
-    count[k] = c;
+    count[k] = c;  // negative for the first part
   }
   __syncthreads();
   const int k0 = threadIdx.x * kPlanPer;
-  int run[kPlanPer], sum = 0;
+  int run[kPlanPer], sum[2] = {0, 0};
 #pragma unroll
   for (int i = 0; i < kPlanPer; ++i) {
     run[i] = count[k0 + i];
-    sum += run[i];
+    sum[0] += max(-run[i], 0);
+    sum[1] += max(run[i], 0);
   }
-  int incl = sum;
+  int incl[2] = {sum[0], sum[1]};
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int t = __shfl_up(incl[x], o);
+      if (lane >= o) incl[x] += t;
+    }
     ext += __shfl_xor(ext, o);
     items += __shfl_xor(items, o);
   }
-  if (lane == 63) wrun[wid] = incl;
+  if (lane == 63) {
+    wrun[0][wid] = incl[0];
+    wrun[1][wid] = incl[1];
+  }
   if (lane == 0) {
     wext[wid] = ext;
     witems[wid] = items;
   }
   __syncthreads();
-  int at = incl - sum, total = 0;
+  int at[2] = {incl[0] - sum[0], incl[1] - sum[1]}, total[2] = {0, 0};
 #pragma unroll
   for (int w = 0; w < kPlanThreads / 64; ++w) {
-    at += w < wid ? wrun[w] : 0;
-    total += wrun[w];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      at[x] += w < wid ? wrun[x][w] : 0;
+      total[x] += wrun[x][w];
+    }
   }
 #pragma unroll
   for (int i = 0; i < kPlanPer; ++i) {
-    count[k0 + i] = at;
-    at += run[i];
+    count[k0 + i] = run[i] < 0 ? at[0] : total[0] + at[1];
+    at[0] += max(-run[i], 0);
+    at[1] += max(run[i], 0);
   }
   __syncthreads();
   for (int k = threadIdx.x; k < kNKeys; k += kPlanThreads) keyoff[k] = count[k];
@@ -663,7 +685,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(
                      ? 1
                      : (((err_a && *err_a) || (err_b && *err_b)) ? 2 : 0);
     *cnt = c;
-    *list_len = total;
+    list_len[0] = total[0] + total[1];
+    list_len[1] = total[0];
+    list_len[2] = P.tile;
   }
   if (threadIdx.x < kMaxQueues) ctr[threadIdx.x] = 0;
 }
@@ -724,7 +748,7 @@ UngappedWs carve(void* d_ws, size_t ws_bytes) {
   return W;
 }
 
-PlanShape shape_of(const plast_tuning_t& t, uint32_t mask, int rows) {
+PlanShape shape_of(const plast_tuning_t& t, uint32_t mask, int rows, int large = INT32_MAX) {
   PlanShape P;
   for (int c = 0; c < kClasses; ++c) {
     P.min_n2[c] = t.class_min_n2[c];
@@ -732,6 +756,8 @@ PlanShape shape_of(const plast_tuning_t& t, uint32_t mask, int rows) {
   }
   P.mask = mask;
   P.rows = rows;
+  P.large = large;
+  P.tile = 0;
   return P;
 }
 
@@ -898,7 +924,10 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   const Tile tile = fill_args(A, a, b, p, d_hits, capacity, &W.cnt->n_hits);
   const int grid = persistent_grid(tile);
   if (grid <= 0) return set_error(PLAST_E_HIP, "cannot query device occupancy");
-  const PlanShape P = shape_of(t, class_mask, tile == Tile::kMfma ? kMRows : kTileRows);
+  const bool wave = tile == Tile::kWaveF16 || tile == Tile::kWaveI16;
+  PlanShape P = shape_of(t, class_mask, tile == Tile::kMfma ? kMRows : kTileRows,
+                         wave ? w_large(a, b, t, grid) : INT32_MAX);
+  P.tile = (int32_t)tile;
   timing_mark(kStagePlan, false, stream);
   hipLaunchKernelGGL(k_plan_count, dim3(1), dim3(kPlanThreads), 0, stream, a->key_off, b->key_off, P, W.keycnt,
                      W.max_items, err_a, err_b, W.cnt, W.ctr, W.list_len);
@@ -911,10 +940,10 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   const bool xcd = w_shared(b);
   if (tile == Tile::kWaveF16)
     hipLaunchKernelGGL(k_ungapped_wave<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
-                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, xcd);
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues, xcd);
   else if (tile == Tile::kWaveI16)
     hipLaunchKernelGGL(k_ungapped_wave<false>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
-                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, xcd);
+                       (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues, xcd);
   else if (tile == Tile::kMfma)
     hipLaunchKernelGGL(k_ungapped_mfma, dim3(grid), dim3(kMThreads), 0, stream, A, (const WorkItem*)W.items,
                        (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues);

@@ -36,6 +36,17 @@ constexpr int64_t kWXcdMin = 512 * (int64_t)kNKeys, kWXcdMax = 64000000;
 inline bool w_shared(const plast_index_t* b) { return b->n_padded >= kWXcdMin && b->n_padded <= kWXcdMax; }
 constexpr int64_t kWMaxCols = 200;                  // codes of bank b per key
 
+// Keys whose items are large (many rows of many columns) are left to the workgroups, as
+// in the kernel of an item per workgroup, once their wavefronts have ended: the 32-row
+// tile reads a window once for 32 rows instead of 4, and shares an item of many hits
+// between 8 wavefronts.  Banks whose sequences share low-complexity words have a few such
+// keys whatever their size.  Rows x columns of an item from which that pays, where a
+// wavefront takes up to half of an item's columns (200 x 10,000 proteins 148 us, from
+// 8192 on 141, from 32768 164, and 189 with none; 30 x 100,000 285, 351, 299 and 350; 10 x
+// 300,000 742, 766, 765 and 755), and more where it takes fewer.  With runs over the same
+// two letters in a tenth of 200 x 10,000 proteins 0.97 ms, 4.5 with no such keys.
+constexpr int kWLarge = 16384;
+constexpr int kWLargeCols = 4096;  // columns of an item that count: the wider ones of 1 to 3 rows stay
 constexpr int kWMatRow = 22;                        // entries of a matrix row in LDS: dwords of two letters
 constexpr int kWRows = 8;                           // rows of an item that a wavefront takes at a time
 constexpr int kWSlices = 16;                        // most slices of an item's columns
@@ -46,6 +57,24 @@ constexpr int kWSlices = 16;                        // most slices of an item's 
 // it full an atomic of its own, 14 ns each on the one counter: 200 x 10,000 proteins at a
 // threshold of 25 instead of 38 took 1.92 ms, 0.24 now.)
 constexpr int kWSlots = 4 * 64;
+
+// Slices of an item's columns in a list of n_items.  A wavefront of the launch takes 1 of
+// `waves` items, or those of its XCD's eighth of the columns.
+__host__ __device__ inline int w_slices(bool xcd, int64_t waves, int64_t n_items) {
+  return (int)min((int64_t)kWSlices, 1 + (xcd ? 8 : 4) * waves / max(n_items, (int64_t)1));
+}
+
+// PlanShape::large, for as many items as banks of ordinary sequences make.
+inline int w_large(const plast_index_t* a, const plast_index_t* b, const plast_tuning_t& t, int grid) {
+  const int64_t n2 = b->n_padded / kNKeys;
+  int c = 0;
+  for (int i = 1; i < kClasses; ++i)
+    if (n2 >= t.class_min_n2[i]) c = i;
+  const int64_t n_items = min(a->n_padded, (int64_t)kNKeys) * (n2 / t.item_cols[c] + 1);
+  const bool xcd = w_shared(b);
+  return kWLarge * max(w_slices(xcd, (int64_t)grid * kWWaves / (xcd ? kMaxQueues : 1), n_items) / 2, 1);
+}
+
 struct __align__(16) WSmem {
   uint8_t prof[kWWaves][kProfRG];      // 8-byte entries
   uint16_t mat[kNLet * kWMatRow];      // profile values (int16 or binary16 bits)
@@ -180,8 +209,12 @@ __device__ __forceinline__ int run_item_w(const UngappedArgs& A, const WorkItem 
 template <bool F16>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4)))
 void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const UngappedCounters* __restrict__ cnt,
-                     const int32_t* __restrict__ list_len, bool xcd) {
-  __shared__ WSmem S;
+                     const int32_t* __restrict__ list_len, int32_t* __restrict__ ctr, int32_t n_queues, bool xcd) {
+  __shared__ union {
+    WSmem wave;
+    Smem group;
+  } L;
+  WSmem& S = L.wave;
   for (int i = threadIdx.x; i < kNLet * kNLet; i += kThreads) {
     uint16_t v;
     if constexpr (F16)
@@ -192,7 +225,10 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
   }
   __syncthreads();
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : *list_len);
+  const int n_large = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : list_len[1]);
+  const int n_items = __builtin_amdgcn_readfirstlane(cnt->overflow ? 0 : list_len[0]) - n_large;
+  const WorkItem* __restrict__ large = items;
+  items += n_large;
   int n = 0;  // staged hits
   if (xcd) {
     // Each XCD (workgroups are dealt to them round robin) takes an eighth of every
@@ -200,7 +236,7 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
     // most windows.  A unit is a slice of an item's columns there.
     const int x = blockIdx.x % kMaxQueues;
     const int waves = ((int)gridDim.x - x + kMaxQueues - 1) / kMaxQueues * kWWaves;
-    const int slices = min(kWSlices, 1 + 8 * waves / max(n_items, 1));
+    const int slices = w_slices(true, waves, n_items);
     const int64_t n_units = (int64_t)n_items * slices;
     for (int64_t u = (int64_t)(blockIdx.x / kMaxQueues) * kWWaves + wid; u < n_units; u += waves) {
       const WorkItem it = items[u % n_items];
@@ -216,7 +252,7 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
     constexpr int kUnits = kTileRows / kWRows;
     const int64_t stride = (int64_t)gridDim.x * kWWaves;
     // and of a slice of its columns where the list has few items for the wavefronts
-    const int slices = (int)min((int64_t)kWSlices, 1 + 4 * stride / max(n_items, 1));
+    const int slices = w_slices(false, stride, n_items);
     const int64_t n_units = (int64_t)n_items * kUnits * slices;
     for (int64_t u = (int64_t)blockIdx.x * kWWaves + wid; u < n_units; u += stride) {
       // all first units before all second ones: neighbouring wavefronts have like work
@@ -238,4 +274,8 @@ void k_ungapped_wave(UngappedArgs A, const WorkItem* __restrict__ items, const U
   unsigned long long base = S.base;
   for (int w = 0; w < wid; ++w) base += S.n_hit[w];
   w_write(A, S, wid, n, base);
+  if (n_large == 0) return;
+  __syncthreads();
+  smem_init<F16, kThreads>(A, L.group);  // its barrier comes with the first item
+  work_loop(n_large, ctr, n_queues, &L.group.item, [&](int i) { run_item<F16>(A, large[i], L.group); });
 }

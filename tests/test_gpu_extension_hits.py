@@ -15,8 +15,9 @@ from paper_0804_3643_amd import synth
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
 
-# Words that banks a and b are brought to with runs of one letter, another one in each.
-PATHS = {"wave": (0, 0), "matrix": (120_000, 2_700_000)}
+# Words that banks a and b are brought to with runs of one letter, another one in each, and the kernel that must run
+# (0: matrix cores, 3: an item per wavefront, in binary16).
+PATHS = {"wave": (0, 0, 3), "wave_many_rows": (12_000, 0, 3), "matrix": (120_000, 2_700_000, 0)}
 
 
 @pytest.fixture(scope="module")
@@ -35,6 +36,16 @@ def _banks(path, a, b):
     return _filled(a, PATHS[path][0], "M"), _filled(b, PATHS[path][1], "K")
 
 
+def _extend(B, ia, ib, s1, path, **kw):
+    """The hits and pairs of a call, whose workspace header says which kernel ran and how many items it has in all and as
+    large ones."""
+    e = B.Extender(ia, ib, s1, **kw)
+    hits, n_ext = e.run()
+    head = e.ws[64:76].view(torch.int32).tolist()
+    assert head[2] == PATHS[path][2], head
+    return hits, n_ext, head[0], head[1]
+
+
 def _indexes(B, *banks):
     return [B.build_index(*B.bank_to_device(b, "cuda")) for b in banks]
 
@@ -51,7 +62,8 @@ def _word_seqs(rng, n, word=RICH):
 
 
 # The counts of columns around a group and a staging area, and keys of several items.
-@pytest.mark.parametrize("rows,cols", [(1, 64), (1, 257), (4, 64), (4, 65), (4, 640), (9, 700), (40, 1300), (70, 5000)])
+@pytest.mark.parametrize("rows,cols", [(1, 64), (1, 257), (4, 64), (4, 65), (4, 640), (9, 700), (40, 1300), (70, 5000),
+                                       (3, 6000), (5, 4200), (33, 500), (64, 520)])
 @pytest.mark.parametrize("path", PATHS)
 def test_every_pair_a_hit(B, path, rows, cols):
     rng = np.random.default_rng(rows + cols)
@@ -59,8 +71,10 @@ def test_every_pair_a_hit(B, path, rows, cols):
     ia, ib = _indexes(B, a, b)
     ref, ref_ext = C.ungapped_hits(a, b, 42, matrix=O.BLOSUM62)
     for tuning in (None, {"item_cols": [512] * 4, "xcd_queues": 8}):
-        hits, n_ext = B.ungapped_extend(ia, ib, 42, tuning=tuning)
+        hits, n_ext, items, large = _extend(B, ia, ib, 42, path, tuning=tuning)
         assert n_ext == ref_ext and len(ref) >= rows * cols
+        if path == "wave_many_rows":  # the word's key has large items where 16384 pairs fit one
+            assert (large > 0) == (min(rows, 32) * min(cols, 512 if tuning else 4096) >= 16384) and large < items
         assert np.array_equal(B.canonical_hits(hits), ref)
 
 
@@ -74,7 +88,7 @@ def test_hits_in_part_of_a_key(B, path, order):
     a, b = _banks(path, _word_seqs(rng, 50), cols)
     ia, ib = _indexes(B, a, b)
     ref, ref_ext = C.ungapped_hits(a, b, 42, matrix=O.BLOSUM62)
-    hits, n_ext = B.ungapped_extend(ia, ib, 42, tuning={"item_cols": [4096] * 4, "xcd_queues": 8})
+    hits, n_ext, _, _ = _extend(B, ia, ib, 42, path, tuning={"item_cols": [4096] * 4, "xcd_queues": 8})
     assert n_ext == ref_ext and 125_000 <= len(ref) < 150_000
     assert np.array_equal(B.canonical_hits(hits), ref)
 
@@ -100,9 +114,13 @@ def test_capacity_is_kept(B, path, capacity):
     assert len(kept) == capacity and kept <= {tuple(r) for r in ref.tolist()}
 
 
-def _proteins(rng, n, mean=300):
+def _proteins(rng, n, runs=0.0):
+    """n proteins; in a share of them a run of 200 letters over two."""
     p = synth.BACKGROUND / synth.BACKGROUND.sum()
-    return [rng.choice(20, size=int(k), p=p).astype(np.uint8) for k in rng.integers(mean // 2, 3 * mean // 2, n)]
+    seqs = [rng.choice(20, size=int(k), p=p).astype(np.uint8) for k in rng.integers(200, 401, n)]
+    for s in seqs[:round(runs * n)]:
+        s[:200] = rng.choice([0, 2], 200)
+    return seqs
 
 
 def _kernel_ms(B, ia, ib, s1, reps=5):
@@ -118,10 +136,13 @@ def _kernel_ms(B, ia, ib, s1, reps=5):
     return min(t)
 
 
-# Times the kernel's time at the default threshold that a lower one may take: 1.3 and 2.6 measured (the pairs, and writing
-# the hits), and 10 where an atomic on the one counter serves a few hundred hits at most.
-@pytest.mark.parametrize("n1,n2,s1,times", [(200, 10_000, 25, 3.0), (500, 20_000, 20, 6.0)])
-def test_time_with_many_hits(B, n1, n2, s1, times):
+# Times the kernel's time on ordinary proteins at the default threshold that a lower threshold, or runs over the same two
+# letters in both banks, may take.  Measured: 1.4, 2.6, 7.9 and 2.4, the pairs and writing the hits; 10, 10, 24 and 16 where an
+# atomic on the one counter serves a few hundred hits at most, or one wavefront has all of a key's columns.
+@pytest.mark.parametrize("n1,n2,s1,runs,times", [(200, 10_000, 25, 0.0, 3.0), (500, 20_000, 20, 0.0, 6.0),
+                                                 (200, 10_000, 38, 0.1, 12.0), (500, 20_000, 38, 0.05, 8.0)])
+def test_time_with_many_hits(B, n1, n2, s1, runs, times):
     rng = np.random.default_rng(3)
-    ia, ib = _indexes(B, *(synth.Bank.from_seqs(_proteins(rng, n)) for n in (n1, n2)))
-    assert _kernel_ms(B, ia, ib, s1) < times * _kernel_ms(B, ia, ib, 38)
+    usual = _indexes(B, *(synth.Bank.from_seqs(_proteins(rng, n)) for n in (n1, n2)))
+    ia, ib = _indexes(B, *(synth.Bank.from_seqs(_proteins(rng, n, runs)) for n in (n1, n2)))
+    assert _kernel_ms(B, ia, ib, s1) < times * _kernel_ms(B, *usual, 38)
