@@ -425,13 +425,9 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
     const int j = g * 32 + c;
     return A.b.occ[b0 + it.col0 + (j < it.ncols ? j : 0)];
   };
-  enum { kStage, kCount, kWrite };
-  int mode = kStage;
-  int first = wid;                 // the group where counting began
-  int counted = 0;                 // hits from there on
-  unsigned long long at = 0;       // where they go
-  int n = 0, out = 0;              // hits staged now, and written out before
-  for (;;) {
+  // The groups from `first` on: finish(g, t, scores of tile t), and after each group
+  // last(g), until that returns true.
+  auto scan = [&](int first, auto finish, auto last) {
     int q = 0, q_nxt = 0;
     uint32_t raw[12];
     if (first < groups) {
@@ -465,34 +461,44 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
       if (tiles > 1) m_side<0, kMRight>(S, 1, lane, B, zero, m1);
       m_columns<false>(S, win, B);
       const mf16 r0 = m0, r1 = m1;
-      auto finish = [&](int t, const mf16& m) {
-        if (mode == kStage) {
-          n = m_finish(A, S, it, b0, wid, g, t, n, m, out);
-          return;
-        }
-        const int hits = m_count(A, m);
-        if (mode == kCount) {
-          counted += hits;
-        } else if (hits) {
-          m_put(A, S, it, b0, g, t, at, m);
-          at += hits;
-        }
-      };
       m_side<kMRight, kMSteps>(S, 0, lane, B, r0, m0);
-      finish(0, m0);
+      finish(g, 0, m0);
       if (tiles > 1) {
         m_side<kMRight, kMSteps>(S, 1, lane, B, r1, m1);
-        finish(1, m1);
+        finish(g, 1, m1);
       }
-      if (mode == kStage && out > 0 && out + n >= kMHotHits * ((g >> 2) + 1) && groups - g > kMHotRest * kMWaves) {
-        mode = kCount;
-        first = g + kMWaves;
-      }
+      if (last(g)) return;
     }
-    if (mode != kCount || counted == 0) break;
-    if (lane == 0) at = atomicAdd(A.n_hits, (unsigned long long)counted);
-    at = __shfl(at, 0);
-    mode = kWrite;
+  };
+  int n = 0, out = 0;              // hits staged now, and written out before
+  int rest = groups;               // the group from which the hits are counted first
+  scan(wid, [&](int g, int t, const mf16& m) { n = m_finish(A, S, it, b0, wid, g, t, n, m, out); },
+       [&](int g) {
+         if (out == 0 || out + n < kMHotHits * ((g >> 2) + 1) || groups - g <= kMHotRest * kMWaves) return false;
+         rest = g + kMWaves;
+         return true;
+       });
+  if (rest < groups) {
+    int counted = 0;
+    unsigned long long at = 0;     // where they go
+    bool write = false;
+    for (;;) {
+      scan(rest,
+           [&](int g, int t, const mf16& m) {
+             const int hits = m_count(A, m);
+             if (!write) {
+               counted += hits;
+             } else if (hits) {
+               m_put(A, S, it, b0, g, t, at, m);
+               at += hits;
+             }
+           },
+           [](int) { return false; });
+      if (write || counted == 0) break;
+      if (lane == 0) at = atomicAdd(A.n_hits, (unsigned long long)counted);
+      at = __shfl(at, 0);
+      write = true;
+    }
   }
   // the item's hits go out with one global atomic
   if (lane == 0) S.n_hit[wid] = n;
