@@ -52,6 +52,7 @@
 #include <vector>
 
 #include "plast_internal.h"
+#include "ungapped_route.h"
 
 namespace plast {
 
@@ -507,6 +508,8 @@ __device__ __forceinline__ void work_loop(int n_items, int32_t* __restrict__ ctr
   }
 }
 
+double words_of(const plast_index_t* x) { return bank_words(x->n_padded, x->n_seqs); }
+
 #include "ungapped_mfma.h"
 #include "ungapped_wave.h"
 
@@ -798,16 +801,11 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
     const uint16_t h = (uint16_t)(int16_t)t;
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   }
-  // Small banks: an item per wavefront.
-  const double codes2 = (double)a->n_padded * (double)b->n_padded;
-  if (codes2 <= kWCodes || (codes2 <= kWMaxCodes && b->n_padded < kWMaxCols * kNKeys) || a->n_padded < kNKeys / 2 ||
-      (w_shared(b) && a->n_padded < 3 * kNKeys / 2))
-    return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
-  // The matrix-core tile counts on pairs of score 0 not being hits, and pays
-  // from about 12 rows a key on: against 100,000 proteins, a query of 450 (143,000
-  // codes) takes 1.25 ms on it and 1.39 on the VALU tiles, one of 200 (64,000) 0.91
-  // and 0.82.
-  return maxabs <= kMaxEntry && p->s1 >= 1 && a->n_padded >= (int64_t)kMMinRows * kNKeys ? Tile::kMfma : (f16 ? Tile::kF16 : Tile::kI16);
+  switch (ungapped_route(words_of(a), words_of(b), b->n_padded, p->s1 >= 1 && maxabs <= kMaxEntry)) {
+    case Route::kWave: return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
+    case Route::kMatrix: return Tile::kMfma;  // (counts on pairs of score 0 not being hits)
+    default: return f16 ? Tile::kF16 : Tile::kI16;
+  }
 }
 
 // Workgroups of a persistent kernel resident on the device at once (0 on error).
@@ -937,7 +935,7 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
-  const bool xcd = w_shared(b);
+  const bool xcd = columns_shared(b->n_padded);
   if (tile == Tile::kWaveF16)
     hipLaunchKernelGGL(k_ungapped_wave<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
                        (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues, xcd);

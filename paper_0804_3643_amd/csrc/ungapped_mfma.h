@@ -74,7 +74,6 @@ typedef uint32_t mu4 __attribute__((ext_vector_type(4)));
 // 100,000 proteins: 0.21 ms without the rule, 0.14 with it; 450 proteins against 1M:
 // 12.3 and 11.6 ms (limits of 8, 12 and 16 rows within 1%).
 constexpr int kMNarrow = 8;
-constexpr int kMMinRows = 12;                 // codes of bank a per key from which the kernel is chosen
 static_assert(kMNarrow == 8, "run_narrow has tiles of 4 and 8 rows");
 
 struct __align__(16) MSmem {

@@ -17,25 +17,10 @@
 // place past it; while an eighth of the bank about fits one, each XCD takes the columns
 // of its eighth of the bank.
 //
-// Measured, against a workgroup per item (proteins, us): 200 x 2000 62 and 164, 30 x
-// 2000 26 and 72, 3 x 300 10 and 22, 100 x 10,000 115 and 172, 3 x 100,000 87 and 128
-// (112 without the XCDs' shares), 30 x 100,000 361 and 466 (504), 3 x 1M 1186 and 1563.
+// Measured, against a workgroup per item (proteins, us): 200 x 2000 63 and 162, 30 x
+// 2000 28 and 72, 3 x 300 14 and 22, 100 x 10,000 103 and 175, 3 x 100,000 88 and 130
+// (112 without the XCDs' shares), 30 x 100,000 290 and 466 (418), 3 x 1M 1116 and 1533.
 constexpr int kWWaves = kThreads / 64;
-// Chosen for few pairs in all, as the product of the banks' codes says, and for more
-// of them where a key has few columns or hardly a row (us here and on a workgroup per
-// item): 200 x 4000 95 and 180, 400 x 5000 167 and 209, 200 x 10,000 202 and 202 (2.6e11),
-// 1000 x 2000 189 and 237, 30 x 100,000 361 and 466, 10 x 300,000 759 and 929, 10 x 1M 2605
-// and 3386, but 100 x 30,000 261 and 234 (3.9e11); 1000 x 5000 325 and 267, 10,000 x 2000
-// 2990 and 1250.
-constexpr double kWCodes = 2.5e11;
-constexpr double kWMaxCodes = 4e11;
-// Codes of bank b from which the XCDs share its columns (512 a key: an XCD's share of a
-// key is a group of 64; 100 x 10,000, fewer, would take 135 us instead of 123), and up
-// to which (300,000 proteins, 1.1e8 codes, 338 and 342 us; 1M 1454 and 1187).
-constexpr int64_t kWXcdMin = 512 * (int64_t)kNKeys, kWXcdMax = 64000000;
-inline bool w_shared(const plast_index_t* b) { return b->n_padded >= kWXcdMin && b->n_padded <= kWXcdMax; }
-constexpr int64_t kWMaxCols = 200;                  // codes of bank b per key
-
 // Keys whose items are large (many rows of many columns) are left to the workgroups, as
 // in the kernel of an item per workgroup, once their wavefronts have ended: the 32-row
 // tile reads a window once for 32 rows instead of 4, and shares an item of many hits
@@ -43,9 +28,13 @@ constexpr int64_t kWMaxCols = 200;                  // codes of bank b per key
 // keys whatever their size.  Rows x columns of an item from which that pays, where a
 // wavefront takes up to half of an item's columns (200 x 10,000 proteins 148 us, from
 // 8192 on 141, from 32768 164, and 189 with none; 30 x 100,000 285, 351, 299 and 350; 10 x
-// 300,000 742, 766, 765 and 755), and more where it takes fewer.  With runs over the same
-// two letters in a tenth of 200 x 10,000 proteins 0.97 ms, 4.5 with no such keys.
+// 300,000 742, 766, 765 and 755), more where it takes fewer, and three times as many
+// where there are few pairs in all, as the product of the words says, since what is left
+// to the end then takes as long as all else (100 proteins x 60,000 fragments 50 and 56
+// us).  With runs over the same two letters in a tenth of 200 x 10,000 proteins 0.97 ms,
+// 4.5 with no such keys.
 constexpr int kWLarge = 16384;
+constexpr double kWFew = 3e10;
 constexpr int kWLargeCols = 4096;  // columns of an item that count: the wider ones of 1 to 3 rows stay
 constexpr int kWMatRow = 22;                        // entries of a matrix row in LDS: dwords of two letters
 constexpr int kWRows = 8;                           // rows of an item that a wavefront takes at a time
@@ -66,13 +55,14 @@ __host__ __device__ inline int w_slices(bool xcd, int64_t waves, int64_t n_items
 
 // PlanShape::large, for as many items as banks of ordinary sequences make.
 inline int w_large(const plast_index_t* a, const plast_index_t* b, const plast_tuning_t& t, int grid) {
-  const int64_t n2 = b->n_padded / kNKeys;
+  const int64_t n2 = (int64_t)(words_of(b) / kNKeys);
   int c = 0;
   for (int i = 1; i < kClasses; ++i)
     if (n2 >= t.class_min_n2[i]) c = i;
-  const int64_t n_items = min(a->n_padded, (int64_t)kNKeys) * (n2 / t.item_cols[c] + 1);
-  const bool xcd = w_shared(b);
-  return kWLarge * max(w_slices(xcd, (int64_t)grid * kWWaves / (xcd ? kMaxQueues : 1), n_items) / 2, 1);
+  const int64_t n_items = min((int64_t)words_of(a), (int64_t)kNKeys) * (n2 / t.item_cols[c] + 1);
+  const bool xcd = columns_shared(b->n_padded);
+  const int slices = w_slices(xcd, (int64_t)grid * kWWaves / (xcd ? kMaxQueues : 1), n_items);
+  return kWLarge * max(slices / 2, 1) * (words_of(a) * words_of(b) < kWFew ? 3 : 1);
 }
 
 struct __align__(16) WSmem {

@@ -17,7 +17,7 @@ pytestmark = [pytest.mark.gpu,
 
 # Words that banks a and b are brought to with runs of one letter, another one in each, and the kernel that must run
 # (0: matrix cores, 3: an item per wavefront, in binary16).
-PATHS = {"wave": (0, 0, 3), "wave_many_rows": (12_000, 0, 3), "matrix": (120_000, 2_700_000, 0)}
+PATHS = {"wave": (0, 0, 3), "wave_many_rows": (12_000, 2_600_000, 3), "matrix": (120_000, 2_700_000, 0)}
 
 
 @pytest.fixture(scope="module")
