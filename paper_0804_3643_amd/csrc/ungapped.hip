@@ -801,7 +801,10 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
     const uint16_t h = (uint16_t)(int16_t)t;
     A.thr = (uint32_t)h | ((uint32_t)h << 16);
   }
-  switch (ungapped_route(words_of(a), words_of(b), b->n_padded, p->s1 >= 1 && maxabs <= kMaxEntry)) {
+  int equal = 0;
+  for (int x = 0; x < 20; ++x) equal += A.mat[x * kNLet + x];
+  switch (ungapped_route(words_of(a), words_of(b), b->n_padded, p->s1 >= 1 && maxabs <= kMaxEntry,
+                         low_threshold(p->s1, equal))) {
     case Route::kWave: return f16 ? Tile::kWaveF16 : Tile::kWaveI16;
     case Route::kMatrix: return Tile::kMfma;  // (counts on pairs of score 0 not being hits)
     default: return f16 ? Tile::kF16 : Tile::kI16;

@@ -31,8 +31,13 @@ enum class Route {
   kMatrix,  // an item per workgroup, on the matrix cores
 };
 
+// Whether a threshold is so low that a quarter and more of ordinary pairs are hits: below
+// three and a half times the matrix's mean score of equal letters (20.3 for BLOSUM62;
+// equal: their sum over the 20 letters).
+inline bool low_threshold(int32_t s1, int equal) { return 40 * (int64_t)s1 < 7 * (int64_t)equal; }
+
 // words1 and words2: of banks a and b; codes2: of bank b; matrix: the matrix cores hold
-// the scores.
+// the scores; low: of the threshold.
 //
 // An item per wavefront where there are few pairs in all, as the product of the words
 // says, and more of them where a key has few columns (us there, and on a workgroup per
@@ -45,6 +50,12 @@ enum class Route {
 // 6.9 2544, 2623 and 2448.  The same by words with fragments as bank a: 4.6 rows against
 // 60,000 proteins 371, 410 and 455, 9.2 566, 565 and 575.
 //
+// Not at a low threshold, unless there are few pairs or rows: a wavefront there writes its
+// hits out by the 256, each time with an atomic on their one counter (200 x 10,000
+// proteins at thresholds of 20, 16 and 12: 443, 941 and 1252 us, by workgroup 419, 570 and
+// 645; 200 x 2000 at 12 360 and 249; 1000 x 2000 at 16 1061, 489 and on the matrix cores
+// 601; but 30 x 100,000, where a workgroup's tile has no more rows, 2029 and 3044).
+//
 // The matrix cores from 12 rows a key on (against 30,000 proteins 10.0 rows 360 and 378,
 // 11.9 396 and 397, 16 484 and 456), and from fewer where bank b is large and its windows
 // are the bound, which the 64 rows of an item share (10.0 rows against 80,000 proteins
@@ -52,10 +63,12 @@ enum class Route {
 constexpr double kWavePairs = 2.15e11, kWaveMorePairs = 3.4e11, kWaveMoreCols = 185;
 constexpr double kFewRows = 8, kFewRowsLarge = 4.5, kManyRows = 12;
 constexpr int64_t kLargeCodes = 24000000;
-inline Route ungapped_route(double words1, double words2, int64_t codes2, bool matrix) {
+constexpr double kLowRows = 4, kLowPairs = 2e10;
+inline Route ungapped_route(double words1, double words2, int64_t codes2, bool matrix, bool low) {
   const double rows = words1 / kRouteKeys, cols = words2 / kRouteKeys, pairs = words1 * words2;
   const double few = codes2 > kXcdMaxCodes ? kFewRowsLarge : kFewRows;
-  if (rows < few || pairs <= kWavePairs || (pairs <= kWaveMorePairs && cols < kWaveMoreCols)) return Route::kWave;
+  if (rows < few || pairs <= kWavePairs || (pairs <= kWaveMorePairs && cols < kWaveMoreCols))
+    return low && rows >= kLowRows && pairs >= kLowPairs ? Route::kGroup : Route::kWave;
   return matrix && (rows >= kManyRows || codes2 >= kLargeCodes) ? Route::kMatrix : Route::kGroup;
 }
 

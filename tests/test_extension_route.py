@@ -20,19 +20,20 @@ def rules(tmp_path_factory):
     src.write_text("""
 #include <stdio.h>
 #include "ungapped_route.h"
-int main() {  // lines of: codes and sequences of bank a, of bank b, whether the matrix cores hold the scores
+int main() {  // lines of: codes and sequences of bank a, of bank b, whether the matrix cores hold the scores, threshold
   long long ca, cb;
-  int na, nb, m;
-  while (scanf("%lld %d %lld %d %d", &ca, &na, &cb, &nb, &m) == 5) {
+  int na, nb, m, s1;
+  while (scanf("%lld %d %lld %d %d %d", &ca, &na, &cb, &nb, &m, &s1) == 6) {
+    const bool low = plast::low_threshold(s1, 116);  // BLOSUM62's diagonal
     const double a = plast::bank_words(ca, na), b = plast::bank_words(cb, nb);
-    printf("%.0f %.0f %d %d\\n", a, b, (int)plast::ungapped_route(a, b, cb, m != 0), (int)plast::columns_shared(cb));
+    printf("%.0f %.0f %d %d\\n", a, b, (int)plast::ungapped_route(a, b, cb, m != 0, low), (int)plast::columns_shared(cb));
   }
 }
 """)
     subprocess.check_call(["g++", "-std=c++17", "-I" + CSRC, str(src), "-o", str(exe)])
 
     def ask(*rows):
-        text = "".join("%d %d %d %d %d\n" % r for r in rows)
+        text = "".join("%d %d %d %d %d %d\n" % (*r, *((38,) if len(r) == 5 else ())) for r in rows)
         out = subprocess.run([str(exe)], input=text, capture_output=True, text=True, check=True).stdout
         return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
     return ask
@@ -68,6 +69,18 @@ def test_route_by_words(rules, length1, words1, words2, expected):
     held, other = rules((*a, *b, 1), (*a, *b, 0))
     assert held[2] == expected
     assert other[2] == (GROUP if expected == MATRIX else expected)
+
+
+@pytest.mark.parametrize("words1,words2,expected", [
+    (60_000, 3_000_000, GROUP), (300_000, 600_000, GROUP), (60_000, 600_000, GROUP),  # rows and pairs enough
+    (60_000, 300_000, WAVE), (8_000, 30_000_000, WAVE),                               # few pairs, few rows
+    (120_000, 9_000_000, MATRIX), (90_000, 9_000_000, GROUP)])                        # as at any threshold
+def test_route_at_low_thresholds(rules, words1, words2, expected):
+    a, b = _bank(words1, 300), _bank(words2, 300)
+    got = [r[2] for r in rules(*((*a, *b, 1, s1) for s1 in (-5, 1, 20, 21, 38)))]
+    assert got[:3] == [expected] * 3 and got[3] == got[4] == rules((*a, *b, 1))[0][2]
+    if expected != GROUP or words2 == 9_000_000:
+        assert got[3] == expected
 
 
 def test_shared_columns(rules):
