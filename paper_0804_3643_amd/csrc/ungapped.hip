@@ -938,7 +938,7 @@ int ungapped_enqueue_batched(const plast_index_t* a, const plast_index_t* b, con
   timing_mark(kStagePlan, true, stream);
   timing_mark(kStageUngapped, false, stream);
   if (ev0) PLAST_HIP(hipEventRecord(ev0, stream));
-  const bool xcd = columns_shared(b->n_padded);
+  const bool xcd = columns_shared(b->n_padded, grid);
   if (tile == Tile::kWaveF16)
     hipLaunchKernelGGL(k_ungapped_wave<true>, dim3(grid), dim3(kThreads), 0, stream, A, (const WorkItem*)W.items,
                        (const UngappedCounters*)W.cnt, (const int32_t*)W.list_len, W.ctr, (int32_t)t.xcd_queues, xcd);

@@ -21,9 +21,13 @@ inline double bank_words(int64_t n_padded, int32_t n_seqs) {
 // eighth of bank b, as the bank's codes say: from the size that a few L2s hold (100 x
 // 10,000 proteins, 3.2M codes, 103 us, shared 126; 100 x 30,000, 9.5M, 216 and 198; 30 x
 // 300,000 fragments, 10.8M, 80 and 71), and while an eighth about fits one (3 x 100,000,
-// 32M, 112 and 88; 3 x 1M 1126 and 1398).
+// 32M, 112 and 88; 3 x 1M 1126 and 1398).  A launch of fewer workgroups than XCDs would
+// have none for some eighths.
 constexpr int64_t kXcdMinCodes = 4500000, kXcdMaxCodes = 64000000;
-inline bool columns_shared(int64_t codes2) { return codes2 >= kXcdMinCodes && codes2 <= kXcdMaxCodes; }
+constexpr int kXcds = 8;
+inline bool columns_shared(int64_t codes2, int64_t workgroups) {
+  return codes2 >= kXcdMinCodes && codes2 <= kXcdMaxCodes && workgroups >= kXcds;
+}
 
 enum class Route {
   kWave,    // an item per wavefront

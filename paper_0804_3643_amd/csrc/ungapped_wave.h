@@ -21,6 +21,7 @@
 // 2000 28 and 72, 3 x 300 14 and 22, 100 x 10,000 103 and 175, 3 x 100,000 88 and 130
 // (112 without the XCDs' shares), 30 x 100,000 290 and 466 (418), 3 x 1M 1116 and 1533.
 constexpr int kWWaves = kThreads / 64;
+static_assert(kXcds == kMaxQueues, "an eighth of the columns, and a queue, an XCD");
 // Keys whose items are large (many rows of many columns) are left to the workgroups, as
 // in the kernel of an item per workgroup, once their wavefronts have ended: the 32-row
 // tile reads a window once for 32 rows instead of 4, and shares an item of many hits
@@ -60,7 +61,7 @@ inline int w_large(const plast_index_t* a, const plast_index_t* b, const plast_t
   for (int i = 1; i < kClasses; ++i)
     if (n2 >= t.class_min_n2[i]) c = i;
   const int64_t n_items = min((int64_t)words_of(a), (int64_t)kNKeys) * (n2 / t.item_cols[c] + 1);
-  const bool xcd = columns_shared(b->n_padded);
+  const bool xcd = columns_shared(b->n_padded, grid);
   const int slices = w_slices(xcd, (int64_t)grid * kWWaves / (xcd ? kMaxQueues : 1), n_items);
   return kWLarge * max(slices / 2, 1) * (words_of(a) * words_of(b) < kWFew ? 3 : 1);
 }
