@@ -44,15 +44,17 @@
 // which no window reaches (about 5% of the band).
 //
 // General path (narrower bands, larger entries or costs): the same shifted
-// recurrence, anti-diagonal maxima and pair table in int32 (table entries in
-// int16), one lane per side of a hit: the lower half of a wavefront takes the right
-// sides of 32 hits, the upper half their left sides, whose letters run backward.
-// A cell is 6 instructions (the score's half of a table entry is sign-extended by
-// the addition), so a side costs about 1.35 of a packed one.  It is compiled for
-// the even bands and masks the outermost cells for the odd ones and 0.  Measured on
-// 390,000 hits, against one lane per hit with its windows as bytes in LDS and no
-// shift: band 10, window 40 0.43 -> 0.15 ms; band 4, window 64 0.68 -> 0.12; band 16
-// with costs past the packed path's 0.58 -> 0.36.
+// recurrence and anti-diagonal maxima in int32, one lane per side of a hit: the lower
+// half of a wavefront takes the right sides of 32 hits, the upper half their left
+// sides, whose letters run backward.  A cell is 6 instructions, so a side costs about
+// 1.35 of a packed one.  It is compiled for the even bands and masks the outermost cells
+// for the odd ones and 0.  The scores are int32 in LDS: one a lookup up to band 12 (1.8
+// KB), two beyond (74 KB, which allows the two wavefronts a SIMD that the registers of
+// these bands do).  Measured on 390,000 hits, against one lane per hit with its windows
+// as bytes in LDS and no shift: band 10, window 40 0.46 -> 0.16 ms; band 4, window 64 0.71
+// -> 0.13; band 16 with costs past the packed path's 0.62 -> 0.35.  On 1.6M hits by one and
+// by two scores a lookup: band 4 0.49 and 0.53 ms, 8 0.76 and 0.81, 12 1.10 and 1.10, 16
+// 1.52 and 1.40.
 #include <type_traits>
 
 #include "plast_internal.h"
@@ -64,7 +66,7 @@ namespace {
 constexpr int kGMaxWin = 64;
 constexpr int kGMaxBand = 16;
 constexpr int kGCells = 2 * kGMaxBand + 1;  // 33
-constexpr int kWallScore = -16000;          // of a separator: any value <= 0 works that an int16 holds with 2 extend
+constexpr int kWallScore = -16000;          // of a separator: any value works that is <= 0 with 2 extend
 constexpr int kNeg = -(1 << 28);
 
 struct GappedArgs {
@@ -74,7 +76,7 @@ struct GappedArgs {
   const int64_t* b_seq_start;
   int32_t a_nseq, b_nseq;
   int32_t window, band, gap_open, gap_extend, s2, pad_;
-  int16_t mat[kNLet * kNLet];     // [x letter][y letter], score + 2 extend (general path)
+  int32_t mat[kNLet * kNLet];     // [x letter][y letter], score + 2 extend (general path)
   uint16_t tbl16[kNLet * kNLet];  // binary16 [x letter][y letter], -inf where either is the separator (20)
 };
 
@@ -127,11 +129,19 @@ __device__ __forceinline__ uint32_t load4(const uint8_t* __restrict__ buf, int64
 __device__ __forceinline__ uint32_t byte_of(uint32_t v, int k) { return (v >> (8 * k)) & 0xffu; }
 
 // ---------------------------------------------------------------- general path
+// What a lookup gives: the score of an x letter against one y letter, or against two
+// consecutive ones, in the order of (x, y) or (x, y1, y2).
+constexpr int kOneScore = 12;  // up to this band one score
+template <int BAND>
+using Scores = typename std::conditional<BAND <= kOneScore, int, int2>::type;
+template <int BAND>
+constexpr int kScores = BAND <= kOneScore ? kNLet * kNLet : kPairDwords;
+
 // One side of a hit on one lane: lx x lx letters from qa and ly from qb, forward
 // or (back) backward from the letters before them.  All lanes of a wavefront call
 // it together.
 template <int BAND, bool MASK>
-__device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* tbl, int64_t qa, int64_t qb, int lx,
+__device__ __forceinline__ int gapped_side(const GappedArgs& G, const Scores<BAND>* tbl, int64_t qa, int64_t qb, int lx,
                                            int ly, bool back) {
   constexpr int kCells = 2 * BAND + 1;
   constexpr int kY = kCells + kFBlock;  // y letters held for a block of rows
@@ -146,10 +156,19 @@ __device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* 
   };
   const int op = G.gap_open, ex = G.gap_extend;
   int H[kCells], F[kCells];
-  // YY[k]: pair-table offset of the letters at y indices i0 + k - BAND - 1 and
-  // i0 + k - BAND for the block at row i0; ylast: the last letter of the last pair
-  uint32_t YY[kY - 1];
+  // YY[k]: table offset of the letter at y index i0 + k - BAND - 1 for the block at row
+  // i0, or of it and the next one (then YY[kY - 1] is unused, and ylast the last letter)
+  constexpr bool kOne = BAND <= kOneScore;
+  constexpr uint32_t kXRow = (uint32_t)(sizeof(Scores<BAND>) * kScores<BAND> / kNLet);
+  uint32_t YY[kY];
   uint32_t ylast = kPadCode;
+  auto put = [&](int k, uint32_t y) {  // the letter at k
+    if (kOne)
+      YY[k] = y * 4u;
+    else if (k > 0)
+      YY[k - 1] = ylast * (uint32_t)(kNLet * 8) + y * 8u;
+    ylast = y;
+  };
   // row 0 (shifted): H(0, 0) = 0, H(0, j) + j * extend = -open for 0 < j <= band; F holds F(1, j)
 #pragma unroll
   for (int d = 0; d < kCells; ++d) {
@@ -163,18 +182,14 @@ __device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* 
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int k = 4 * g + t;
-      if (k < kY) {
-        const uint32_t y = letter(w, t, k - BAND, ly);
-        if (k > 0) YY[k - 1] = ylast * (uint32_t)(kNLet * 4) + y * 4u;
-        ylast = y;
-      }
+      if (k < kY) put(k, letter(w, t, k - BAND, ly));
     }
   }
   uint32_t xb[kFBlock];
   {
     const uint32_t w = letters(G.a_scan, qa, 0);
 #pragma unroll
-    for (int r = 0; r < kFBlock; ++r) xb[r] = letter(w, r, r, lx) * kXRowBytes;
+    for (int r = 0; r < kFBlock; ++r) xb[r] = letter(w, r, r, lx) * kXRow;
   }
   int best = 0;  // H(0, 0): the empty alignment
   // best shifted value per anti-diagonal i + j = 2 i0 - BAND + t of the current block
@@ -192,10 +207,15 @@ __device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* 
     const uint32_t ny = letters(G.b_scan, qb, k0);
     // table lookups (one per two cells) are issued kAhead pairs ahead
     constexpr int kPairs = (kCells + 1) / 2, kSeq = kFBlock * kPairs, kAhead = 5;
-    uint32_t sc[kSeq];
+    int2 sc[kSeq];
     auto issue = [&](int q) {
       const int r = q / kPairs, p = q % kPairs;
-      sc[q] = *(const uint32_t*)(tb + (xb[r] + YY[2 * p + r]));
+      if (kOne) {
+        sc[q].x = *(const int*)(tb + (xb[r] + YY[2 * p + r]));
+        sc[q].y = 2 * p + 1 < kCells ? *(const int*)(tb + (xb[r] + YY[2 * p + r + 1])) : 0;
+      } else {
+        sc[q] = *(const int2*)(tb + (xb[r] + YY[2 * p + r]));
+      }
     };
 #pragma unroll
     for (int q = 0; q < kAhead; ++q) issue(q);
@@ -212,7 +232,7 @@ __device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* 
         // cell (i0 + r, d) lies on anti-diagonal t; in an odd row it shares it with
         // cell d + 2 of the row above, still in H[d + 2]
         const int t = 2 * r + d;
-        const int s = (int)(int16_t)(sc[q] >> (16 * c));
+        const int s = c ? sc[q].y : sc[q].x;
         const int f = d + 1 < kCells ? F[d + 1] : kNeg;
         int h = max(max(H[d] + s, e), f);
         if (MASK && (d < 2 || d >= kCells - 2)) h = abs(d - BAND) > G.band ? kNeg : h;
@@ -232,13 +252,11 @@ __device__ __forceinline__ int gapped_side(const GappedArgs& G, const uint32_t* 
 #pragma unroll
     for (int t = 0; t < kAcc; ++t) acc[t] = t + kDone < kAcc ? acc[t + kDone] : kNeg;
 #pragma unroll
-    for (int k = 0; k + kFBlock < kY - 1; ++k) YY[k] = YY[k + kFBlock];
+    for (int k = 0; k + kFBlock < kY; ++k) YY[k] = YY[k + kFBlock];
 #pragma unroll
     for (int t = 0; t < kFBlock; ++t) {
-      const uint32_t y = letter(ny, t, k0 + t, ly);
-      YY[kY - 1 - kFBlock + t] = ylast * (uint32_t)(kNLet * 4) + y * 4u;
-      ylast = y;
-      xb[t] = letter(nx, t, i0 - 1 + kFBlock + t, lx) * kXRowBytes;
+      put(kY - kFBlock + t, letter(ny, t, k0 + t, ly));
+      xb[t] = letter(nx, t, i0 - 1 + kFBlock + t, lx) * kXRow;
     }
   }
 #pragma unroll
@@ -253,10 +271,14 @@ template <int BAND, bool MASK>
 __global__ __launch_bounds__(kGThreads) void k_gapped(GappedArgs G, const plast_hit_t* __restrict__ hits,
                                                       int64_t n_hits, const unsigned long long* __restrict__ n_dev,
                                                       int32_t* __restrict__ gscore, uint8_t* __restrict__ pass) {
-  __shared__ uint32_t tbl[kPairDwords];
-  for (int i = threadIdx.x; i < kPairDwords; i += kGThreads) {
-    const int x = i / kPairRow, y1 = (i / kNLet) % kNLet, y2 = i % kNLet;
-    tbl[i] = (uint32_t)(uint16_t)G.mat[x * kNLet + y1] | ((uint32_t)(uint16_t)G.mat[x * kNLet + y2] << 16);
+  __shared__ Scores<BAND> tbl[kScores<BAND>];
+  for (int i = threadIdx.x; i < kScores<BAND>; i += kGThreads) {
+    if constexpr (BAND <= kOneScore) {
+      tbl[i] = G.mat[i];
+    } else {
+      const int x = i / kPairRow, y1 = (i / kNLet) % kNLet, y2 = i % kNLet;
+      tbl[i] = make_int2(G.mat[x * kNLet + y1], G.mat[x * kNLet + y2]);
+    }
   }
   if (n_dev) n_hits = min(n_hits, (int64_t)*n_dev);
   __syncthreads();
@@ -796,7 +818,7 @@ int gapped_filter_impl(const plast_index_t* a, const plast_index_t* b, const pla
   int maxabs = 0;
   for (int x = 0; x < kNLet; ++x)
     for (int y = 0; y < kNLet; ++y) {
-      G.mat[x * kNLet + y] = (int16_t)(((x < 20 && y < 20) ? m[x * 20 + y] : kWallScore) + 2 * g->gap_extend);
+      G.mat[x * kNLet + y] = ((x < 20 && y < 20) ? m[x * 20 + y] : kWallScore) + 2 * g->gap_extend;
       if (x < 20 && y < 20) maxabs = max(maxabs, abs((int)m[x * 20 + y]));
     }
   const uint16_t ninf16 = 0xFC00;  // binary16 -inf
