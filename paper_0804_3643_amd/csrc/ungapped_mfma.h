@@ -341,12 +341,13 @@ __device__ __forceinline__ void m_put(const UngappedArgs& A, const MSmem& S, con
 }
 
 // Finishes tile t of the column group g: its hits into the staging area (n staged
-// before; returns how many are staged after, and adds to `out` those written out).
+// before; returns how many are staged after).  `out` counts those written out; once they
+// are many, `end`, which the groups go up to, becomes the next one.
 // Register i holds rows 8 (i / 4) + i % 4 (lower half of the wavefront) and the ones 4
 // below (upper half); one or two registers of a tile hold a hit, so four at a time are
 // tested first.  A tile that may not fit the area is written out with the staged hits.
 __device__ __forceinline__ int m_finish(const UngappedArgs& A, MSmem& S, const WorkItem& it, int64_t b0, int wid, int g,
-                                        int t, int n, const mf16& m, int& out) {
+                                        int t, int n, const mf16& m, int& out, int& end) {
   unsigned long long any[4];
   int most = 0;
 #pragma unroll
@@ -367,6 +368,7 @@ __device__ __forceinline__ int m_finish(const UngappedArgs& A, MSmem& S, const W
       m_put(A, S, it, b0, g, t, base + n, m);
       m_wave_sync();
       out += n + total;
+      if (out >= kMHotHits * ((g >> 2) + 1) && end - g > kMHotRest * kMWaves) end = g + 1;
       return 0;
     }
   }
@@ -424,9 +426,8 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
     const int j = g * 32 + c;
     return A.b.occ[b0 + it.col0 + (j < it.ncols ? j : 0)];
   };
-  // The groups from `first` on: finish(g, t, scores of tile t), and after each group
-  // last(g), until that returns true.
-  auto scan = [&](int first, auto finish, auto last) {
+  // The groups from `first` on, below `end`: finish(g, t, scores of tile t).
+  auto scan = [&](int first, const int& end, auto finish) {
     int q = 0, q_nxt = 0;
     uint32_t raw[12];
     if (first < groups) {
@@ -434,7 +435,7 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
       load_window_raw(A, q, raw);
     }
     if (first + kMWaves < groups) q_nxt = occ_of(first + kMWaves);
-    for (int g = first; g < groups; g += kMWaves) {
+    for (int g = first; g < end; g += kMWaves) {
       uint32_t win[11];
       const int sh = (q - kNbr) & 3;
 #pragma unroll
@@ -466,23 +467,18 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
         m_side<kMRight, kMSteps>(S, 1, lane, B, r1, m1);
         finish(g, 1, m1);
       }
-      if (last(g)) return;
     }
   };
   int n = 0, out = 0;              // hits staged now, and written out before
-  int rest = groups;               // the group from which the hits are counted first
-  scan(wid, [&](int g, int t, const mf16& m) { n = m_finish(A, S, it, b0, wid, g, t, n, m, out); },
-       [&](int g) {
-         if (out == 0 || out + n < kMHotHits * ((g >> 2) + 1) || groups - g <= kMHotRest * kMWaves) return false;
-         rest = g + kMWaves;
-         return true;
-       });
-  if (rest < groups) {
+  int end = groups;
+  scan(wid, end, [&](int g, int t, const mf16& m) { n = m_finish(A, S, it, b0, wid, g, t, n, m, out, end); });
+  if (end < groups) {
+    const int rest = end - 1 + kMWaves;
     int counted = 0;
     unsigned long long at = 0;     // where they go
     bool write = false;
     for (;;) {
-      scan(rest,
+      scan(rest, groups,
            [&](int g, int t, const mf16& m) {
              const int hits = m_count(A, m);
              if (!write) {
@@ -491,8 +487,7 @@ __device__ void run_item_m(const UngappedArgs& A, const WorkItem it, MSmem& S) {
                m_put(A, S, it, b0, g, t, at, m);
                at += hits;
              }
-           },
-           [](int) { return false; });
+           });
       if (write || counted == 0) break;
       if (lane == 0) at = atomicAdd(A.n_hits, (unsigned long long)counted);
       at = __shfl(at, 0);
