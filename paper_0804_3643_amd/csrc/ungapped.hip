@@ -31,8 +31,10 @@
 // item with one global atomic (a wavefront whose reservation does not fit the
 // staging area writes directly).  Order of hits is unspecified.
 //
-// The BATCHED schedule runs matrices of small entries and banks of enough rows a
-// key on the matrix cores instead (ungapped_mfma.h), on items of 64 rows.
+// The BATCHED schedule has two more kernels (the rules of the choice are in
+// ungapped_route.h): banks of few pairs or few rows a key take an item per wavefront
+// (ungapped_wave.h), and matrices of small entries, with banks of enough rows a key, the
+// matrix cores, on items of 64 rows (ungapped_mfma.h).
 //
 // Schedules.  PLAIN: one grid per key with candidate pairs, in key order, one
 // item of 4096 columns per workgroup (the paper's one-launch-per-seed GPU
@@ -83,7 +85,6 @@ struct BankView {
 struct UngappedArgs {
   BankView a, b;
   uint32_t thr;                // packed pair: threshold - 1 (int16 or f16)
-  int32_t s1;
   plast_hit_t* hits;
   int64_t capacity;
   unsigned long long* n_hits;
@@ -772,7 +773,6 @@ Tile fill_args(UngappedArgs& A, const plast_index_t* a, const plast_index_t* b, 
                plast_hit_t* d_hits, int64_t capacity, unsigned long long* n_hits) {
   A.a = BankView{a->key_off, a->occ, a->occ_seq, a->scan_codes, a->seq_start};
   A.b = BankView{b->key_off, b->occ, b->occ_seq, b->scan_codes, b->seq_start};
-  A.s1 = p->s1;
   A.hits = d_hits;
   A.capacity = capacity;
   A.n_hits = n_hits;

@@ -14,9 +14,10 @@
 // the 24 rightward steps, then 10 for the leftward ones, whose chain starts
 // from the best of the right side (the composition of the VALU tile).  Two
 // C(k) enter one v_max3_f32, 8 a lane per MFMA, which is what bounds the
-// kernel: an MFMA takes 32 cycles of the matrix core and 8 v_max3_f32 with the MFMA's
-// issue 42 cycles of a SIMD (measured with nothing else in the loop, 2
-// wavefronts per SIMD), 21 a step, where the VALU tile needs 60.
+// kernel: an MFMA takes 33 to 37 cycles of a SIMD by itself, with 8 v_max3_f32 of
+// unrelated registers 43, and with the accumulators of the step before kept for its
+// maxima, as here, 47 (measured with nothing else in the loop, 2 wavefronts per SIMD):
+// 24 a step, where the VALU tile needs 60.
 //
 // Exactness.  The profile holds score / 2 in 6 bits (E2M3, multiples of 1/2 up
 // to 7.5: every integer score up to 15 in magnitude, kMaxEntry; other matrices
@@ -38,12 +39,12 @@
 // workgroup of 4 wavefronts: two workgroups on a compute unit, so that one works while
 // the other builds its profile.
 //
-// Measured: 10,000 x 100,000 proteins (1.65e10 pairs) 12.8 ms, 19.6 on the VALU tile
-// alone; 1,001 proteins against 1.5M fragments 1.31 and 1.75 ms.  A tile takes about
-// 1900 cycles of a SIMD: 1050 for the MFMAs and maxima, 400 for the columns of two
-// tiles (per tile half), 200 for its hits, 200 for the item's profile and end.  With few
+// Measured: 10,000 x 100,000 proteins (1.65e10 pairs) 12.8 ms, 19.2 on the VALU tile
+// alone; 1,001 proteins against 1.5M fragments 1.25 and 1.81 ms.  A tile takes about
+// 1950 cycles of a SIMD: 1050 for the MFMAs and maxima, the rest for the one-hot
+// operands of its columns, its hits, and the item's profile and end.  With few
 // rows a key and a bank b that no cache holds, the windows are the bound as well: 450
-// proteins against 1M read 60 GB of lines in 11.7 ms.
+// proteins against 1M read 60 GB of lines in 10.9 ms.
 constexpr int kMThreads = 256;
 constexpr int kMWaves = kMThreads / 64;
 constexpr int kMTile = 32;
@@ -70,7 +71,7 @@ typedef uint32_t mu4 __attribute__((ext_vector_type(4)));
 // An item of kMNarrow rows at most (the rest of a key, or a key of a small query
 // bank) takes the VALU tile, whose cost goes with its 4-row groups (about 330
 // cycles of a SIMD each per 32 x 32 pairs' columns), while a tile here costs about
-// 1900 for any rows, 500 of them for its columns.  A 3-protein query against
+// 1950 for any rows.  A 3-protein query against
 // 100,000 proteins: 0.21 ms without the rule, 0.14 with it; 450 proteins against 1M:
 // 12.3 and 11.6 ms (limits of 8, 12 and 16 rows within 1%).
 constexpr int kMNarrow = 8;
@@ -86,7 +87,6 @@ struct __align__(16) MSmem {
     };
     SmemT<kMNarrow / 4> narrow;
   };
-//      // profile operands: dwords 0..2 and 3..5 of each lane
   uint4 row[2][kNLet + 1];         // s and s+ of a bank-a letter, slots 0..19
   uint4 prev[2][kNLet + 1];        // s-, slots 20..29 (dwords 3, 4, 5), by half; entry kNLet: none
   union {
