@@ -17,9 +17,9 @@ reported:
   * bank-vs-bank wall time from host-resident encoded banks to the host hit
     list (host-to-device copy, both indexes, ungapped, gapped, device-to-host),
     for both schedules;
-  * ``roofline`` for the dominant kernel (the persistent ungapped kernel):
-    algorithmic int16 ALU operations (44 additions and 44 maxima per
-    extension) per second against the packed-int16 VALU peak;
+  * ``roofline`` for the ungapped kernel that ran (as the library says): on the
+    matrix cores the MFMAs' operations against their peak, on the VALU 44
+    additions and 44 maxima per extension against the packed 16-bit peak;
   * ``stage32``: stage 3.2 (full gapped alignment, with the list of pieces of
     computed alignments) over the hits that pass the filter, outside the step:
     wall time of the call, DP cells per second, and the C oracle on a seeded
@@ -46,13 +46,10 @@ METRIC = "ungapped extensions/sec and bank-vs-bank wall time (plain vs batched, 
 # Ungapped extension, per candidate pair: 44 scan steps, each one substitution
 # lookup, one addition and one maximum.  The kernel serves the lookups from an
 # LDS profile (2 bytes per step), so its VALU work is the 88 additions and
-# maxima and its LDS work is 88 bytes; counting the lookups as ALU operations
-# too gives 132 operations per pair.
+# maxima and its LDS work is 88 bytes.
 OPS_PER_EXT = 88
-MFMA_MIN_CODES = 12 * 8800          # codes of bank 1 from which the extension runs on the matrix cores
 MFMA_FLOPS_PER_EXT = 22 * 2 * 64    # 22 MFMAs of 32 x 32 x 64 per 1024 pairs
 PEAK_F6F4_TFLOPS = 256 * 4 * 2 * 32 * 32 * 64 / 32 * 2.4e9 / 1e12  # a 32 x 32 x 64 in 32 clocks of each of 1024 SIMDs
-OPS_PER_EXT_WITH_LOOKUPS = 132
 LDS_BYTES_PER_EXT = 88
 # MI355X: 256 CUs x 64 VALU lanes x 2 int16 ops per packed instruction x 2.4 GHz
 PEAK_INT16_TOPS = 256 * 64 * 2 * 2.4e9 / 1e12
@@ -67,21 +64,56 @@ GAPPED_OPS_PER_CELL = 8
 # diagonal add; two maxima for H) against 256 CUs x 64 VALU lanes x 2.4 GHz
 ALIGN_OPS_PER_CELL = 7
 PEAK_INT32_TOPS = 256 * 64 * 2.4e9 / 1e12
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "ungapped_persistent_cfg1_traffic.md")
-KERNEL_SRC = os.path.join(ROOT, "paper_0804_3643_amd", "csrc", "ungapped.hip")
-MFMA_SRC = os.path.join(ROOT, "paper_0804_3643_amd", "csrc", "ungapped_mfma.h")
+CSRC = os.path.join(ROOT, "paper_0804_3643_amd", "csrc")
+# sources of the ungapped extension's kernels, and of the gapped filter's
+UNGAPPED_SRC = [os.path.join(CSRC, f) for f in ("ungapped.hip", "ungapped_mfma.h", "ungapped_route.h", "ungapped_wave.h")]
+GAPPED_SRC = [os.path.join(CSRC, "gapped.hip")]
+UNGAPPED_KERNELS = ("k_ungapped_mfma", "k_ungapped_persistent<true>", "k_ungapped_persistent<false>",
+                    "k_ungapped_wave<true>", "k_ungapped_wave<false>")
 
 
 def log(msg):
     print("[bench] " + msg, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash(src=KERNEL_SRC):
-    with open(src, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def kernel_source_hash(src=UNGAPPED_SRC):
+    h = hashlib.sha256()
+    for name in [src] if isinstance(src, str) else src:
+        with open(name, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
-def recorded_traffic(path, src=KERNEL_SRC, key="traffic_bytes_per_launch"):
+def ungapped_kernel(torch, ext):
+    """The kernel that the library chose for an extension call, as its workspace's header says."""
+    return UNGAPPED_KERNELS[ext.ws[64:76].view(torch.int32).tolist()[2]]
+
+
+def ungapped_roofline(kernel, n_ext, ms, peaks):
+    """The ungapped extension's rate against what bounds its kernel: on the matrix cores the MFMAs' peak, on the VALU the
+    packed 16-bit one.  On the matrix cores the additions are the MFMAs' and a three-way maximum takes four prefixes, so
+    a pair is not 88 VALU operations there and no fraction of the VALU's peak is given."""
+    rate = n_ext / (ms * 1e-3) / 1e12
+    if kernel == "k_ungapped_mfma":
+        return {"bound": "mfma", "achieved": rate * MFMA_FLOPS_PER_EXT, "peak": PEAK_F6F4_TFLOPS, "unit": "TFLOP/s",
+                "frac": rate * MFMA_FLOPS_PER_EXT / PEAK_F6F4_TFLOPS, "flops_per_ext": MFMA_FLOPS_PER_EXT,
+                "note": "22 v_mfma_f32_32x32x64_f8f6f4 per 1024 pairs, padding not counted; with them go 176 "
+                        "v_max3_f32, which share the SIMD's issue"}
+    alu = rate * OPS_PER_EXT
+    lds = rate * LDS_BYTES_PER_EXT
+    return {"bound": "alu", "achieved": alu, "peak": PEAK_INT16_TOPS, "unit": "TOP/s", "frac": alu / PEAK_INT16_TOPS,
+            "ops_per_ext": OPS_PER_EXT, "measured_peak": peaks["valu_pk_f16"]["rate"] / 1e12,
+            "frac_of_measured_peak": alu / (peaks["valu_pk_f16"]["rate"] / 1e12),
+            "note": "88 algorithmic operations per extension (44 additions, 44 maxima) against 2 packed 16-bit "
+                    "operations per lane per clock; a three-way maximum serves two steps",
+            "lds": {"bound": "lds", "achieved": lds, "peak": PEAK_LDS_TBS, "unit": "TB/s", "frac": lds / PEAK_LDS_TBS,
+                    "bytes_per_ext": LDS_BYTES_PER_EXT, "measured_peak": peaks["lds_b64"]["rate"] / 1e12,
+                    "frac_of_measured_peak": lds / (peaks["lds_b64"]["rate"] / 1e12),
+                    "note": "profile lookups: 44 scores of 2 bytes per pair, read 4 rows at a time with "
+                            "ds_read_b64, against 256 B per CU per clock"}}
+
+
+def recorded_traffic(path, src=UNGAPPED_SRC, key="traffic_bytes_per_launch"):
     """HBM bytes per launch of a kernel from a committed rocprofv3 counter
     summary, if it was taken on the current kernel source (``key`` names the
     figure, e.g. the one for a given workgroup size)."""
@@ -587,6 +619,7 @@ def run_translated(args, plastx=False):
         tuning, _ = B.autotune(ia, ib, params.S1, params.S2, reps=args.tune_reps)
     ext = B.Extender(ia, ib, params.S1, mode="batched", tuning=tuning)
     hits, n_ext = ext.run()
+    kernel = ungapped_kernel(torch, ext)
     cap = ext.hits.shape[0]
     gbuf = torch.empty(cap, dtype=torch.int32, device=dev)
     pbuf = torch.empty(cap, dtype=torch.uint8, device=dev)
@@ -967,8 +1000,6 @@ def main():
     log("measured peaks")
     peaks = measured_peaks(B, torch, dev)
 
-    achieved = n_ext * OPS_PER_EXT / (batched_kernel_ms * 1e-3) / 1e12
-    lds_achieved = n_ext * LDS_BYTES_PER_EXT / (batched_kernel_ms * 1e-3) / 1e12
     gapped_threads = (tuning if tuning is not None else B.tuning_default()).as_dict()["gapped_threads"]
     gapped_kernel_ms = float(np.mean(stage_ms["gapped_ms"]))
     h_host = host_b[0].numpy()
@@ -1021,42 +1052,15 @@ def main():
         "bank_vs_bank_wall_s": {"batched": wall_b, "plain": wall_p},
         "bit_exact": {"plain_equals_batched": plain_eq, "no_duplicate_pairs": no_dups,
                       "graph_equals_eager": graph_eq},
-        "roofline": {
-            "bound": "alu", "achieved": achieved, "peak": PEAK_INT16_TOPS, "unit": "TOP/s",
-            "frac": achieved / PEAK_INT16_TOPS,
-            "traffic": recorded_traffic(traffic_file("ungapped_mfma", args.config), MFMA_SRC),
-            "kernel": "k_ungapped_mfma" if w.bank1.codes.shape[0] >= MFMA_MIN_CODES else "k_ungapped_wave",
-            "ops_per_ext": OPS_PER_EXT,
-            "kernel_ms": batched_kernel_ms, "extensions_per_launch": n_ext,
-            "measured_peak": peaks["valu_pk_f16"]["rate"] / 1e12,
-            "frac_of_measured_peak": achieved / (peaks["valu_pk_f16"]["rate"] / 1e12),
-            "note": "88 algorithmic operations per extension (44 additions, 44 maxima) against 2 packed "
-                    "16-bit operations per lane per clock; the additions are done by the matrix cores and a "
-                    "three-way maximum takes four prefixes, so this fraction passes 1",
-            "matrix": {"bound": "mfma", "flops_per_ext": MFMA_FLOPS_PER_EXT,
-                       "achieved": achieved / OPS_PER_EXT * MFMA_FLOPS_PER_EXT, "peak": PEAK_F6F4_TFLOPS,
-                       "unit": "TFLOP/s", "frac": achieved / OPS_PER_EXT * MFMA_FLOPS_PER_EXT / PEAK_F6F4_TFLOPS,
-                       "note": "22 v_mfma_f32_32x32x64_f8f6f4 per 1024 pairs, padding not counted; with them go 176 "
-                               "v_max3_f32, which share the SIMD's issue"},
-            "with_lookups_as_alu_ops": {
-                "ops_per_ext": OPS_PER_EXT_WITH_LOOKUPS,
-                "achieved": achieved * OPS_PER_EXT_WITH_LOOKUPS / OPS_PER_EXT,
-                "frac": achieved * OPS_PER_EXT_WITH_LOOKUPS / OPS_PER_EXT / PEAK_INT16_TOPS,
-                "note": "counts the 44 substitution lookups per pair as ALU operations; the matrix cores' operands "
-                        "or the LDS serve them, so this fraction exceeds 1"},
-            "lds": {"bound": "lds", "achieved": lds_achieved, "peak": PEAK_LDS_TBS, "unit": "TB/s",
-                    "frac": lds_achieved / PEAK_LDS_TBS, "bytes_per_ext": LDS_BYTES_PER_EXT,
-                    "measured_peak": peaks["lds_b64"]["rate"] / 1e12,
-                    "frac_of_measured_peak": lds_achieved / (peaks["lds_b64"]["rate"] / 1e12),
-                    "note": "profile lookups of the VALU tiles: 44 scores of 2 bytes per pair, read 4 rows at a time "
-                            "with ds_read_b64, against 256 B per CU per clock"},
-            "gapped": {"bound": "alu", "kernel": "k_gapped_f16", "achieved": gapped_achieved,
-                       "peak": PEAK_INT16_TOPS, "unit": "TOP/s", "frac": gapped_achieved / PEAK_INT16_TOPS,
-                       "kernel_ms": gapped_kernel_ms, "dp_cells": cells, "ops_per_cell": GAPPED_OPS_PER_CELL,
-                       "traffic": recorded_traffic(traffic_file("gapped", args.config),
-                                                   os.path.join(ROOT, "paper_0804_3643_amd", "csrc", "gapped.hip"),
-                                                   "traffic_bytes_per_launch_threads_%d" % gapped_threads)},
-        },
+        "roofline": dict(
+            ungapped_roofline(kernel, n_ext, batched_kernel_ms, peaks),
+            traffic=recorded_traffic(traffic_file(kernel[2:].split("<")[0], args.config)),
+            kernel=kernel, kernel_ms=batched_kernel_ms, extensions_per_launch=n_ext,
+            gapped={"bound": "alu", "kernel": "k_gapped_f16", "achieved": gapped_achieved,
+                    "peak": PEAK_INT16_TOPS, "unit": "TOP/s", "frac": gapped_achieved / PEAK_INT16_TOPS,
+                    "kernel_ms": gapped_kernel_ms, "dp_cells": cells, "ops_per_cell": GAPPED_OPS_PER_CELL,
+                    "traffic": recorded_traffic(traffic_file("gapped", args.config), GAPPED_SRC,
+                                                "traffic_bytes_per_launch_threads_%d" % gapped_threads)}),
         "cpu_baseline": None,
         "stage32": stage32,
         "plant_recall": recall,
