@@ -619,7 +619,6 @@ def run_translated(args, plastx=False):
         tuning, _ = B.autotune(ia, ib, params.S1, params.S2, reps=args.tune_reps)
     ext = B.Extender(ia, ib, params.S1, mode="batched", tuning=tuning)
     hits, n_ext = ext.run()
-    kernel = ungapped_kernel(torch, ext)
     cap = ext.hits.shape[0]
     gbuf = torch.empty(cap, dtype=torch.int32, device=dev)
     pbuf = torch.empty(cap, dtype=torch.uint8, device=dev)
@@ -853,6 +852,7 @@ def main():
         log("tuned: %s (%.1f s)" % (tuning.as_dict(), tune_s))
     ext = B.Extender(ia, ib, params.S1, mode="batched", tuning=tuning)
     hits, n_ext = ext.run()
+    kernel = ungapped_kernel(torch, ext)
     cap = ext.hits.shape[0]
     gbuf = torch.empty(cap, dtype=torch.int32, device=dev)
     pbuf = torch.empty(cap, dtype=torch.uint8, device=dev)
