@@ -1,6 +1,7 @@
-"""GPU test of the gapped filter at every band: the packed kernel is compiled for
-bands of 4, 8, 12 and 16 and masks the ones between; scores equal the oracle's
-exactly, with gaps cheap enough that the best paths run along the band's edges."""
+"""GPU test of the gapped filter at every band: the packed kernel has band 16 alone,
+the general one is compiled for the even bands and masks the outermost cells of the
+ones between; scores equal the oracle's exactly, with gaps cheap enough that the best
+paths run along the band's edges."""
 import numpy as np
 import pytest
 import torch
